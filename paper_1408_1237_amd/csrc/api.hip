@@ -277,7 +277,7 @@ static int kmvp_single(const krr_points *pts, int kernel, double sigma, double s
     if (L.total > ws_bytes) return KRR_EWORKSPACE;
     L = carve(ws, pts->n, pts->d, o, K_MVP);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    KRR_HIP_STATUS(prepare_points(L.P, pts->x, sigma, L.temp, L.temp_bytes, s, kernel));
+    KRR_HIP_STATUS(prepare_points(L.P, pts->x, sigma, L.temp, L.temp_bytes, s, kernel, prep_need(prec)));
     if (prec == KRR_FP64) {
         KRR_HIP_STATUS((gather_sorted<double, double>(L.P, static_cast<const double *>(q), static_cast<double *>(L.q), s)));
         if (tune) KRR_HIP_STATUS(kmvp_tune(L.P, prec, L.q, L.y, L.W.ksc, s));
@@ -332,7 +332,7 @@ int kmvp_gauss_multi(const krr_points *pts, double sigma, double shift, int32_t 
     if (L.total > ws_bytes) return KRR_EWORKSPACE;
     L = carve_multi(ws, pts->n, pts->d, nrhs);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    KRR_HIP_STATUS(prepare_points(L.P, pts->x, sigma, L.temp, L.temp_bytes, s));
+    KRR_HIP_STATUS(prepare_points(L.P, pts->x, sigma, L.temp, L.temp_bytes, s, KRR_KERNEL_GAUSS, prep_need(prec)));
     KRR_HIP_STATUS(kmvp_multi(L.P, prec, nrhs, shift, L.P.perm, Q, ldq, Y, ldy, L.scratch, s));
     return KRR_OK;
 }
@@ -350,8 +350,8 @@ static int kmvp_cross_impl(const krr_points *targets, const krr_points *sources,
     if (L.total > ws_bytes) return KRR_EWORKSPACE;
     L = carve_cross(ws, targets->n, sources->n, targets->d);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    KRR_HIP_STATUS(prepare_points(L.T, targets->x, sigma, L.temp, L.temp_bytes, s, kernel));
-    KRR_HIP_STATUS(prepare_points(L.S, sources->x, sigma, L.temp, L.temp_bytes, s, kernel));
+    KRR_HIP_STATUS(prepare_points(L.T, targets->x, sigma, L.temp, L.temp_bytes, s, kernel, prep_need(prec)));
+    KRR_HIP_STATUS(prepare_points(L.S, sources->x, sigma, L.temp, L.temp_bytes, s, kernel, prep_need(prec)));
     if (prec == KRR_FP64) {
         KRR_HIP_STATUS((gather_sorted<double, double>(L.S, static_cast<const double *>(q), static_cast<double *>(L.q), s)));
         KRR_HIP_STATUS(kmvp_cross_sorted(L.T, L.S, prec, L.q, L.y, L.ksc, s));
@@ -389,7 +389,7 @@ int kmvp_grad(const krr_points *pts, double sigma, double gamma, int32_t prec, c
     if (L.total > ws_bytes) return KRR_EWORKSPACE;
     L = carve_grad(ws, pts->n, pts->d);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    KRR_HIP_STATUS(prepare_points(L.P, pts->x, sigma, L.temp, L.temp_bytes, s));
+    KRR_HIP_STATUS(prepare_points(L.P, pts->x, sigma, L.temp, L.temp_bytes, s, KRR_KERNEL_GAUSS, prep_need(prec)));
     KRR_HIP_STATUS(kmvp_grad_run(L.P, prec, sigma, gamma, lam, w, gx, g_logsigma, g_loggamma, L.scratch, s));
     return KRR_OK;
 }
@@ -408,7 +408,8 @@ int cg_inner_solve(const krr_points *pts, double sigma, double shift, int32_t pr
     if (L.total > ws_bytes) return KRR_EWORKSPACE;
     L = carve(ws, pts->n, pts->d, o, K_INNER);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    KRR_HIP_STATUS(prepare_points(L.P, pts->x, sigma, L.temp, L.temp_bytes, s));
+    KRR_HIP_STATUS(prepare_points(L.P, pts->x, sigma, L.temp, L.temp_bytes, s, KRR_KERNEL_GAUSS,
+                                  PREP_FP64 | prep_need(prec)));  // the tuning times an FP64 product
     if (prec == KRR_FP64)
         KRR_HIP_STATUS((gather_sorted<double, double>(L.P, static_cast<const double *>(v), L.W.b, s)));
     else
@@ -434,7 +435,8 @@ static int solve_one(const krr_points *pts, double sigma, double gamma, const do
     Layout L = carve(nullptr, pts->n, pts->d, o, kind);
     if (L.total > ws_bytes) return KRR_EWORKSPACE;
     L = carve(ws, pts->n, pts->d, o, kind);
-    KRR_HIP_STATUS(prepare_points(L.P, pts->x, sigma, L.temp, L.temp_bytes, s, o.kernel));
+    KRR_HIP_STATUS(prepare_points(L.P, pts->x, sigma, L.temp, L.temp_bytes, s, o.kernel,
+                                  PREP_FP64 | prep_need(o.inner_prec)));
     int flags = 0;
     KRR_HIP_STATUS(hipMemcpyAsync(&flags, L.P.flags, sizeof(int), hipMemcpyDeviceToHost, s));
     KRR_HIP_STATUS(hipStreamSynchronize(s));

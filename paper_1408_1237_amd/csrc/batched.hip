@@ -868,6 +868,7 @@ int batch_setup(BatchRun &R, const krr_points *probs, int nprob, const double *s
                        B.col_mvp64, B.col_cycles, B.cand, B.restart, B.cg_iters};
     for (int *p : zero_int) hipLaunchKernelGGL(kb_fill_i, dim3(cb), dim3(BLOCK), 0, s, p, C, 0);
     BH(fill_d(B.est, C, 0.0, s));
+    const int inner_prec = (o.inner_prec == KRR_BF16) ? KRR_BF16 : KRR_FP32;
 
     // prepare every system; gather its right-hand sides; x = 0
     for (int k = 0; k < nprob; ++k) {
@@ -875,7 +876,8 @@ int batch_setup(BatchRun &R, const krr_points *probs, int nprob, const double *s
         S.sigma = sigma[k];
         S.gamma = gamma[k];
         S.delta = o.delta >= 0 ? o.delta : (gamma[k] > 0 ? 10 * gamma[k] : 1e-3);
-        BH(prepare_points(S.P, probs[k].x, sigma[k], L.temp, L.temp_bytes, s));
+        BH(prepare_points(S.P, probs[k].x, sigma[k], L.temp, L.temp_bytes, s, KRR_KERNEL_GAUSS,
+                          PREP_FP64 | prep_need(inner_prec)));
         int flag = 0;
         BH(hipMemcpyAsync(&flag, S.P.flags, sizeof(int), hipMemcpyDeviceToHost, s));
         BH(hipStreamSynchronize(s));
@@ -886,7 +888,6 @@ int batch_setup(BatchRun &R, const krr_points *probs, int nprob, const double *s
                            Rp, Y[k], ld, L.b + S.base);
     }
     BH(fill_d(L.x, L.L, 0.0, s));
-    const int inner_prec = (o.inner_prec == KRR_BF16) ? KRR_BF16 : KRR_FP32;
 
     // systems grouped by compiled dimension, largest first inside a class
     std::vector<int> order(nprob);

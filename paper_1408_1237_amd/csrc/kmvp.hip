@@ -2750,7 +2750,7 @@ KmvpScratch carve_kmvp_scratch(Carver &cv, const Prepared &P) {
 // the rest the VALU kernels.
 // KRR_KMVP_VALU=1 forces the VALU kernel and KRR_KMVP_MG32=1 the FP32
 // matrix-core form for FP32 / BF16 (both used to cross-check the kernels).
-static bool use_valu_kernel() {
+bool use_valu_kernel() {
     const char *v = std::getenv("KRR_KMVP_VALU");
     return v && v[0] == '1';
 }

@@ -168,8 +168,15 @@ Prepared carve_prepared(Carver &cv, int64_t n, int d);
 // prep_temp_bytes(n).  Returns a HIP error code.
 // sigma: the Gaussian bandwidth, or the Matern length scale h (kernel ==
 // KRR_KERNEL_MATERN32: coordinates scaled by sqrt(3) / h).
+// need: the precisions whose offsets, weights and slots are written (prep_need;
+// the others' arrays stay as they were).
+constexpr int PREP_FP64 = 1, PREP_FP32 = 2, PREP_BF16 = 4;
+constexpr int PREP_PM = 8;  // the point-major copies, all precisions (set by prepare_points itself)
+constexpr int prep_need(int prec) { return prec == KRR_FP64 ? PREP_FP64 : prec == KRR_FP32 ? PREP_FP32 : PREP_BF16; }
 hipError_t prepare_points(Prepared &P, const double *x, double sigma, void *temp, size_t temp_bytes,
-                          hipStream_t s, int kernel = KRR_KERNEL_GAUSS);
+                          hipStream_t s, int kernel, int need);
+// KRR_KMVP_VALU=1: products take the VALU kernels (kmvp.hip).
+bool use_valu_kernel();
 
 // Gather an original-order vector into sorted order (padding 0), and back.
 template <typename Tin, typename Tout>

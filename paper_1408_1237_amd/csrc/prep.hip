@@ -11,6 +11,9 @@
 
 namespace krr {
 
+constexpr int BBOX_BLOCKS = 64;  // slices of the bounding box pass (one lane each in k_morton)
+constexpr int BBOX_THREADS = 1024;
+
 static const int kDims[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64};
 
 int dim_instance(int d) {
@@ -68,8 +71,8 @@ size_t prep_temp_bytes(int64_t n) {
     cv.take<uint64_t>(n);
     cv.take<int32_t>(n);
     cv.take<int32_t>(n);
-    cv.take<double>(2 * KRR_MAX_DIM * 1024);
-    cv.take<double>(2 * KRR_MAX_DIM);
+    cv.take<double>(2 * KRR_MAX_DIM * BBOX_BLOCKS);
+    cv.take<int>(KRR_MAX_DIM * BBOX_BLOCKS);
     cv.take<char>(sort_scratch_bound(n));
     return cv.off + 256;
 }
@@ -89,59 +92,87 @@ __device__ T block_reduce(T v, Op op, T *lds /* >= BLOCK/WAVE */) {
     return r;
 }
 
-struct MinOp { __device__ double operator()(double a, double b) const { return fmin(a, b); } };
 struct MaxOp { __device__ double operator()(double a, double b) const { return fmax(a, b); } };
 
 // ---------------------------------------------------------------- kernels
 
-// Per-block min / max of the scaled coordinate t over a slice of points
-// (grid: nblk x d); part[(t * 2 + 0|1) * nblk + blk].  Flags non-finite input.
-__global__ __launch_bounds__(BLOCK) void k_bbox_partial(const double *__restrict__ x, int64_t n, int d,
-                                                        double scale, double *part, int *flags) {
-    __shared__ double lds[BLOCK / WAVE];
+// Bounding box, first half: block (blk, t) takes the min / max of the scaled
+// coordinate t over its slice of the points; part[(t * 2 + 0|1) * nblk + blk].
+// bad[t * nblk + blk]: a non-finite coordinate in the slice.  The few partials
+// (at most BBOX_BLOCKS per coordinate) are combined by every block of k_morton,
+// which takes the place of a kernel whose one thread per coordinate walked up to
+// 1024 of them (N = 1e5, d = 3: 55 us; with the fill of the flags, three launches
+// became one).
+__global__ __launch_bounds__(BBOX_THREADS) void k_bbox_partial(const double *__restrict__ x, int64_t n, int d,
+                                                               double scale, double *part, int *bad) {
+    __shared__ double s_lo[BBOX_THREADS / WAVE], s_hi[BBOX_THREADS / WAVE];
     const int t = blockIdx.y;
     const int nblk = gridDim.x;
     double lo = INFINITY, hi = -INFINITY;
-    int bad = 0;
-    for (int64_t i = blockIdx.x * (int64_t)BLOCK + threadIdx.x; i < n; i += (int64_t)nblk * BLOCK) {
+    int nf = 0;
+#pragma unroll 4
+    for (int64_t i = blockIdx.x * static_cast<int64_t>(BBOX_THREADS) + threadIdx.x; i < n;
+         i += static_cast<int64_t>(nblk) * BBOX_THREADS) {
         double v = x[i * d + t];
-        if (!isfinite(v)) bad = 1;
+        nf |= isfinite(v) ? 0 : 1;
         v *= scale;
         lo = fmin(lo, v);
         hi = fmax(hi, v);
     }
-    if (bad) atomicOr(flags, 1);
-    lo = block_reduce(lo, MinOp(), lds);
-    hi = block_reduce(hi, MaxOp(), lds);
+#pragma unroll
+    for (int off = WAVE / 2; off > 0; off /= 2) {
+        lo = fmin(lo, __shfl_xor(lo, off, WAVE));
+        hi = fmax(hi, __shfl_xor(hi, off, WAVE));
+    }
+    if (threadIdx.x % WAVE == 0) {
+        s_lo[threadIdx.x / WAVE] = lo;
+        s_hi[threadIdx.x / WAVE] = hi;
+    }
+    nf = __syncthreads_or(nf);
     if (threadIdx.x == 0) {
+        for (int w = 1; w < BBOX_THREADS / WAVE; ++w) {
+            lo = fmin(lo, s_lo[w]);
+            hi = fmax(hi, s_hi[w]);
+        }
         part[(t * 2 + 0) * nblk + blockIdx.x] = lo;
         part[(t * 2 + 1) * nblk + blockIdx.x] = hi;
+        bad[t * nblk + blockIdx.x] = nf;
     }
-}
-
-__global__ void k_bbox_final(const double *part, int nblk, int d, double *bbox) {
-    const int t = threadIdx.x;
-    if (t >= d) return;
-    double lo = INFINITY, hi = -INFINITY;
-    for (int b = 0; b < nblk; ++b) {
-        lo = fmin(lo, part[(t * 2 + 0) * nblk + b]);
-        hi = fmax(hi, part[(t * 2 + 1) * nblk + b]);
-    }
-    bbox[2 * t] = lo;
-    bbox[2 * t + 1] = hi;
 }
 
 // Morton code: the first dm = min(d, 63) scaled coordinates quantised to
 // bits = min(63 / dm, 31) bits each over the bounding box, bits interleaved.
+// Every block combines the box partials itself (one wave per coordinate bound;
+// min and max do not depend on the order); block 0 also stores the flags.
 __global__ __launch_bounds__(BLOCK) void k_morton(const double *__restrict__ x, int64_t n, int d, double scale,
-                                                  const double *__restrict__ bbox, int dm, int bits,
-                                                  uint64_t *keys, int32_t *vals) {
+                                                  const double *__restrict__ part, const int *__restrict__ bad,
+                                                  int nblk, int dm, int bits, uint64_t *keys, int32_t *vals,
+                                                  int *flags) {
+    __shared__ double s_box[2 * KRR_MAX_DIM];
+    const int wv = threadIdx.x / WAVE, lane = threadIdx.x % WAVE;
+    for (int b = wv; b < 2 * dm; b += BLOCK / WAVE) {
+        const bool mx = b & 1;
+        double v = lane < nblk ? part[b * nblk + lane] : (mx ? -INFINITY : INFINITY);
+#pragma unroll
+        for (int off = WAVE / 2; off > 0; off /= 2) {
+            const double u = __shfl_xor(v, off, WAVE);
+            v = mx ? fmax(v, u) : fmin(v, u);
+        }
+        if (lane == 0) s_box[b] = v;
+    }
+    if (blockIdx.x == 0) {
+        int nf = 0;
+        for (int k = threadIdx.x; k < d * nblk; k += BLOCK) nf |= bad[k];
+        nf = __syncthreads_or(nf);
+        if (threadIdx.x < 4) flags[threadIdx.x] = threadIdx.x == 0 && nf ? 1 : 0;
+    }
+    __syncthreads();
     const int64_t i = blockIdx.x * (int64_t)BLOCK + threadIdx.x;
     if (i >= n) return;
     const double qmax = static_cast<double>((uint64_t(1) << bits) - 1);
     uint64_t code = 0;
     for (int t = 0; t < dm; ++t) {
-        const double lo = bbox[2 * t], hi = bbox[2 * t + 1];
+        const double lo = s_box[2 * t], hi = s_box[2 * t + 1];
         const double ext = hi - lo;
         double f = ext > 0 ? (x[i * d + t] * scale - lo) / ext : 0.0;
         f = fmin(fmax(f, 0.0), 1.0);
@@ -152,7 +183,50 @@ __global__ __launch_bounds__(BLOCK) void k_morton(const double *__restrict__ x, 
     vals[i] = static_cast<int32_t>(i);
 }
 
-// One block per tile: anchor, offsets, radius, normaliser and weights.
+// Sorted order of a small set by counting: the rank of a key is the number of
+// keys below it (ties by index: the stable order of the radix sort).  A block
+// ranks 64 keys, one per lane; its 16 waves share the comparisons by chunks of
+// 64 keys, read at wave-uniform addresses (scalar loads), two VALU operations
+// per comparison.  One launch in place of four to eight.
+constexpr int RANK_THREADS = 1024;
+constexpr int64_t RANK_MAX_N = 8192;
+__global__ __launch_bounds__(RANK_THREADS) void k_rank(const uint64_t *__restrict__ keys, int n, int32_t *order) {
+    constexpr int NW = RANK_THREADS / WAVE;
+    __shared__ int s_cnt[NW][WAVE];
+    const int lane = threadIdx.x % WAVE;
+    const int wv = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / WAVE);
+    const int i = blockIdx.x * WAVE + lane;
+    const uint64_t key = i < n ? keys[i] : 0;
+    int cnt = 0;
+    for (int c = wv; c * WAVE < n; c += NW) {
+        const uint64_t *kc = keys + c * WAVE;
+        const int m = min(WAVE, n - c * WAVE);
+        if (c == static_cast<int>(blockIdx.x)) {
+            for (int u = 0; u < m; ++u) cnt += kc[u] < key || (kc[u] == key && u < lane) ? 1 : 0;
+        } else {
+            // before this block's keys: equal keys come first (key + 1 <= 2^63)
+            const uint64_t lim = c < static_cast<int>(blockIdx.x) ? key + 1 : key;
+            if (m == WAVE) {
+#pragma unroll 16
+                for (int u = 0; u < WAVE; ++u) cnt += kc[u] < lim ? 1 : 0;
+            } else {
+                for (int u = 0; u < m; ++u) cnt += kc[u] < lim ? 1 : 0;
+            }
+        }
+    }
+    s_cnt[wv][lane] = cnt;
+    __syncthreads();
+    if (threadIdx.x < WAVE && i < n) {
+        int r = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) r += s_cnt[w][threadIdx.x];
+        order[r] = i;
+    }
+}
+
+// One block per tile: anchor, offsets, radius, normaliser and weights, and the
+// slot vectors (split16.h) of the FP32 and BF16 offsets, in the precisions of
+// `need` (a product call uses one of the three).
 //
 // The anchor is the centre of the tile's bounding box, which minimises the
 // largest offset, whenever that keeps the tile narrow enough to fold its
@@ -162,160 +236,199 @@ __global__ __launch_bounds__(BLOCK) void k_morton(const double *__restrict__ x, 
 // offsets then stay short and keep their absolute precision when rounded to
 // FP32 or BF16 (with the box centre the group's offsets would be as long as the
 // tile, and its pairs' distances would carry that rounding).
-__global__ __launch_bounds__(TILE) void k_tiles(const double *__restrict__ x, int64_t n, int d, int dpad,
-                                                double scale, const int32_t *__restrict__ sorted_idx,
-                                                Prepared P, int matern) {
+//
+// What bounds it is latency: a point's coordinates stay in registers (one read),
+// the box goes through LDS 16 coordinates at a time with 16 lanes per
+// coordinate, and the medians (256 comparisons per point and coordinate) are
+// ranked on the wide tiles alone.  Ranking every tile and reducing the box one
+// coordinate at a time took 805 us at N = 44,484, d = 41 and 155 us at
+// N = 50,021, d = 8, beside products of 749 and 430 us.
+//
+// Slots.  Gaussian: the offsets o and no source constant.  Matern: o' = log2(e) o
+// and the constant |o'|^2, so that the product forms (log2(e) r)^2.
+template <int D, bool BF, bool MAT>
+__device__ __forceinline__ void store_slots(const Prepared &P, int64_t j, const float (&of)[D]) {
+    constexpr int KC = split_chunks(D);
+    if constexpr (KC > 0) {
+        HiLo v[D];
+        double so = 0.0;
+#pragma unroll
+        for (int k = 0; k < D; ++k) {
+            float o = of[k];
+            if (MAT) {
+                o *= LOG2E_F;
+                so = __builtin_fma(static_cast<double>(o), static_cast<double>(o), so);
+            }
+            v[k] = split_f16(o);
+        }
+        const HiLo one{static_cast<_Float16>(1.f), static_cast<_Float16>(1.f)};
+        const HiLo zero{static_cast<_Float16>(0.f), static_cast<_Float16>(0.f)};
+        const HiLo e = MAT ? split_f16(static_cast<float>(so)) : zero;
+        half8_t *out = static_cast<half8_t *>(BF ? P.slot16 : P.slot32);
+#pragma unroll
+        for (int w = 0; w < 2 * KC; ++w) out[w * P.n_pad + j] = slot_octet<D, true>(w, v, one, e);
+    }
+}
+
+template <int D, bool MAT>
+__global__ __launch_bounds__(TILE) void k_tiles(const double *__restrict__ x, int64_t n, int d, double scale,
+                                                const int32_t *__restrict__ sorted_idx, Prepared P, int need) {
+    constexpr int CH = D < 16 ? D : 16;  // coordinates per pass of the box
+    constexpr int LANES = 16;            // lanes per coordinate
+    __shared__ double s_v[CH][TILE + 4];
+    __shared__ double s_lo[D], s_hi[D], s_median[D];
     __shared__ double lds[TILE / WAVE];
-    __shared__ double vals[TILE];
-    __shared__ double s_centre[KRR_MAX_DIM];
-    __shared__ double s_median[KRR_MAX_DIM];
-    const int J = blockIdx.x;
-    const int64_t j = static_cast<int64_t>(J) * TILE + threadIdx.x;
+    const int J = blockIdx.x, tid = threadIdx.x;
+    const int64_t j = static_cast<int64_t>(J) * TILE + tid;
     const bool real = j < n;
     const int32_t idx = real ? sorted_idx[j] : -1;
     const int64_t t0 = static_cast<int64_t>(J) * TILE;
     const int nreal = static_cast<int>(n - t0 < TILE ? n - t0 : TILE);  // real points come first in a tile
     P.perm[j] = idx;
-    auto coord = [&](int t) { return (real && t < d) ? x[static_cast<int64_t>(idx) * d + t] * scale : 0.0; };
-    // pass 1: both candidate anchors, and the radius about the box centre
-    double sqc = 0.0;
-    for (int t = 0; t < d; ++t) {
-        const double v = coord(t);
-        const double lo = block_reduce(real ? v : INFINITY, MinOp(), lds);
-        const double hi = block_reduce(real ? v : -INFINITY, MaxOp(), lds);
-        const double c = 0.5 * (lo + hi);
-        // rank of this point's coordinate among the tile's real points (ties by
-        // position); the point of rank (nreal - 1) / 2 is the median
-        vals[threadIdx.x] = v;
-        if (threadIdx.x == 0) {
-            s_centre[t] = c;
-            s_median[t] = c;  // replaced below (kept only if a non-finite value breaks the ranks)
+    double xr[D];  // the point's coordinates, unscaled (0 beyond d and on the padding)
+#pragma unroll
+    for (int t = 0; t < D; ++t) xr[t] = (real && t < d) ? x[static_cast<int64_t>(idx) * d + t] : 0.0;
+#pragma unroll
+    for (int c0 = 0; c0 < D; c0 += CH) {
+#pragma unroll
+        for (int k = 0; k < CH; ++k)
+            if (c0 + k < D) s_v[k][tid] = real ? xr[c0 + k] * scale : NAN;  // fmin / fmax pass a NaN over
+        __syncthreads();
+        const int k = tid / LANES, part = tid % LANES;
+        if (k < CH && c0 + k < D) {
+            double lo = INFINITY, hi = -INFINITY;
+#pragma unroll
+            for (int i = 0; i < TILE / LANES; ++i) {
+                const double v = s_v[k][i * LANES + part];
+                lo = fmin(lo, v);
+                hi = fmax(hi, v);
+            }
+#pragma unroll
+            for (int off = LANES / 2; off > 0; off /= 2) {
+                lo = fmin(lo, __shfl_xor(lo, off, WAVE));
+                hi = fmax(hi, __shfl_xor(hi, off, WAVE));
+            }
+            if (part == 0) {
+                s_lo[c0 + k] = lo;
+                s_hi[c0 + k] = hi;
+            }
         }
         __syncthreads();
-        if (real) {
-            int rank = 0;
-            for (int k = 0; k < nreal; ++k) {
-                const double u = vals[k];
-                rank += (u < v || (u == v && k < static_cast<int>(threadIdx.x))) ? 1 : 0;
-            }
-            if (rank == (nreal - 1) / 2) s_median[t] = v;
-        }
-        __syncthreads();  // vals is rewritten for the next coordinate
-        const double o = real ? v - c : 0.0;
-        sqc += o * o;
+    }
+    // the radius about the box centre decides between the two anchors
+    double sqc = 0.0;
+#pragma unroll
+    for (int t = 0; t < D; ++t) {
+        const double o = (real && t < d) ? __builtin_fma(xr[t], scale, -0.5 * (s_lo[t] + s_hi[t])) : 0.0;
+        sqc = __builtin_fma(o, o, sqc);
     }
     const bool median = block_reduce(sqc, MaxOp(), lds) > WIDE_R2_FP32;
-    // pass 2: offsets from the chosen anchor (padding coordinates are zero)
-    double sq64 = 0.0, sq32 = 0.0, sq16 = 0.0;
-    for (int t = 0; t < dpad; ++t) {
-        const double a = t < d ? (median ? s_median[t] : s_centre[t]) : 0.0;
-        const double o = real ? coord(t) - a : 0.0;
-        const float o32 = static_cast<float>(o);
-        if (threadIdx.x == 0) P.anchor[static_cast<size_t>(J) * dpad + t] = a;
-        P.off64[t * P.n_pad + j] = o;
-        P.off32[t * P.n_pad + j] = o32;
-        if (P.pm64 != nullptr) {
-            P.pm64[j * dpad + t] = o;
-            P.pm32[j * dpad + t] = o32;
+    if (median) {
+        // rank of this point's coordinate among the tile's real points (ties by
+        // position); the point of rank (nreal - 1) / 2 is the median
+#pragma unroll 1
+        for (int t = 0; t < d; ++t) {
+            const double v = real ? x[static_cast<int64_t>(idx) * d + t] * scale : 0.0;
+            s_v[0][tid] = v;
+            if (tid == 0) s_median[t] = 0.5 * (s_lo[t] + s_hi[t]);  // kept if a non-finite value breaks the ranks
+            __syncthreads();
+            if (real) {
+                int rank = 0;
+                for (int k = 0; k < nreal; ++k) {
+                    const double u = s_v[0][k];
+                    rank += (u < v || (u == v && k < tid)) ? 1 : 0;
+                }
+                if (rank == (nreal - 1) / 2) s_median[t] = v;
+            }
+            __syncthreads();  // s_v is rewritten for the next coordinate
         }
-        sq64 += o * o;
-        sq32 += static_cast<double>(o32) * static_cast<double>(o32);
     }
-    // offsets of the BF16 products: rounded to BF16 on a compact tile (this
-    // thread reads back the FP32 offsets it wrote)
+    // offsets from the chosen anchor (padding coordinates and points are zero)
+    double sq64 = 0.0, sq32 = 0.0, sq16 = 0.0;
+    float of[D];
+#pragma unroll
+    for (int t = 0; t < D; ++t) {
+        const double a = t < d ? (median ? s_median[t] : 0.5 * (s_lo[t] + s_hi[t])) : 0.0;
+        const double o = (real && t < d) ? __builtin_fma(xr[t], scale, -a) : 0.0;
+        of[t] = static_cast<float>(o);
+        if (tid == 0) P.anchor[static_cast<size_t>(J) * D + t] = a;
+        if (need & PREP_FP64) P.off64[t * P.n_pad + j] = o;
+        if (need & PREP_FP32) P.off32[t * P.n_pad + j] = of[t];
+        if constexpr (D > 16) {
+            if (need & PREP_PM) {
+                P.pm64[j * D + t] = o;
+                P.pm32[j * D + t] = of[t];
+            }
+        }
+        sq64 = __builtin_fma(o, o, sq64);
+        sq32 = __builtin_fma(static_cast<double>(of[t]), static_cast<double>(of[t]), sq32);
+    }
+    if (need & PREP_FP32) store_slots<D, false, MAT>(P, j, of);
+    // offsets of the BF16 products: rounded to BF16 on a compact tile
     const bool compact = block_reduce(sq64, MaxOp(), lds) <= COMPACT_R2_BF16;
-    for (int t = 0; t < dpad; ++t) {
-        const float o32 = P.off32[t * P.n_pad + j];
-        const float ob = compact ? bf16_to_f32(f32_to_bf16_rne(o32)) : o32;
-        P.offb[t * P.n_pad + j] = ob;
-        if (P.pmb != nullptr) P.pmb[j * dpad + t] = ob;
-        sq16 += static_cast<double>(ob) * static_cast<double>(ob);
+#pragma unroll
+    for (int t = 0; t < D; ++t) {
+        if (compact) of[t] = bf16_to_f32(f32_to_bf16_rne(of[t]));
+        if (need & PREP_BF16) P.offb[t * P.n_pad + j] = of[t];
+        if constexpr (D > 16) {
+            if (need & PREP_PM) P.pmb[j * D + t] = of[t];
+        }
+        sq16 = __builtin_fma(static_cast<double>(of[t]), static_cast<double>(of[t]), sq16);
     }
+    if (need & PREP_BF16) store_slots<D, true, MAT>(P, j, of);
     const double r2 = block_reduce(fmax(sq64, fmax(sq32, sq16)), MaxOp(), lds);
     const double nj = floor(0.5 * r2);
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
         P.tile_r2[J] = r2;
         P.tile_nj[J] = nj;
         // Gaussian: a target at |t| from the anchor has exponent
         // <= -(|t| - R)^2 + R^2 - N_J against every source of the tile, <= -200
         // beyond this |t|^2; Matern: scaled distance >= 111 (exp2 of -log2(e) s
         // is 0 in FP32) beyond (R + 111)^2; 1e-4 margin
-        const double u = matern ? sqrt(r2) + 111.0 : sqrt(r2) + sqrt(200.0 + r2 - nj);
+        const double u = MAT ? sqrt(r2) + 111.0 : sqrt(r2) + sqrt(200.0 + r2 - nj);
         P.tile_far[J] = static_cast<float>(1.0001 * u * u);
         // FP64 Gaussian product: exponents <= -1100 (exp2 is 0 in FP64)
         const double u64 = sqrt(r2) + sqrt(1100.0 + r2 - nj);
         P.tile_far64[J] = static_cast<float>(1.0001 * u64 * u64);
     }
-    P.sq64[j] = sq64;
-    P.w64[j] = (real && r2 <= WIDE_R2_FP64) ? exp2(nj - sq64) : 0.0;
-    P.w32[j] = (real && r2 <= WIDE_R2_FP32) ? static_cast<float>(exp2(nj - sq32)) : 0.0f;
-    P.w16[j] = (real && r2 <= WIDE_R2_FP32) ? static_cast<float>(exp2(nj - sq16)) : 0.0f;
-}
-
-// Source slot vectors (split16.h) of the FP32 or BF16 offsets, once per set.
-// Gaussian: the offsets o and no source constant.  Matern: o' = log2(e) o and
-// the constant |o'|^2, so that the product forms (log2(e) r)^2.
-template <int D, bool BF, bool MAT>
-__global__ __launch_bounds__(BLOCK) void k_slots(Prepared P) {
-    const int64_t j = blockIdx.x * static_cast<int64_t>(BLOCK) + threadIdx.x;
-    if (j >= P.n_pad) return;
-    constexpr int KC = split_chunks(D);
-    HiLo v[D];
-    double so = 0.0;
-#pragma unroll
-    for (int k = 0; k < D; ++k) {
-        float o = BF ? P.offb[k * P.n_pad + j] : P.off32[k * P.n_pad + j];
-        if (MAT) {
-            o *= LOG2E_F;
-            so = __builtin_fma(static_cast<double>(o), static_cast<double>(o), so);
-        }
-        v[k] = split_f16(o);
+    if (need & PREP_FP64) {
+        P.sq64[j] = sq64;
+        P.w64[j] = (real && r2 <= WIDE_R2_FP64) ? exp2(nj - sq64) : 0.0;
     }
-    const HiLo one{static_cast<_Float16>(1.f), static_cast<_Float16>(1.f)};
-    const HiLo zero{static_cast<_Float16>(0.f), static_cast<_Float16>(0.f)};
-    const HiLo e = MAT ? split_f16(static_cast<float>(so)) : zero;
-    half8_t *out = static_cast<half8_t *>(BF ? P.slot16 : P.slot32);
-#pragma unroll
-    for (int w = 0; w < 2 * KC; ++w) out[w * P.n_pad + j] = slot_octet<D, true>(w, v, one, e);
+    if (need & PREP_FP32) P.w32[j] = (real && r2 <= WIDE_R2_FP32) ? static_cast<float>(exp2(nj - sq32)) : 0.0f;
+    if (need & PREP_BF16) P.w16[j] = (real && r2 <= WIDE_R2_FP32) ? static_cast<float>(exp2(nj - sq16)) : 0.0f;
 }
 
 template <int D>
-static hipError_t launch_slots(const Prepared &P, hipStream_t s) {
-    const dim3 g((P.n_pad + BLOCK - 1) / BLOCK);
-    if (P.kernel == KRR_KERNEL_MATERN32) {
-        hipLaunchKernelGGL((k_slots<D, false, true>), g, dim3(BLOCK), 0, s, P);
-        hipLaunchKernelGGL((k_slots<D, true, true>), g, dim3(BLOCK), 0, s, P);
-    } else {
-        hipLaunchKernelGGL((k_slots<D, false, false>), g, dim3(BLOCK), 0, s, P);
-        hipLaunchKernelGGL((k_slots<D, true, false>), g, dim3(BLOCK), 0, s, P);
-    }
+static hipError_t launch_tiles(const Prepared &P, const double *x, const int32_t *order, int need, hipStream_t s) {
+    if (P.kernel == KRR_KERNEL_MATERN32)
+        hipLaunchKernelGGL((k_tiles<D, true>), dim3(P.ntiles), dim3(TILE), 0, s, x, P.n, P.d, P.scale, order, P, need);
+    else
+        hipLaunchKernelGGL((k_tiles<D, false>), dim3(P.ntiles), dim3(TILE), 0, s, x, P.n, P.d, P.scale, order, P,
+                           need);
     return hipGetLastError();
 }
 
-static hipError_t build_slots(const Prepared &P, hipStream_t s) {
+static hipError_t build_tiles(const Prepared &P, const double *x, const int32_t *order, int need, hipStream_t s) {
     switch (P.dpad) {
-        case 1: return launch_slots<1>(P, s);
-        case 2: return launch_slots<2>(P, s);
-        case 3: return launch_slots<3>(P, s);
-        case 4: return launch_slots<4>(P, s);
-        case 6: return launch_slots<6>(P, s);
-        case 8: return launch_slots<8>(P, s);
-        case 12: return launch_slots<12>(P, s);
-        case 16: return launch_slots<16>(P, s);
-        case 24: return launch_slots<24>(P, s);
-        case 32: return launch_slots<32>(P, s);
-        case 48: return launch_slots<48>(P, s);
-        default: return hipSuccess;  // d = 64 takes the VALU kernel
+        case 1: return launch_tiles<1>(P, x, order, need, s);
+        case 2: return launch_tiles<2>(P, x, order, need, s);
+        case 3: return launch_tiles<3>(P, x, order, need, s);
+        case 4: return launch_tiles<4>(P, x, order, need, s);
+        case 6: return launch_tiles<6>(P, x, order, need, s);
+        case 8: return launch_tiles<8>(P, x, order, need, s);
+        case 12: return launch_tiles<12>(P, x, order, need, s);
+        case 16: return launch_tiles<16>(P, x, order, need, s);
+        case 24: return launch_tiles<24>(P, x, order, need, s);
+        case 32: return launch_tiles<32>(P, x, order, need, s);
+        case 48: return launch_tiles<48>(P, x, order, need, s);
+        case 64: return launch_tiles<64>(P, x, order, need, s);
+        default: return hipErrorInvalidValue;
     }
 }
 
-__global__ void k_fill_int(int *p, int n, int v) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
-}
-
 hipError_t prepare_points(Prepared &P, const double *x, double sigma, void *temp, size_t temp_bytes,
-                          hipStream_t s, int kernel) {
+                          hipStream_t s, int kernel, int need) {
     const int64_t n = P.n;
     const int d = P.d;
     P.kernel = kernel;
@@ -323,38 +436,43 @@ hipError_t prepare_points(Prepared &P, const double *x, double sigma, void *temp
     // scaled distance ||x~_i - x~_j|| is sqrt(3) r / h
     P.scale = kernel == KRR_KERNEL_MATERN32 ? std::sqrt(3.0) / sigma
                                             : std::sqrt(std::log2(std::exp(1.0))) / (sigma * std::sqrt(2.0));
+    // the point-major copies feed the VALU cross-check kernels only
+    if (P.dpad > 16 && use_valu_kernel()) need |= PREP_PM;
     Carver cv(temp);
     uint64_t *k0 = cv.take<uint64_t>(n);
     uint64_t *k1 = cv.take<uint64_t>(n);
     int32_t *v0 = cv.take<int32_t>(n);
     int32_t *v1 = cv.take<int32_t>(n);
-    double *part = cv.take<double>(2 * KRR_MAX_DIM * 1024);
-    double *bbox = cv.take<double>(2 * KRR_MAX_DIM);
+    double *part = cv.take<double>(2 * KRR_MAX_DIM * BBOX_BLOCKS);
+    int *bad = cv.take<int>(KRR_MAX_DIM * BBOX_BLOCKS);
     const size_t sort_cap = sort_scratch_bound(n);
     char *sort_tmp = cv.take<char>(sort_cap);
     if (cv.off > temp_bytes) return hipErrorInvalidValue;
 
-    hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, s, P.flags, 4, 0);
-    const int nblk = static_cast<int>(std::min<int64_t>(1024, (n + BLOCK - 1) / BLOCK));
-    hipLaunchKernelGGL(k_bbox_partial, dim3(nblk, d), dim3(BLOCK), 0, s, x, n, d, P.scale, part, P.flags);
-    hipLaunchKernelGGL(k_bbox_final, dim3(1), dim3(KRR_MAX_DIM), 0, s, part, nblk, d, bbox);
+    const int nblk = static_cast<int>(std::min<int64_t>(BBOX_BLOCKS, (n + BBOX_THREADS - 1) / BBOX_THREADS));
+    hipLaunchKernelGGL(k_bbox_partial, dim3(nblk, d), dim3(BBOX_THREADS), 0, s, x, n, d, P.scale, part, bad);
     const int dm = d < 63 ? d : 63;
     const int bits = (63 / dm) < 31 ? 63 / dm : 31;
-    hipLaunchKernelGGL(k_morton, dim3((n + BLOCK - 1) / BLOCK), dim3(BLOCK), 0, s, x, n, d, P.scale, bbox, dm,
-                       bits, k0, v0);
+    hipLaunchKernelGGL(k_morton, dim3((n + BLOCK - 1) / BLOCK), dim3(BLOCK), 0, s, x, n, d, P.scale, part, bad, nblk,
+                       dm, bits, k0, v0, P.flags);
     KRR_HIP(hipGetLastError());
+    // counting ranks grows with n^2; measured against the radix sort it is ahead
+    // up to RANK_MAX_N
+    if (n <= RANK_MAX_N) {
+        hipLaunchKernelGGL(k_rank, dim3(static_cast<unsigned>((n + WAVE - 1) / WAVE)), dim3(RANK_THREADS), 0, s, k0,
+                           static_cast<int>(n), v1);
+        KRR_HIP(hipGetLastError());
+        return build_tiles(P, x, v1, need, s);
+    }
     rocprim::double_buffer<uint64_t> keys(k0, k1);
     rocprim::double_buffer<int32_t> vals(v0, v1);
-    size_t need = 0;
-    KRR_HIP(rocprim::radix_sort_pairs(nullptr, need, keys, vals, static_cast<size_t>(n), 0u,
+    size_t bytes = 0;
+    KRR_HIP(rocprim::radix_sort_pairs(nullptr, bytes, keys, vals, static_cast<size_t>(n), 0u,
                                       static_cast<unsigned>(dm * bits), s));
-    if (need > sort_cap) return hipErrorInvalidValue;
-    KRR_HIP(rocprim::radix_sort_pairs(sort_tmp, need, keys, vals, static_cast<size_t>(n), 0u,
+    if (bytes > sort_cap) return hipErrorInvalidValue;
+    KRR_HIP(rocprim::radix_sort_pairs(sort_tmp, bytes, keys, vals, static_cast<size_t>(n), 0u,
                                       static_cast<unsigned>(dm * bits), s));
-    hipLaunchKernelGGL(k_tiles, dim3(P.ntiles), dim3(TILE), 0, s, x, n, d, P.dpad, P.scale,
-                       static_cast<const int32_t *>(vals.current()), P, kernel == KRR_KERNEL_MATERN32 ? 1 : 0);
-    KRR_HIP(hipGetLastError());
-    return build_slots(P, s);
+    return build_tiles(P, x, static_cast<const int32_t *>(vals.current()), need, s);
 }
 
 // ---------------------------------------------------------------- gather / scatter
