@@ -8,7 +8,7 @@
 // n_pad_k x Rp block, Rp = 16 ceil(nrhs / 16)), so the kernel products of a
 // system are one multi-RHS matrix-core launch.  Reductions are segmented: every
 // 256-element chunk belongs to one column; a block reduces its chunk and the
-// last block of the column (per-column counter) adds the column's partials in
+// kernel that needs a column's total adds the column's partials in a fixed
 // order.  All solver scalars are per column in device memory; a column that has
 // converged (or broken down) drops out through its active flags.  The inner CG
 // sequence (its products and vector kernels on fixed buffers) is captured once
@@ -22,6 +22,7 @@
 #include <vector>
 
 #include "kmvp_multi.h"
+#include "orth.h"
 #include "solvers.h"
 
 namespace krr {
@@ -29,9 +30,13 @@ namespace krr {
 namespace {
 
 struct BCols {  // per-column device state (arrays of C entries unless noted)
-    // inner CG (FP32)
-    float *rr, *rr0, *thresh, *alpha, *beta;
-    int *cg_active, *cg_iters;
+    // inner CG (FP32): r.r, the active flag and the iteration count of iteration
+    // it live at [it & 1][C] (a kernel reads one half and writes the other)
+    float *rr, *thresh;
+    int *act, *iters;
+    int *brk;                         // [C]: the iteration's p.Ap was not positive
+    double *cgp, *cgr;                // partial sums: p.Ap per 64 rows, r.r per 256
+    int *cg_active, *cg_iters;        // plain CG
     // FGMRES
     double *bnorm, *beta_o, *est, *wnorm0;
     int *breakdown, *in_cycle, *kcol, *valid;
@@ -115,7 +120,15 @@ __device__ __forceinline__ void col_total(const BCols &B, int c, double (&v)[NV]
     const int64_t e = static_cast<int64_t>(blockIdx.x) * BLOCK + threadIdx.x
 
 // ---------------------------------------------------------------- inner CG (FP32)
+//
+// One iteration is four launches: the product, its finish with the chunk sums
+// of p.Ap (kmvp_multi.hip), the update of z and r, and the new direction with
+// the next product's Q'.  At the sizes of a batch a launch costs about 4.7 us
+// whatever it does, so no kernel only adds up another's partial sums: every
+// block that needs a column's total adds the (few) partials itself, in the same
+// order as every other block, and one block per column records the new state.
 
+// z = 0, r = p = v and the chunk sums of v.v.
 __global__ __launch_bounds__(BLOCK) void kb_cg_init(BCols B, const double *__restrict__ vin, float *z, float *r,
                                                     float *p) {
     BCHUNK;
@@ -125,79 +138,114 @@ __global__ __launch_bounds__(BLOCK) void kb_cg_init(BCols B, const double *__res
     r[e] = v;
     p[e] = v;
     double acc[1] = {static_cast<double>(v) * v};
-    seg_partial(acc, B);
+    bblock_sum(acc);
+    if (threadIdx.x == 0) B.cgr[blockIdx.x] = acc[0];
 }
 
-__global__ __launch_bounds__(BLOCK) void kb_cg_init_col(BCols B, int C, double tol2, int maxit) {
-    const int c = wave_col(C);
-    if (c < 0 || !B.in_cycle[c]) return;
-    double acc[1];
-    col_total(B, c, acc);
-    if (threadIdx.x % WAVE == 0) {
-        const float rr = static_cast<float>(acc[0]);
-        B.rr[c] = rr;
-        B.rr0[c] = rr;
-        B.thresh[c] = static_cast<float>(tol2 * acc[0]);
-        B.cg_iters[c] = 0;
-        B.cg_active[c] = (rr > 0.f && maxit > 0) ? 1 : 0;
-    }
+// Sum of n partials from src, in every lane of the wave (as col_sum).
+__device__ __forceinline__ double wave_total(const double *__restrict__ src, int n) {
+    const int lane = static_cast<int>(threadIdx.x) % WAVE;
+    double s = 0.0;
+    for (int q = lane; q < n; q += WAVE) s += src[q];
+    return bwave_sum(s);
 }
 
-__global__ __launch_bounds__(BLOCK) void kb_cg_alpha(BCols B, const float *__restrict__ p,
-                                                     const float *__restrict__ Ap) {
+// alpha = rr / p.Ap, z += alpha p, r -= alpha Ap, and the chunk sums of r.r.
+__global__ __launch_bounds__(BLOCK) void kb_cg_update(BCols B, int C, int par, float *z, float *r,
+                                                      const float *__restrict__ p, const float *__restrict__ Ap) {
+    __shared__ double s_pAp;
     BCHUNK;
-    if (!B.in_cycle[c] || !B.cg_active[c]) return;
-    double acc[1] = {static_cast<double>(p[e]) * Ap[e]};
-    seg_partial(acc, B);
-}
-
-__global__ __launch_bounds__(BLOCK) void kb_cg_alpha_col(BCols B, int C) {
-    const int c = wave_col(C);
-    if (c < 0 || !B.in_cycle[c] || !B.cg_active[c]) return;
-    double acc[1];
-    col_total(B, c, acc);
-    if (threadIdx.x % WAVE == 0) {
-        const float pAp = static_cast<float>(acc[0]);
-        if (!(pAp > 0.f) || !isfinite(pAp))
-            B.cg_active[c] = 0;
-        else
-            B.alpha[c] = B.rr[c] / pAp;
+    if (!B.in_cycle[c] || !B.act[par * C + c]) return;
+    const int c0 = B.col_chunk0[c];
+    if (threadIdx.x < WAVE) {
+        const double t = wave_total(B.cgp + 4 * static_cast<int64_t>(c0), 4 * B.col_nchunk[c]);
+        if (threadIdx.x == 0) s_pAp = t;
     }
-}
-
-__global__ __launch_bounds__(BLOCK) void kb_cg_update(BCols B, float *z, float *r, const float *__restrict__ p,
-                                                      const float *__restrict__ Ap) {
-    BCHUNK;
-    if (!B.in_cycle[c] || !B.cg_active[c]) return;
-    const float a = B.alpha[c];
+    __syncthreads();
+    const float pAp = static_cast<float>(s_pAp);
+    const bool bad = !(pAp > 0.f) || !isfinite(pAp);
+    if (threadIdx.x == 0 && static_cast<int>(blockIdx.x) == c0) B.brk[c] = bad ? 1 : 0;
+    if (bad) return;
+    const float a = B.rr[par * C + c] / pAp;
     z[e] += a * p[e];
     const float ri = r[e] - a * Ap[e];
     r[e] = ri;
     double acc[1] = {static_cast<double>(ri) * ri};
-    seg_partial(acc, B);
+    bblock_sum(acc);
+    if (threadIdx.x == 0) B.cgr[blockIdx.x] = acc[0];
 }
 
-// Also retires a column whose CG reached maxit (keeps the products of the next
-// iteration off it).
-__global__ __launch_bounds__(BLOCK) void kb_cg_update_col(BCols B, int C, int maxit) {
-    const int c = wave_col(C);
-    if (c < 0 || !B.in_cycle[c] || !B.cg_active[c]) return;
-    double acc[1];
-    col_total(B, c, acc);
-    if (threadIdx.x % WAVE == 0) {
-        const float rr = static_cast<float>(acc[0]);
-        B.beta[c] = rr / B.rr[c];
-        B.rr[c] = rr;
-        const int it = B.cg_iters[c] + 1;
-        B.cg_iters[c] = it;
-        if (!isfinite(rr) || rr <= B.thresh[c] || it >= maxit) B.cg_active[c] = 0;
+// The new direction p = r + beta p and the next product's Q' = p w (FIRST: p as
+// kb_cg_init left it), for one system of a class per blockIdx.y and one block of
+// 64 rows x 16 columns per blockIdx.x: columns read along memory, Q' turned
+// over in LDS.  The block of a column's first rows records its state: FIRST
+// from v.v, else from the iteration's r.r (a column that broke down, converged
+// or reached maxit goes inactive, which keeps the next products off it).
+template <int PREC, bool FIRST>
+__global__ __launch_bounds__(BLOCK) void kb_cg_direction(BCols B, int C, int par, const MSysB *__restrict__ S,
+                                                         const float *__restrict__ r, float *p, double tol2,
+                                                         int maxit) {
+    constexpr int ROWS = 64;
+    __shared__ float s_p[16][ROWS + 1];
+    __shared__ int s_live[16];
+    const MSysB &m = S[blockIdx.y];
+    const int64_t n_pad = m.a.n_pad;
+    const int nchunk = static_cast<int>(n_pad / ROWS);
+    if (static_cast<int>(blockIdx.x) >= nchunk * m.a.nrb) return;
+    const int rbk = blockIdx.x / nchunk;
+    const int64_t row0 = static_cast<int64_t>(blockIdx.x % nchunk) * ROWS;
+    const int wv = threadIdx.x / WAVE, lane = threadIdx.x % WAVE;
+    const int in = FIRST ? 0 : par * C, out = FIRST ? 0 : (par ^ 1) * C;
+    bool any = false;
+    for (int k = wv; k < 16; k += BLOCK / WAVE) {
+        const int c = m.col0 + rbk * 16 + k;
+        int live = 0;
+        if (B.in_cycle[c]) {
+            const bool writer = row0 == 0 && lane == 0;
+            float beta = 0.f;
+            if (FIRST || (B.act[in + c] && !B.brk[c])) {
+                const double t = wave_total(B.cgr + B.col_chunk0[c], B.col_nchunk[c]);
+                const float rr = static_cast<float>(t);
+                if constexpr (FIRST) {
+                    live = rr > 0.f && maxit > 0 ? 1 : 0;
+                    if (writer) {
+                        B.thresh[c] = static_cast<float>(tol2 * t);
+                        B.iters[c] = 0;
+                    }
+                } else {
+                    const int it = B.iters[in + c] + 1;
+                    beta = rr / B.rr[in + c];
+                    live = !isfinite(rr) || rr <= B.thresh[c] || it >= maxit ? 0 : 1;
+                    if (writer) B.iters[out + c] = it;
+                }
+                if (writer) B.rr[out + c] = rr;
+            } else if (writer) {
+                B.iters[out + c] = B.iters[in + c];
+            }
+            if (writer) B.act[out + c] = live;
+            if (live) {
+                const int64_t e = m.base + static_cast<int64_t>(rbk * 16 + k) * n_pad + row0 + lane;
+                float v = p[e];
+                if constexpr (!FIRST) {
+                    v = r[e] + beta * v;
+                    p[e] = v;
+                }
+                if (PREC == KRR_BF16) v = bf16_to_f32(f32_to_bf16_rne(v));
+                s_p[k][lane] = v;
+            }
+        }
+        if (lane == 0) s_live[k] = live;
+        any = any || live;
     }
-}
-
-__global__ __launch_bounds__(BLOCK) void kb_cg_pupdate(BCols B, const float *__restrict__ r, float *p) {
-    BCHUNK;
-    if (!B.in_cycle[c] || !B.cg_active[c]) return;
-    p[e] = r[e] + B.beta[c] * p[e];
+    if (!__syncthreads_or(any)) return;
+    const bool wide = m.a.tile_r2[row0 / TILE] > WIDE_R2_FP32;
+    const float *w = static_cast<const float *>(m.w);
+    float *qwt = static_cast<float *>(const_cast<void *>(m.a.qwt)) + (rbk * n_pad + row0) * 16;
+#pragma unroll
+    for (int k = 0; k < ROWS * 16 / BLOCK; ++k) {
+        const int l = threadIdx.x + k * BLOCK;  // row l / 16, column l % 16
+        if (s_live[l % 16]) qwt[l] = wide ? s_p[l % 16][l / 16] : s_p[l % 16][l / 16] * w[row0 + l / 16];
+    }
 }
 
 // ---------------------------------------------------------------- FGMRES (FP64)
@@ -264,11 +312,12 @@ __global__ __launch_bounds__(BLOCK) void kb_first_basis(BCols B, const double *_
 
 // z (FP32 inner solution) -> Z_j; the column's first chunk block also adds the
 // inner iterations of this step to its count.
-__global__ __launch_bounds__(BLOCK) void kb_cast_z(BCols B, const float *__restrict__ z, double *Zj) {
+__global__ __launch_bounds__(BLOCK) void kb_cast_z(BCols B, const int *__restrict__ iters,
+                                                   const float *__restrict__ z, double *Zj) {
     BCHUNK;
     if (!B.in_cycle[c]) return;
     Zj[e] = static_cast<double>(z[e]);
-    if (threadIdx.x == 0 && static_cast<int>(blockIdx.x) == B.col_chunk0[c]) B.col_inner[c] += B.cg_iters[c];
+    if (threadIdx.x == 0 && static_cast<int>(blockIdx.x) == B.col_chunk0[c]) B.col_inner[c] += iters[c];
 }
 
 __global__ __launch_bounds__(BLOCK) void kb_copy(BCols B, const double *__restrict__ a, double *bout) {
@@ -400,6 +449,32 @@ __global__ __launch_bounds__(BLOCK) void kb_wsq(BCols B, const double *__restric
     seg_partial(acc, B);
 }
 
+// The rotated column's outcome: rotation j and the residual estimate; the
+// column leaves its cycle on convergence of the estimate or on a happy breakdown
+// (h_next = h_{j+1,j} <= 1e-14 ||K z_j||), and is retired (KRR_BREAKDOWN, its
+// steps before this one kept; false) on a non-finite value.
+__device__ __forceinline__ bool givens_finish(const BCols &B, int c, int j, int m, double tol, double rho, double cj,
+                                              double sj, double h_next, double wnorm0) {
+    double *g = B.g + static_cast<int64_t>(c) * (m + 1);
+    const double est = fabs(-sj * g[j]) / B.bnorm[c];
+    if (!isfinite(est) || !isfinite(rho)) {
+        B.status[c] = KRR_BREAKDOWN;
+        B.kcol[c] = j;
+        B.in_cycle[c] = 0;
+        return false;
+    }
+    B.cs[static_cast<int64_t>(c) * m + j] = cj;
+    B.sn[static_cast<int64_t>(c) * m + j] = sj;
+    g[j + 1] = -sj * g[j];
+    g[j] = cj * g[j];
+    B.est[c] = est;
+    B.kcol[c] = j + 1;
+    const int brk = (h_next > 1e-14 * wnorm0) ? 0 : 1;
+    B.breakdown[c] = brk;
+    if (brk || est <= tol) B.in_cycle[c] = 0;
+    return true;
+}
+
 // Givens step of every column in its cycle (one thread per column); a column
 // leaves the cycle on convergence of its estimate or on breakdown, and is
 // retired (KRR_BREAKDOWN, its steps before this one kept) on a non-finite value.
@@ -408,8 +483,7 @@ __global__ void kb_givens(BCols B, int C, int j, int m, double tol) {
     if (c >= C || !B.in_cycle[c]) return;
     const double *hc = B.hcol + static_cast<int64_t>(c) * (m + 2);
     double *col = B.H + (static_cast<int64_t>(c) * m + j) * (m + 1);
-    double *cs = B.cs + static_cast<int64_t>(c) * m, *sn = B.sn + static_cast<int64_t>(c) * m;
-    double *g = B.g + static_cast<int64_t>(c) * (m + 1);
+    const double *cs = B.cs + static_cast<int64_t>(c) * m, *sn = B.sn + static_cast<int64_t>(c) * m;
     B.col_outer[c] += 1;
     B.col_mvp64[c] += 1;
     for (int i = 0; i <= j + 1; ++i) col[i] = hc[i];
@@ -421,24 +495,52 @@ __global__ void kb_givens(BCols B, int C, int j, int m, double tol) {
     const double a = col[j], b = col[j + 1];
     const double rho = sqrt(a * a + b * b);
     const double cj = a / rho, sj = b / rho;
-    const double est = fabs(-sj * g[j]) / B.bnorm[c];
-    if (!isfinite(est) || !isfinite(rho)) {
-        B.status[c] = KRR_BREAKDOWN;
-        B.kcol[c] = j;
-        B.in_cycle[c] = 0;
-        return;
-    }
-    cs[j] = cj;
-    sn[j] = sj;
+    if (!givens_finish(B, c, j, m, tol, rho, cj, sj, hc[j + 1], B.wnorm0[c])) return;
     col[j] = rho;
     col[j + 1] = 0.0;
-    g[j + 1] = -sj * g[j];
-    g[j] = cj * g[j];
-    B.est[c] = est;
-    B.kcol[c] = j + 1;
-    const int brk = (hc[j + 1] > 1e-14 * B.wnorm0[c]) ? 0 : 1;
-    B.breakdown[c] = brk;
-    if (brk || est <= tol) B.in_cycle[c] = 0;
+}
+
+// The whole orthogonalisation of one column's Arnoldi vector, v_{j+1} and its
+// Givens step (orth.h), one block per column, for batches whose columns are at
+// most ORTH_MAX_N long: one launch in place of 2 j + 6.
+template <bool CGS2>
+__global__ __launch_bounds__(ORTH_THREADS) void kb_orth_column(BCols B, const double *__restrict__ w, double *V,
+                                                               int64_t LL, int j, int m, double tol) {
+    __shared__ OrthShared sh;
+    const int c = blockIdx.x, tid = threadIdx.x;
+    if (!B.in_cycle[c]) return;
+    const int n = B.col_nchunk[c] * BLOCK;
+    const int64_t off = B.col_off[c];
+    double x[ORTH_PER];
+#pragma unroll
+    for (int k = 0; k < ORTH_PER; ++k) {
+        const int e = tid + k * ORTH_THREADS;
+        x[k] = e < n ? w[off + e] : 0.0;
+    }
+    double wnorm0;
+    const double hn = orth_column<CGS2>(x, n, V + off, LL, j, sh, wnorm0);
+    double *vn = V + (j + 1) * LL + off;
+#pragma unroll
+    for (int k = 0; k < ORTH_PER; ++k) {
+        const int e = tid + k * ORTH_THREADS;
+        if (e < n) vn[e] = x[k] / hn;
+    }
+    for (int i = tid; i < j; i += ORTH_THREADS) {
+        sh.cs[i] = B.cs[static_cast<int64_t>(c) * m + i];
+        sh.sn[i] = B.sn[static_cast<int64_t>(c) * m + i];
+    }
+    __syncthreads();
+    if (tid == 0) {
+        B.col_outer[c] += 1;
+        B.col_mvp64[c] += 1;
+        B.wnorm0[c] = wnorm0;
+        double cj, sj;
+        const double rho = orth_givens(sh, j, cj, sj);
+        givens_finish(B, c, j, m, tol, rho, cj, sj, hn, wnorm0);
+    }
+    __syncthreads();
+    double *col = B.H + (static_cast<int64_t>(c) * m + j) * (m + 1);
+    for (int i = tid; i <= j + 1; i += ORTH_THREADS) col[i] = sh.h[i];
 }
 
 __global__ __launch_bounds__(BLOCK) void kb_normalize(BCols B, const double *__restrict__ w, double *vnext, int j,
@@ -685,12 +787,22 @@ struct BatchLayout {
 };
 
 // Candidate column tiles per work item of a batched product (the autotuner
-// times them once per dimension class and keeps the fastest).
+// times them once per dimension class and keeps the fastest): the tiles of a
+// system of at least 256 tiles; a smaller one is cut into as many parts (256 /
+// tps) as that one would be, down to single tiles.  At whole 16-tile items a
+// batch of small systems left the chip idle (four systems of 833 to 2500
+// points, d = 4, 16 right-hand sides: 28 items on 256 CUs, 92 us per FP32 and
+// 208 us per FP64 product).
 constexpr int kTpsCands[] = {16, 32, 64, 128};
 constexpr int kTpsMin = 16;
+int system_tps(int ntiles, int tps) {
+    if (ntiles >= 256) return ntiles < tps ? ntiles : tps;
+    const int t = (ntiles * tps + 255) / 256;
+    return t < 1 ? 1 : (t > ntiles ? ntiles : t);
+}
 
 int64_t items_of(int ntiles, int tps, int nrb) {
-    const int t = ntiles < tps ? ntiles : tps;
+    const int t = system_tps(ntiles, tps);
     return static_cast<int64_t>(ntiles) * ((ntiles + t - 1) / t) * nrb;
 }
 
@@ -708,7 +820,7 @@ BatchLayout carve_batch(void *ws, const krr_points *probs, int nprob, int nrhs, 
         L.sys[k].base = L.L;
         L.L += L.sys[k].P.n_pad * L.Rp;
         if (probs[k].n > maxn) maxn = probs[k].n;
-        L.sys[k].pscratch = cv.take<char>(batched_product_scratch_bytes(L.sys[k].P, L.Rp, kTpsMin));
+        L.sys[k].pscratch = cv.take<char>(batched_product_scratch_bytes(L.sys[k].P, L.Rp, system_tps(L.sys[k].P.ntiles, kTpsMin)));
         nitems += items_of(L.sys[k].P.ntiles, kTpsMin, nrb);
     }
     L.nitems = static_cast<int>(nitems);
@@ -736,11 +848,13 @@ BatchLayout carve_batch(void *ws, const krr_points *probs, int nprob, int nrhs, 
     const int C = L.C;
     const int mm = m > 0 ? m : 1;
     BCols &B = L.B;
-    B.rr = cv.take<float>(C);
-    B.rr0 = cv.take<float>(C);
+    B.rr = cv.take<float>(2 * C);
     B.thresh = cv.take<float>(C);
-    B.alpha = cv.take<float>(C);
-    B.beta = cv.take<float>(C);
+    B.act = cv.take<int>(2 * C);
+    B.iters = cv.take<int>(2 * C);
+    B.brk = cv.take<int>(C);
+    B.cgp = cv.take<double>(4 * static_cast<size_t>(L.nchunks));
+    B.cgr = cv.take<double>(L.nchunks);
     B.cg_active = cv.take<int>(C);
     B.cg_iters = cv.take<int>(C);
     B.bnorm = cv.take<double>(C);
@@ -809,9 +923,31 @@ struct BatchRun {
     int nprob = 0, nrhs = 0;
     double t_prep_ms = 0.0;
 
-    hipError_t products(const void *Q, void *Yo, bool inner, ColGate gate, hipStream_t st) const {
-        for (size_t c = 0; c < bp_in.size(); ++c)
-            KRR_HIP(batched_product(inner ? bp_in[c] : bp_out[c], Q, Yo, inner ? 1 : 0, gate, st));
+    // FP64 products (with the outer shift)
+    hipError_t products(const void *Q, void *Yo, ColGate gate, hipStream_t st) const {
+        for (const BatchedProduct &bp : bp_out) KRR_HIP(batched_product(bp, Q, Yo, 0, gate, st));
+        return hipSuccess;
+    }
+    // the inner CG's products, on the Q' that directions() left: Yo and the
+    // 64-row sums of Q Yo
+    hipError_t inner_products(const void *Q, void *Yo, ColGate gate, double *dots, hipStream_t st) const {
+        for (const BatchedProduct &bp : bp_in) KRR_HIP(batched_product(bp, Q, Yo, 1, gate, st, true, dots));
+        return hipSuccess;
+    }
+    // the inner CG's directions (par < 0: the first one)
+    hipError_t directions(const BCols &B, int C, int par, const float *r, float *p, double tol2, int maxit,
+                          hipStream_t st) const {
+        for (const BatchedProduct &bp : bp_in) {
+            const dim3 g(static_cast<unsigned>(bp.max_elems / (64 * 16)), bp.nsys);
+            auto go = [&](auto kern) {
+                hipLaunchKernelGGL(kern, g, dim3(BLOCK), 0, st, B, C, par, bp.d_sys, r, p, tol2, maxit);
+                return hipGetLastError();
+            };
+            if (bp.prec == KRR_BF16)
+                KRR_HIP(par < 0 ? go(kb_cg_direction<KRR_BF16, true>) : go(kb_cg_direction<KRR_BF16, false>));
+            else
+                KRR_HIP(par < 0 ? go(kb_cg_direction<KRR_FP32, true>) : go(kb_cg_direction<KRR_FP32, false>));
+        }
         return hipSuccess;
     }
 };
@@ -821,7 +957,7 @@ void class_items(const BatchLayout &L, const std::vector<int> &order, int pos, i
                  std::vector<MItem> &items) {
     for (int e = pos; e < end; ++e) {
         const Prepared &P = L.sys[order[e]].P;
-        const int t = P.ntiles < tps ? P.ntiles : tps;
+        const int t = system_tps(P.ntiles, tps);
         const int splits = (P.ntiles + t - 1) / t;
         for (int bx = 0; bx < P.ntiles; ++bx)
             for (int by = 0; by < splits; ++by)
@@ -903,8 +1039,9 @@ int batch_setup(BatchRun &R, const krr_points *probs, int nprob, const double *s
     auto fill_class = [&](int pos, int end, int tps) {
         for (int e = pos; e < end; ++e) {
             const Sys &S = L.sys[order[e]];
-            fill_msys(hin[e], S.P, inner_prec, Rp, S.pscratch, S.base, S.delta, S.gamma, tps);
-            fill_msys(hout[e], S.P, KRR_FP64, Rp, S.pscratch, S.base, S.delta, S.gamma, tps);
+            const int t = system_tps(S.P.ntiles, tps);
+            fill_msys(hin[e], S.P, inner_prec, Rp, S.pscratch, S.base, S.delta, S.gamma, t);
+            fill_msys(hout[e], S.P, KRR_FP64, Rp, S.pscratch, S.base, S.delta, S.gamma, t);
             hin[e].col0 = hout[e].col0 = order[e] * Rp;
         }
     };
@@ -951,9 +1088,12 @@ int batch_setup(BatchRun &R, const krr_points *probs, int nprob, const double *s
                 BH(hipEventCreate(&e1));
             }
             float best_ms = 1e30f;
+            size_t last_items = 0;
             for (int cand : kTpsCands) {
                 std::vector<MItem> ci;
                 class_items(L, order, pos, end, cand, nrb, ci);
+                if (ci.size() == last_items) continue;  // the same cut as the candidate before
+                last_items = ci.size();
                 fill_class(pos, end, cand);
                 BatchedProduct bt = tune_inner ? bi : bo;
                 const void *tq = tune_inner ? static_cast<const void *>(L.p32) : static_cast<const void *>(L.b);
@@ -1095,32 +1235,39 @@ int batched_fgmres(const krr_points *probs, int nprob, const double *sigma, cons
     // Products run only on the columns that use them: the inner CG's on columns
     // in their cycle with an active CG, the Arnoldi step's on columns in their
     // cycle, the cycle-end residual's on columns that took a step this cycle.
-    const ColGate gate_inner{B.in_cycle, B.cg_active}, gate_arnoldi{B.in_cycle, nullptr},
-        gate_cycle_end{B.kcol, nullptr};
+    const ColGate gate_arnoldi{B.in_cycle, nullptr}, gate_cycle_end{B.kcol, nullptr};
 
     // one outer step j on fixed buffers: the inner CG (V_j -> z32 -> Z_j), the
     // outer product w = K Z_j, Gram-Schmidt, v_{j+1}, Givens
     const double tol2 = o.inner_tol * o.inner_tol;
+    bool short_cols = true;
+    for (const Sys &S : L.sys) short_cols = short_cols && S.P.n_pad <= ORTH_MAX_N;
     auto step_seq = [&](int j, hipStream_t st) -> hipError_t {
         double *Vj = L.V + static_cast<int64_t>(j) * LL;
         double *Zj = L.Z + static_cast<int64_t>(j) * LL;
         if (o.inner == KRR_INNER_NONE) {
             hipLaunchKernelGGL(kb_copy, dim3(nb), dim3(BLOCK), 0, st, B, Vj, Zj);
         } else {
-            hipLaunchKernelGGL(kb_copy, dim3(nb), dim3(BLOCK), 0, st, B, Vj, L.vin);
-            hipLaunchKernelGGL(kb_cg_init, dim3(nb), dim3(BLOCK), 0, st, B, L.vin, L.z32, L.r32, L.p32);
-            hipLaunchKernelGGL(kb_cg_init_col, dim3(ccb), dim3(BLOCK), 0, st, B, C, tol2, o.inner_maxit);
+            hipLaunchKernelGGL(kb_cg_init, dim3(nb), dim3(BLOCK), 0, st, B, Vj, L.z32, L.r32, L.p32);
+            KRR_HIP(R.directions(B, C, -1, L.r32, L.p32, tol2, o.inner_maxit, st));
             for (int it = 0; it < o.inner_maxit; ++it) {
-                KRR_HIP(R.products(L.p32, L.Ap32, true, gate_inner, st));
-                hipLaunchKernelGGL(kb_cg_alpha, dim3(nb), dim3(BLOCK), 0, st, B, L.p32, L.Ap32);
-                hipLaunchKernelGGL(kb_cg_alpha_col, dim3(ccb), dim3(BLOCK), 0, st, B, C);
-                hipLaunchKernelGGL(kb_cg_update, dim3(nb), dim3(BLOCK), 0, st, B, L.z32, L.r32, L.p32, L.Ap32);
-                hipLaunchKernelGGL(kb_cg_update_col, dim3(ccb), dim3(BLOCK), 0, st, B, C, o.inner_maxit);
-                hipLaunchKernelGGL(kb_cg_pupdate, dim3(nb), dim3(BLOCK), 0, st, B, L.r32, L.p32);
+                const int par = it & 1;
+                KRR_HIP(R.inner_products(L.p32, L.Ap32, ColGate{B.in_cycle, B.act + par * C}, B.cgp, st));
+                hipLaunchKernelGGL(kb_cg_update, dim3(nb), dim3(BLOCK), 0, st, B, C, par, L.z32, L.r32, L.p32, L.Ap32);
+                KRR_HIP(R.directions(B, C, par, L.r32, L.p32, tol2, o.inner_maxit, st));
             }
-            hipLaunchKernelGGL(kb_cast_z, dim3(nb), dim3(BLOCK), 0, st, B, L.z32, Zj);
+            hipLaunchKernelGGL(kb_cast_z, dim3(nb), dim3(BLOCK), 0, st, B, B.iters + (o.inner_maxit & 1) * C, L.z32,
+                               Zj);
         }
-        KRR_HIP(R.products(Zj, L.w, false, gate_arnoldi, st));
+        KRR_HIP(R.products(Zj, L.w, gate_arnoldi, st));
+        if (short_cols) {
+            if (o.gs == KRR_GS_CGS2)
+                hipLaunchKernelGGL(kb_orth_column<true>, dim3(C), dim3(ORTH_THREADS), 0, st, B, L.w, L.V, LL, j, m, o.tol);
+            else
+                hipLaunchKernelGGL(kb_orth_column<false>, dim3(C), dim3(ORTH_THREADS), 0, st, B, L.w, L.V, LL, j, m,
+                                   o.tol);
+            return hipGetLastError();
+        }
         if (o.gs == KRR_GS_CGS2) {
             for (int pass = 0; pass < 2; ++pass) {
                 hipLaunchKernelGGL(kb_gs_dot, dim3(nb), dim3(BLOCK), 0, st, B, L.w, L.V, LL, j, pass == 0 ? 1 : 0);
@@ -1221,7 +1368,7 @@ int batched_fgmres(const krr_points *probs, int nprob, const double *sigma, cons
         hipLaunchKernelGGL(kb_backsolve, dim3(cb), dim3(BLOCK), 0, s, B, C, m);
         hipLaunchKernelGGL(kb_update_x, dim3(nb), dim3(BLOCK), 0, s, B, L.Z, LL, m, L.x);
         ++cycles;
-        BHC(R.products(L.x, L.w, false, gate_cycle_end, s));
+        BHC(R.products(L.x, L.w, gate_cycle_end, s));
         hipLaunchKernelGGL(kb_residual, dim3(nb), dim3(BLOCK), 0, s, B, L.b, L.w, L.r);
         hipLaunchKernelGGL(kb_residual_col, dim3(ccb), dim3(BLOCK), 0, s, B, C, 1, m, o.tol);
         BHC(read_summary());
@@ -1269,7 +1416,7 @@ int batched_cg64(const krr_points *probs, int nprob, const double *sigma, const 
     while (host[2] > 0 || host[3] > 0) {
         if (host[2] > 0) {
             for (int k = 0; k < check; ++k) {
-                BH(R.products(p, Ap, false, gate_active, s));
+                BH(R.products(p, Ap, gate_active, s));
                 hipLaunchKernelGGL(kc_alpha, dim3(nb), dim3(BLOCK), 0, s, B, p, Ap);
                 hipLaunchKernelGGL(kc_alpha_col, dim3(ccb), dim3(BLOCK), 0, s, B, C);
                 hipLaunchKernelGGL(kc_update, dim3(nb), dim3(BLOCK), 0, s, B, L.x, L.r, p, Ap);
@@ -1284,7 +1431,7 @@ int batched_cg64(const krr_points *probs, int nprob, const double *sigma, const 
         }
         if (host[3] > 0) {
             // true residuals of the columns that stopped; accept or restart
-            BH(R.products(L.x, Ap, false, gate_cand, s));
+            BH(R.products(L.x, Ap, gate_cand, s));
             hipLaunchKernelGGL(kc_true, dim3(nb), dim3(BLOCK), 0, s, B, L.b, Ap, L.r);
             hipLaunchKernelGGL(kc_true_col, dim3(ccb), dim3(BLOCK), 0, s, B, C, o.tol, o.max_outer);
             hipLaunchKernelGGL(kc_prestart, dim3(nb), dim3(BLOCK), 0, s, B, L.r, p);

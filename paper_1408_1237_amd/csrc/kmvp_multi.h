@@ -62,8 +62,9 @@ size_t batched_product_scratch_bytes(const Prepared &P, int nrhs, int min_tps);
 void fill_msys(MSysB &m, const Prepared &P, int prec, int nrhs, void *scratch, int64_t base, double shift_in,
                double shift_out, int tps);
 // Y = K_hat Q + shift Q for every system of bp (inner != 0: shift_in), on the
-// live columns of gate.
+// live columns of gate.  scaled: Q' is in place already; dots (optional): the
+// 64-row sums of Q Y of the live columns, at (element offset) / 64.
 hipError_t batched_product(const BatchedProduct &bp, const void *Qall, void *Yall, int inner, ColGate gate,
-                           hipStream_t s);
+                           hipStream_t s, bool scaled = false, double *dots = nullptr);
 
 }  // namespace krr

@@ -670,9 +670,11 @@ __global__ __launch_bounds__(BLOCK) void k_multi_prescale_b(const MSysB *__restr
 // it reads the [row][16] partial sums along memory (the chunks added from the
 // first, in order), turns the 64 x 16 sums over in LDS and writes each column's
 // 64 rows with one wave.
+// dots != null: also the 64-row sums of Q Y (FP64), one per (64 rows of a
+// column), in the order of the concatenated vectors.
 template <int PREC>
 __global__ __launch_bounds__(BLOCK) void k_multi_finish_b(const MSysB *__restrict__ S, const void *Qall_, void *Yall_,
-                                                          int nrhs, int inner, ColGate gate) {
+                                                          int nrhs, int inner, ColGate gate, double *dots) {
     using T = typename MP<PREC>::T;
     constexpr int ROWS = 64;
     constexpr int PER = ROWS * 16 / BLOCK;
@@ -710,13 +712,17 @@ __global__ __launch_bounds__(BLOCK) void k_multi_finish_b(const MSysB *__restric
         const int r = rbk * 16 + c;
         if (r >= nrhs || !gate_live(gate, m.col0 + r)) continue;
         const int64_t i = row0 + il, idx = static_cast<int64_t>(r) * n_pad + i;
-        if (i >= m.a.n) {
-            Y[idx] = T(0);
-            continue;
-        }
-        T qv = Q[idx];
+        const T q = Q[idx];  // 0 on the padding
+        T qv = q;
         if (PREC == KRR_BF16) qv = bf16_to_f32(f32_to_bf16_rne(static_cast<float>(qv)));
-        Y[idx] = s_y[c][il] + shift * qv;
+        const T y = i < m.a.n ? s_y[c][il] + shift * qv : T(0);
+        Y[idx] = y;
+        if (dots != nullptr) {  // il = lane: one wave holds 64 rows of one column
+            double d = static_cast<double>(q) * static_cast<double>(y);
+#pragma unroll
+            for (int o = WAVE / 2; o > 0; o /= 2) d += __shfl_xor(d, o, WAVE);
+            if (il == 0) dots[(m.base + idx) / ROWS] = d;
+        }
     }
 }
 
@@ -789,26 +795,29 @@ static hipError_t launch_multi_b_d(int dpad, const MSysB *S, const MItem *items,
 
 template <int PREC>
 static hipError_t batched_run(const BatchedProduct &bp, const void *Qall, void *Yall, int inner, ColGate gate,
-                              hipStream_t s) {
-    const dim3 g((bp.max_elems + BLOCK - 1) / BLOCK, bp.nsys);
-    hipLaunchKernelGGL(k_multi_prescale_b<PREC>, g, dim3(BLOCK), 0, s, bp.d_sys, Qall, bp.nrhs, gate);
-    KRR_HIP(hipGetLastError());
+                              bool scaled, double *dots, hipStream_t s) {
+    if (!scaled) {
+        const dim3 g((bp.max_elems + BLOCK - 1) / BLOCK, bp.nsys);
+        hipLaunchKernelGGL(k_multi_prescale_b<PREC>, g, dim3(BLOCK), 0, s, bp.d_sys, Qall, bp.nrhs, gate);
+        KRR_HIP(hipGetLastError());
+    }
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     const bool timed = profile_slot(PREC, bp.pairs * bp.nrhs, &ev0, &ev1);
     if (timed) KRR_HIP(hipEventRecord(ev0, s));
     KRR_HIP(launch_multi_b_d<PREC>(bp.dpad, bp.d_sys, bp.d_items, bp.nitems, gate, s));
     if (timed) KRR_HIP(hipEventRecord(ev1, s));
     const dim3 gf((bp.max_elems + 64 * 16 - 1) / (64 * 16), bp.nsys);
-    hipLaunchKernelGGL(k_multi_finish_b<PREC>, gf, dim3(BLOCK), 0, s, bp.d_sys, Qall, Yall, bp.nrhs, inner, gate);
+    hipLaunchKernelGGL(k_multi_finish_b<PREC>, gf, dim3(BLOCK), 0, s, bp.d_sys, Qall, Yall, bp.nrhs, inner, gate,
+                       dots);
     return hipGetLastError();
 }
 
 hipError_t batched_product(const BatchedProduct &bp, const void *Qall, void *Yall, int inner, ColGate gate,
-                           hipStream_t s) {
+                           hipStream_t s, bool scaled, double *dots) {
     switch (bp.prec) {
-        case KRR_FP64: return batched_run<KRR_FP64>(bp, Qall, Yall, inner, gate, s);
-        case KRR_FP32: return batched_run<KRR_FP32>(bp, Qall, Yall, inner, gate, s);
-        case KRR_BF16: return batched_run<KRR_BF16>(bp, Qall, Yall, inner, gate, s);
+        case KRR_FP64: return batched_run<KRR_FP64>(bp, Qall, Yall, inner, gate, scaled, dots, s);
+        case KRR_FP32: return batched_run<KRR_FP32>(bp, Qall, Yall, inner, gate, scaled, dots, s);
+        case KRR_BF16: return batched_run<KRR_BF16>(bp, Qall, Yall, inner, gate, scaled, dots, s);
         default: return hipErrorInvalidValue;
     }
 }

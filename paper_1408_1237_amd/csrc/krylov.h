@@ -46,6 +46,10 @@ hipError_t fill_d(double *p, int64_t n, double v, hipStream_t s);
 hipError_t zero_bytes(void *p, int64_t n, hipStream_t s);  // fill kernel (no memset nodes)
 hipError_t fg_orthogonalize(int gs, int64_t n_pad, int j, double *w, const double *V, double *hcol, double *hscratch,
                             FgmresScalars *F, const Red &R, hipStream_t s);
+// One Arnoldi step's orthogonalisation of w against V_0 .. V_j, its Givens step
+// and v_{j+1}: one launch for short vectors (orth.h), else the kernels below.
+hipError_t fg_arnoldi(int gs, int64_t n_pad, int j, int m, double *w, double *V, double *hcol, double *hscratch,
+                      double *H, double *cs, double *sn, double *g, FgmresScalars *F, const Red &R, hipStream_t s);
 hipError_t fg_givens(int j, int m, const double *hcol, double *H, double *cs, double *sn, double *g,
                      FgmresScalars *F, hipStream_t s);
 hipError_t fg_normalize(int64_t n_pad, const double *w, double *vnext, const double *hcol, int j,

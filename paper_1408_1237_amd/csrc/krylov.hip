@@ -7,6 +7,7 @@
 // convergence flags).  Solver scalars stay in device memory, so no kernel waits
 // for the host.  All vectors are sorted, zero-padded, of length n_pad.
 #include "krylov.h"
+#include "orth.h"
 
 namespace krr {
 
@@ -341,6 +342,56 @@ __global__ void k_givens(int j, int m, const double *hcol, double *H, double *cs
     if (!isfinite(F->est)) F->nonfinite = 1;
 }
 
+// Orthogonalisation, Givens step and v_{j+1} of a short vector in one block
+// (orth.h); the same quantities as the kernels above.
+template <bool CGS2>
+__global__ __launch_bounds__(ORTH_THREADS) void k_orth_step(int n, const double *__restrict__ w, double *V, int j,
+                                                            int m, double *hcol, double *H, double *cs, double *sn,
+                                                            double *g, FgmresScalars *F) {
+    __shared__ OrthShared sh;
+    __shared__ int s_brk;
+    const int tid = threadIdx.x;
+    double x[ORTH_PER];
+#pragma unroll
+    for (int k = 0; k < ORTH_PER; ++k) {
+        const int e = tid + k * ORTH_THREADS;
+        x[k] = e < n ? w[e] : 0.0;
+    }
+    double wnorm0;
+    const double hn = orth_column<CGS2>(x, n, V, n, j, sh, wnorm0);
+    for (int i = tid; i < j; i += ORTH_THREADS) {
+        sh.cs[i] = cs[i];
+        sh.sn[i] = sn[i];
+    }
+    __syncthreads();
+    for (int i = tid; i <= j + 1; i += ORTH_THREADS) hcol[i] = sh.h[i];
+    __syncthreads();
+    if (tid == 0) {
+        double cj, sj;
+        orth_givens(sh, j, cj, sj);
+        cs[j] = cj;
+        sn[j] = sj;
+        g[j + 1] = -sj * g[j];
+        g[j] = cj * g[j];
+        F->wnorm0 = wnorm0;
+        s_brk = (hn > 1e-14 * wnorm0) ? 0 : 1;
+        F->breakdown = s_brk;
+        F->est = fabs(g[j + 1]) / F->bnorm;
+        if (!isfinite(F->est)) F->nonfinite = 1;
+    }
+    __syncthreads();
+    double *col = H + static_cast<int64_t>(j) * (m + 1);
+    for (int i = tid; i <= j + 1; i += ORTH_THREADS) col[i] = sh.h[i];
+    if (s_brk) return;
+    double *vn = V + static_cast<int64_t>(j + 1) * n;
+    const double inv = 1.0 / hn;
+#pragma unroll
+    for (int k = 0; k < ORTH_PER; ++k) {
+        const int e = tid + k * ORTH_THREADS;
+        if (e < n) vn[e] = x[k] * inv;
+    }
+}
+
 // v_{j+1} = w / h_{j+1,j} (not after a breakdown)
 __global__ __launch_bounds__(BLOCK) void k_fg_normalize(int64_t n_pad, const double *__restrict__ w, double *vnext,
                                                         const double *hcol, int j, const FgmresScalars *F) {
@@ -530,6 +581,21 @@ hipError_t fg_orthogonalize(int gs, int64_t n_pad, int j, double *w, const doubl
         }
     }
     return hipGetLastError();
+}
+
+hipError_t fg_arnoldi(int gs, int64_t n_pad, int j, int m, double *w, double *V, double *hcol, double *hscratch,
+                      double *H, double *cs, double *sn, double *g, FgmresScalars *F, const Red &R, hipStream_t s) {
+    if (n_pad <= ORTH_MAX_N) {
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(1), dim3(ORTH_THREADS), 0, s, static_cast<int>(n_pad), w, V, j, m, hcol, H,
+                               cs, sn, g, F);
+            return hipGetLastError();
+        };
+        return gs == KRR_GS_MGS ? go(k_orth_step<false>) : go(k_orth_step<true>);
+    }
+    KRR_HIP(fg_orthogonalize(gs, n_pad, j, w, V, hcol, hscratch, F, R, s));
+    KRR_HIP(fg_givens(j, m, hcol, H, cs, sn, g, F, s));
+    return fg_normalize(n_pad, w, V + static_cast<int64_t>(j + 1) * n_pad, hcol, j, F, s);
 }
 
 hipError_t fg_givens(int j, int m, const double *hcol, double *H, double *cs, double *sn, double *g,

@@ -222,9 +222,7 @@ int fgmres_sorted(const Prepared &P, double gamma, bool x0_zero, const SolverOpt
             KRR_HIP_STATUS(kmvp_sorted(P, KRR_FP64, gamma, Zj, W.w, W.ksc, nullptr, s));
             ++mvp64;
             tm.mark(2, s);
-            KRR_HIP_STATUS(fg_orthogonalize(o.gs, np, j, W.w, W.V, W.hcol, W.hscr, F, W.R, s));
-            KRR_HIP_STATUS(fg_givens(j, m, W.hcol, W.H, W.cs, W.sn, W.g, F, s));
-            KRR_HIP_STATUS(fg_normalize(np, W.w, W.V + static_cast<int64_t>(j + 1) * np, W.hcol, j, F, s));
+            KRR_HIP_STATUS(fg_arnoldi(o.gs, np, j, m, W.w, W.V, W.hcol, W.hscr, W.H, W.cs, W.sn, W.g, F, W.R, s));
             tm.mark(3, s);
             KRR_HIP_STATUS(read_status(W.status, st, s));
             tm.collect();
