@@ -277,24 +277,23 @@ static int kmvp_single(const krr_points *pts, int kernel, double sigma, double s
     if (L.total > ws_bytes) return KRR_EWORKSPACE;
     L = carve(ws, pts->n, pts->d, o, K_MVP);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    KRR_HIP_STATUS(prepare_points(L.P, pts->x, sigma, L.temp, L.temp_bytes, s, kernel, prep_need(prec)));
-    if (prec == KRR_FP64) {
-        KRR_HIP_STATUS((gather_sorted<double, double>(L.P, static_cast<const double *>(q), static_cast<double *>(L.q), s)));
-        if (tune) KRR_HIP_STATUS(kmvp_tune(L.P, prec, L.q, L.y, L.W.ksc, s));
-        KRR_HIP_STATUS(kmvp_sorted(L.P, prec, shift, L.q, L.y, L.W.ksc, nullptr, s));
+    // the preparation also gathers and prescales q; the last kernel scatters y
+    PrepVec v;
+    v.prec = prec;
+    v.q = q;
+    v.qs = prec == KRR_BF16 ? static_cast<void *>(L.q16) : L.q;
+    v.qw = L.W.ksc.qw;
+    v.up = L.W.ksc.up;
+    v.lo = L.W.ksc.lo;
+    KRR_HIP_STATUS(prepare_points(L.P, pts->x, sigma, L.temp, L.temp_bytes, s, kernel, prep_need(prec), &v));
+    if (tune) KRR_HIP_STATUS(kmvp_tune(L.P, prec, v.qs, L.y, L.W.ksc, s));
+    KRR_HIP_STATUS(kmvp_core(L.P, prec, shift, v.qs, L.y, L.W.ksc, nullptr, s));
+    if (kmvp_live_slots(L.P, prec) > 0)
+        KRR_HIP_STATUS(kmvp_finish(L.P, prec, shift, v.qs, y, L.P.perm, L.W.ksc, nullptr, s));
+    else if (prec == KRR_FP64)
         KRR_HIP_STATUS((scatter_sorted<double, double>(L.P, static_cast<double *>(L.y), static_cast<double *>(y), s)));
-    } else {
-        float *qs = static_cast<float *>(L.q);
-        KRR_HIP_STATUS((gather_sorted<float, float>(L.P, static_cast<const float *>(q), qs, s)));
-        const void *qin = qs;
-        if (prec == KRR_BF16) {
-            KRR_HIP_STATUS(to_bf16(qs, L.q16, L.P.n_pad, s));
-            qin = L.q16;
-        }
-        if (tune) KRR_HIP_STATUS(kmvp_tune(L.P, prec, qin, L.y, L.W.ksc, s));
-        KRR_HIP_STATUS(kmvp_sorted(L.P, prec, shift, qin, L.y, L.W.ksc, nullptr, s));
+    else
         KRR_HIP_STATUS((scatter_sorted<float, float>(L.P, static_cast<float *>(L.y), static_cast<float *>(y), s)));
-    }
     return KRR_OK;
 }
 

@@ -112,6 +112,9 @@ struct KArgs {
     int square;
     const int *active;
     const double *row_r2;             // targets: squared radius of each row tile (far-tile skipping)
+    const double *box;                // symmetric products: tile boxes, bounds (krr_internal.h) and the
+    const int *up, *lo;               // exponent eps + log2(tiles) that a negligible pair has to clear
+    int clear;
     unsigned long long *skip_count;   // when profiling: += row-tile rows x column tiles skipped as far
 };
 
@@ -134,6 +137,36 @@ __device__ __forceinline__ bool tiles_far(const double (&aI)[D], double rI, cons
     }
     const double gap = sqrt(dd) - rI;
     return gap > 0.0 && gap * gap > 1.000001 * static_cast<double>(far_t2) + 1e-6;
+}
+
+// Whether the pair of tiles (I, J) of a symmetric product is evaluated: not when
+// every exponent is beyond the product's range (kernel values exactly zero: the
+// Gaussian argument is at most -d2 + |o|^2 - N_J <= -d2 + R2_J / 2 + 1), nor when
+// it is negligible (krr_internal.h).  d2: squared gap of the tiles' boxes.  For
+// Matern, -log2 k = log2(e) s - log2(1 + s) >= 1.2624 s - 1.74 (the tangent of the
+// concave log2(1 + s) at s = 7).  One thread per pair, a block's pairs at once:
+// the test is one round trip to memory.
+template <int D, bool MAT, bool F64>
+__device__ __forceinline__ bool pair_live(const KArgs &a, int I, int J) {
+    const double *bi = a.box + static_cast<int64_t>(I) * 2 * D, *bj = a.box + static_cast<int64_t>(J) * 2 * D;
+    const int need = max(a.up[J] - a.lo[I], a.up[I] - a.lo[J]) + a.clear;
+    const float r2 = MAT ? 0.f : static_cast<float>(a.tile_r2[J]);
+    double d2 = 0.0;
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+        const double g = fmax(0.0, fmax(bj[k] - bi[D + k], bi[k] - bj[D + k]));
+        d2 = __builtin_fma(g, g, d2);
+    }
+    float negl, far;
+    if constexpr (MAT) {
+        const float s = fmaxf(0.f, (static_cast<float>(need) + 1.74f) * 0.7922f);
+        negl = s * s;
+        far = F64 ? 760.f * 760.f : 111.f * 111.f;
+    } else {
+        negl = static_cast<float>(need);
+        far = (F64 ? 1101.f : 201.f) + 0.5f * r2;
+    }
+    return static_cast<float>(d2) < fminf(negl, far) * 1.00001f + 1e-3f;
 }
 
 template <int D, int PREC>
@@ -867,7 +900,7 @@ __device__ __forceinline__ double sum_rows16(double v) {
 }
 
 // Largest group (tiles) of the symmetric product's launch (kmvp_sym_group_tiles
-// stays below it up to 6.7e7 points).
+// stays below it up to 6.7e7 points); also the tile pairs a block tests at once.
 constexpr int MS_MAX_GROUP_TILES = 512;
 
 template <int D>
@@ -915,7 +948,7 @@ __global__ __launch_bounds__(BLOCK, 2) void k_kmvp_ms(KArgs a) {
     // per wave: the source terms of the current tile pair (and, at the end of a
     // row tile, the block's target terms)
     __shared__ T s_z[NW * TILE];
-    // the column tiles of group C not far from the current row tile
+    // the tile pairs to evaluate (pair_live)
     __shared__ unsigned char s_live[MS_MAX_GROUP_TILES];
     // the source terms of group C, when it fits (entry [jl][j] owned by thread j)
     constexpr int ZMAX = ms_zacc_tiles<D, MAT>();
@@ -996,21 +1029,30 @@ __global__ __launch_bounds__(BLOCK, 2) void k_kmvp_ms(KArgs a) {
         zl = sum_halves32(sum_rows16(zl));
         s_z[wv * TILE + cb + r16] = zl;
     };
+    // live tests of the block's tile pairs (the diagonal's lower half unused)
+    const bool skip = a.row_r2 != nullptr;  // null: no skipping
+    const bool at_once = (I1 - I0) * (C1 - C0) <= MS_MAX_GROUP_TILES;
+    if (at_once) {
+        for (int t = tid; t < (I1 - I0) * (C1 - C0); t += BLOCK)
+            s_live[t] = skip ? pair_live<D, MAT, true>(a, I0 + t / (C1 - C0), C0 + t % (C1 - C0)) : 1;
+        __syncthreads();
+    }
     int skipped = 0;
     for (int I = I0; I < I1; ++I) {
         double aI[D];
 #pragma unroll
         for (int k = 0; k < D; ++k) aI[k] = a.row_anchor[static_cast<int64_t>(I) * D + k];
-        const double rI = a.row_r2 != nullptr ? sqrt(a.row_r2[I]) : INFINITY;  // null: no skipping
-        // which column tiles are live: one thread per tile
+        // which column tiles are live: the block's pairs at once, or per row tile
         const int Js = diag ? I : C0;
-        for (int jj = tid; jj < C1 - Js; jj += BLOCK) {
-            const int Jt = Js + jj;
-            s_live[jj] = tiles_far<D>(aI, rI, a.anchor + static_cast<int64_t>(Jt) * D, a.tile_far64[Jt]) ? 0 : 1;
+        const unsigned char *live = s_live;
+        if (!at_once) {
+            for (int jj = tid; jj < C1 - C0; jj += BLOCK) s_live[jj] = skip ? pair_live<D, MAT, true>(a, I, C0 + jj) : 1;
+            __syncthreads();
+        } else {
+            live += (I - I0) * (C1 - C0);
         }
-        __syncthreads();
         auto next_live = [&](int J) {
-            while (J < C1 && s_live[J - Js] == 0) ++J;
+            while (J < C1 && live[J - C0] == 0) ++J;
             return J;
         };
         const int Jfirst = next_live(Js);
@@ -1019,7 +1061,7 @@ __global__ __launch_bounds__(BLOCK, 2) void k_kmvp_ms(KArgs a) {
             // no live column tile: zero target terms (the source-side slots stay as they are)
             const int64_t i = static_cast<int64_t>(I) * TILE + tid;
             if (!diag) yslot[i] = T(0);
-            __syncthreads();  // s_live is rewritten for the next row tile
+            if (!at_once) __syncthreads();  // s_live is rewritten for the next row tile
             continue;
         }
         for (int unit = 0; unit < UNITS; ++unit) {
@@ -1737,20 +1779,29 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(D <= 4 ? 
         swap_halves(zl, z0, z1);
         s_z[wv * TILE + cb + r32] = z0 + z1;
     };
+    // live tests of the block's tile pairs (the diagonal's lower half unused)
+    const bool skip = a.row_r2 != nullptr;  // null: no skipping
+    const bool at_once = (I1 - I0) * (C1 - C0) <= MS_MAX_GROUP_TILES;
+    if (at_once) {
+        for (int t = tid; t < (I1 - I0) * (C1 - C0); t += BLOCK)
+            s_live[t] = skip ? pair_live<D, MAT, false>(a, I0 + t / (C1 - C0), C0 + t % (C1 - C0)) : 1;
+        __syncthreads();
+    }
     int skipped = 0;
     for (int I = I0; I < I1; ++I) {
         double aI[D];
 #pragma unroll
         for (int k = 0; k < D; ++k) aI[k] = a.row_anchor[static_cast<int64_t>(I) * D + k];
-        const double rI = a.row_r2 != nullptr ? sqrt(a.row_r2[I]) : INFINITY;  // null: no skipping
         const int Js = diag ? I : C0;
-        for (int jj = tid; jj < C1 - Js; jj += BLOCK) {
-            const int Jt = Js + jj;
-            s_live[jj] = tiles_far<D>(aI, rI, a.anchor + static_cast<int64_t>(Jt) * D, a.tile_far[Jt]) ? 0 : 1;
+        const unsigned char *live = s_live;
+        if (!at_once) {
+            for (int jj = tid; jj < C1 - C0; jj += BLOCK) s_live[jj] = skip ? pair_live<D, MAT, false>(a, I, C0 + jj) : 1;
+            __syncthreads();
+        } else {
+            live += (I - I0) * (C1 - C0);
         }
-        __syncthreads();
         auto next_live = [&](int J) {
-            while (J < C1 && s_live[J - Js] == 0) ++J;
+            while (J < C1 && live[J - C0] == 0) ++J;
             return J;
         };
         const int Jfirst = next_live(Js);
@@ -1758,7 +1809,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(D <= 4 ? 
         if (Jfirst >= C1) {
             const int64_t i = static_cast<int64_t>(I) * TILE + tid;
             if (!diag) yslot[i] = 0.f;
-            __syncthreads();  // s_live is rewritten for the next row tile
+            if (!at_once) __syncthreads();  // s_live is rewritten for the next row tile
             continue;
         }
         for (int half = 0; half < TILE / UNIT; ++half) {
@@ -2006,18 +2057,23 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(D <= 4 ? 
         atomicAdd(a.skip_count, static_cast<unsigned long long>(skipped) * 2 * TILE);
 }
 
-// qw_j = q_j * w_j (the per-source factor of the folded form), once per product.
+// qw_j = q_j * w_j (the per-source factor of the folded form; w null: none), and
+// the tile's bounds for the symmetric products (reach non-null), once per
+// product; one block per tile.
 template <int PREC>
-__global__ __launch_bounds__(BLOCK) void k_prescale(int64_t n_pad, const void *q_, const void *w_, void *qw_,
-                                                    const int *active) {
+__global__ __launch_bounds__(TILE) void k_prescale(int64_t n, const void *q_, const void *w_, void *qw_,
+                                                   const int *__restrict__ reach, int *up, int *lo,
+                                                   const int *active) {
     if (active != nullptr && *active == 0) return;
     using P = Prec<PREC>;
     using T = typename P::T;
-    const typename P::Q *q = static_cast<const typename P::Q *>(q_);
-    const T *w = static_cast<const T *>(w_);
-    T *qw = static_cast<T *>(qw_);
-    const int64_t i = blockIdx.x * static_cast<int64_t>(BLOCK) + threadIdx.x;
-    if (i < n_pad) qw[i] = P::q(q[i]) * w[i];
+    __shared__ double sh[2 * TILE / SUB];
+    const int64_t i = blockIdx.x * static_cast<int64_t>(TILE) + threadIdx.x;
+    const T q = P::q(static_cast<const typename P::Q *>(q_)[i]);
+    if (w_ != nullptr) static_cast<T *>(qw_)[i] = q * static_cast<const T *>(w_)[i];
+    if (reach != nullptr)
+        tile_bounds(fabs(static_cast<double>(q)), reach + blockIdx.x * (TILE / SUB), i < n, up + blockIdx.x,
+                    lo + blockIdx.x, sh);
 }
 
 // y_i = sum_s parts[s][i] (+ shift q_i when square) for i < n, 0 on the padding.
@@ -2028,10 +2084,11 @@ __global__ __launch_bounds__(BLOCK) void k_prescale(int64_t n_pad, const void *q
 // to cover the latency of its dependent loads.)
 template <int PREC>
 constexpr int finish_rows() { return WAVE * static_cast<int>(16 / sizeof(typename Prec<PREC>::T)); }
+// perm non-null: y in the original order (row i to perm[i], the padding left out).
 template <int PREC>
 __global__ __launch_bounds__(BLOCK) void k_kmvp_finish(int64_t n, int64_t n_pad, int ngroups, const void *parts_,
                                                        const void *q_, double shift, int square, void *y_,
-                                                       const int *active) {
+                                                       const int32_t *__restrict__ perm, const int *active) {
     if (active != nullptr && *active == 0) return;
     using P = Prec<PREC>;
     using T = typename P::T;
@@ -2059,7 +2116,11 @@ __global__ __launch_bounds__(BLOCK) void k_kmvp_finish(int64_t n, int64_t n_pad,
 #pragma unroll
         for (int v = 0; v < V; ++v) {
             const int64_t i = i0 + v;
-            y[i] = i >= n ? T(0) : square ? acc[v] + static_cast<T>(shift) * P::q(q[i]) : acc[v];
+            const T val = i >= n ? T(0) : square ? acc[v] + static_cast<T>(shift) * P::q(q[i]) : acc[v];
+            if (perm == nullptr)
+                y[i] = val;
+            else if (i < n)
+                y[perm[i]] = val;
         }
     }
 }
@@ -2733,15 +2794,12 @@ KmvpPlan kmvp_plan(const Prepared &P, int prec) {
     return heuristic_plan(P);
 }
 
-size_t kmvp_scratch_bytes(const Prepared &P) {
-    const size_t parts = static_cast<size_t>(kmvp_parts_slots(P)) * P.n_pad * 8;
-    return align_up(parts, 256) + align_up(static_cast<size_t>(P.n_pad) * 8, 256);
-}
-
 KmvpScratch carve_kmvp_scratch(Carver &cv, const Prepared &P) {
     KmvpScratch k;
     k.parts = cv.take<double>(static_cast<size_t>(kmvp_parts_slots(P)) * P.n_pad);
     k.qw = cv.take<double>(P.n_pad);
+    k.up = cv.take<int>(P.ntiles);
+    k.lo = cv.take<int>(P.ntiles);
     return k;
 }
 
@@ -2938,11 +2996,43 @@ static hipError_t launch_kmvp_d(int dpad, const KArgs &a, int kernel, hipStream_
     }
 }
 
-// The three kernels of one product: prescale, product, partial-sum finish.
-// R: targets (rows), C: sources (columns); R == C for the square product.
-static hipError_t kmvp_run(const Prepared &R, const Prepared &C, int prec, const KmvpPlan &pl, double shift,
-                           const void *q, void *y, const KmvpScratch &sc, const int *active, bool timed_slot,
-                           hipStream_t s) {
+const void *kmvp_weights(const Prepared &P, int prec) {
+    if (P.kernel != KRR_KERNEL_GAUSS) return nullptr;  // the Matern product reads q itself
+    return prec == KRR_FP64 ? static_cast<const void *>(P.w64)
+           : prec == KRR_FP32 ? static_cast<const void *>(P.w32)
+                              : static_cast<const void *>(P.w16);
+}
+
+static hipError_t launch_prescale(const Prepared &C, int prec, const void *q, const KmvpScratch &sc, bool bounds,
+                                  const int *active, hipStream_t s) {
+    const void *w = kmvp_weights(C, prec);
+    const int *reach = bounds ? C.sub_reach : nullptr;
+    if (w == nullptr && reach == nullptr) return hipSuccess;
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(C.ntiles), dim3(TILE), 0, s, C.n, q, w, sc.qw, reach, sc.up, sc.lo, active);
+        return hipGetLastError();
+    };
+    return prec == KRR_FP64 ? go(k_prescale<KRR_FP64>) : prec == KRR_FP32 ? go(k_prescale<KRR_FP32>) : go(k_prescale<KRR_BF16>);
+}
+
+static hipError_t launch_finish(const Prepared &R, int prec, int ng, double shift, bool square, const void *q, void *y,
+                                const int32_t *perm, const KmvpScratch &sc, const int *active, hipStream_t s) {
+    auto go = [&](auto kern, int rows) {
+        hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>((R.n_pad + rows - 1) / rows)), dim3(BLOCK), 0, s, R.n,
+                           R.n_pad, ng, sc.parts, q, shift, square ? 1 : 0, y, perm, active);
+        return hipGetLastError();
+    };
+    return prec == KRR_FP64   ? go(k_kmvp_finish<KRR_FP64>, finish_rows<KRR_FP64>())
+           : prec == KRR_FP32 ? go(k_kmvp_finish<KRR_FP32>, finish_rows<KRR_FP32>())
+                              : go(k_kmvp_finish<KRR_BF16>, finish_rows<KRR_BF16>());
+}
+
+// One product kernel on prescaled sources.  R: targets (rows), C: sources
+// (columns); R == C for the square product.  Returns in *parts the partial-sum
+// slots it left in sc.parts (0: it wrote y, with the shift).
+static hipError_t kmvp_launch(const Prepared &R, const Prepared &C, int prec, const KmvpPlan &pl, double shift,
+                              const void *q, void *y, const KmvpScratch &sc, const int *active, bool timed_slot,
+                              int *parts, hipStream_t s) {
     const bool square = (&R == &C);
     // the symmetric kernels for square products (plan.sym_gs > 0)
     const bool sym = square && pl.sym_gs > 0;
@@ -2974,19 +3064,13 @@ static hipError_t kmvp_run(const Prepared &R, const Prepared &C, int prec, const
     a.skip_count = nullptr;
     const bool use_parts = a.ngroups > 1 || sym;
     a.out = use_parts ? sc.parts : y;
-    const void *w = prec == KRR_FP64 ? static_cast<const void *>(C.w64)
-                    : prec == KRR_FP32 ? static_cast<const void *>(C.w32)
-                                       : static_cast<const void *>(C.w16);
-    a.w = w;
-    const dim3 gc((C.n_pad + BLOCK - 1) / BLOCK);
-    if (C.kernel == KRR_KERNEL_GAUSS) {  // the Matern product reads q itself
-        switch (prec) {
-            case KRR_FP64: hipLaunchKernelGGL(k_prescale<KRR_FP64>, gc, dim3(BLOCK), 0, s, C.n_pad, q, w, sc.qw, active); break;
-            case KRR_FP32: hipLaunchKernelGGL(k_prescale<KRR_FP32>, gc, dim3(BLOCK), 0, s, C.n_pad, q, w, sc.qw, active); break;
-            default: hipLaunchKernelGGL(k_prescale<KRR_BF16>, gc, dim3(BLOCK), 0, s, C.n_pad, q, w, sc.qw, active); break;
-        }
-        KRR_HIP(hipGetLastError());
-    }
+    a.w = kmvp_weights(C, prec);
+    a.box = C.box;
+    a.up = sc.up;
+    a.lo = sc.lo;
+    a.clear = prec == KRR_FP64 ? EPS_FP64 : EPS_FP32;
+    for (int t = 1; t < C.ntiles; t *= 2) ++a.clear;  // + ceil(log2(tiles))
+    *parts = use_parts ? a.ngroups : 0;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     const bool timed =
         timed_slot && profile_slot(prec, static_cast<double>(R.n) * static_cast<double>(C.n), &ev0, &ev1,
@@ -3019,37 +3103,54 @@ static hipError_t kmvp_run(const Prepared &R, const Prepared &C, int prec, const
     }
     KRR_HIP(e);
     if (timed) KRR_HIP(hipEventRecord(ev1, s));
-    if (use_parts) {
-        const int sq = square ? 1 : 0;
-        const int ng = a.ngroups;
-        auto fgrid = [&](int rows) { return dim3(static_cast<unsigned>((R.n_pad + rows - 1) / rows)); };
-        switch (prec) {
-            case KRR_FP64:
-                hipLaunchKernelGGL(k_kmvp_finish<KRR_FP64>, fgrid(finish_rows<KRR_FP64>()), dim3(BLOCK), 0, s, R.n,
-                                   R.n_pad, ng, sc.parts, q, shift, sq, y, active);
-                break;
-            case KRR_FP32:
-                hipLaunchKernelGGL(k_kmvp_finish<KRR_FP32>, fgrid(finish_rows<KRR_FP32>()), dim3(BLOCK), 0, s, R.n,
-                                   R.n_pad, ng, sc.parts, q, shift, sq, y, active);
-                break;
-            default:
-                hipLaunchKernelGGL(k_kmvp_finish<KRR_BF16>, fgrid(finish_rows<KRR_BF16>()), dim3(BLOCK), 0, s, R.n,
-                                   R.n_pad, ng, sc.parts, q, shift, sq, y, active);
-                break;
-        }
-        KRR_HIP(hipGetLastError());
-    }
     return hipSuccess;
 }
 
-hipError_t kmvp_sorted(const Prepared &P, int prec, double shift, const void *q, void *y, const KmvpScratch &sc,
-                       const int *active, hipStream_t s) {
+// The three kernels of one product: prescale, product, partial-sum finish.
+static hipError_t kmvp_run(const Prepared &R, const Prepared &C, int prec, const KmvpPlan &pl, double shift,
+                           const void *q, void *y, const KmvpScratch &sc, const int *active, bool timed_slot,
+                           hipStream_t s) {
+    const bool square = (&R == &C);
+    int parts = 0;
+    KRR_HIP(launch_prescale(C, prec, q, sc, square && pl.sym_gs > 0, active, s));
+    KRR_HIP(kmvp_launch(R, C, prec, pl, shift, q, y, sc, active, timed_slot, &parts, s));
+    return parts > 0 ? launch_finish(R, prec, parts, shift, square, q, y, nullptr, sc, active, s) : hipSuccess;
+}
+
+static KmvpPlan square_plan(const Prepared &P, int prec) {
     KmvpPlan pl;
     if (use_sym_kernel(P, prec))
         pl.sym_gs = kmvp_sym_group_tiles(P);
     else
         pl = kmvp_plan(P, prec);
-    return kmvp_run(P, P, prec, pl, shift, q, y, sc, active, true, s);
+    return pl;
+}
+
+hipError_t kmvp_sorted(const Prepared &P, int prec, double shift, const void *q, void *y, const KmvpScratch &sc,
+                       const int *active, hipStream_t s) {
+    return kmvp_run(P, P, prec, square_plan(P, prec), shift, q, y, sc, active, true, s);
+}
+
+int kmvp_live_slots(const Prepared &P, int prec) {
+    if (use_sym_kernel(P, prec)) return kmvp_sym_ngroups(P);
+    const int ng = kmvp_ngroups(P);
+    return ng > 1 ? ng : 0;
+}
+
+hipError_t kmvp_prescale(const Prepared &P, int prec, const void *q, const KmvpScratch &sc, const int *active,
+                         hipStream_t s) {
+    return launch_prescale(P, prec, q, sc, use_sym_kernel(P, prec), active, s);
+}
+
+hipError_t kmvp_core(const Prepared &P, int prec, double shift, const void *q, void *y, const KmvpScratch &sc,
+                     const int *active, hipStream_t s) {
+    int parts = 0;
+    return kmvp_launch(P, P, prec, square_plan(P, prec), shift, q, y, sc, active, true, &parts, s);
+}
+
+hipError_t kmvp_finish(const Prepared &P, int prec, double shift, const void *q, void *y, const int32_t *perm,
+                       const KmvpScratch &sc, const int *active, hipStream_t s) {
+    return launch_finish(P, prec, kmvp_live_slots(P, prec), shift, true, q, y, perm, sc, active, s);
 }
 
 // Rectangular product y = K_hat(targets, sources) q on sorted vectors (targets

@@ -153,6 +153,11 @@ struct Prepared {
     // 2 split_chunks(dpad) octets per point, octet-major ([octet][n_pad]), for dpad <= 48
     void *slot32 = nullptr;
     void *slot16 = nullptr;
+    // per tile, dpad <= 16 (the symmetric products): its bounding box in scaled
+    // coordinates ([tile][lo, hi][dpad]) and, per 32 points of it, the ceiling of
+    // -log2 of the kernel across their box (neglog2_kernel; -1: no points)
+    double *box = nullptr;
+    int *sub_reach = nullptr;  // [tile][8]
     int *flags = nullptr;     // [0]: non-finite input seen
     int kernel = KRR_KERNEL_GAUSS;  // krr_kernel of the products on this set
 };
@@ -168,13 +173,21 @@ Prepared carve_prepared(Carver &cv, int64_t n, int d);
 // prep_temp_bytes(n).  Returns a HIP error code.
 // sigma: the Gaussian bandwidth, or the Matern length scale h (kernel ==
 // KRR_KERNEL_MATERN32: coordinates scaled by sqrt(3) / h).
+// v (optional): the product's vector, gathered and prescaled on the way.
 // need: the precisions whose offsets, weights and slots are written (prep_need;
 // the others' arrays stay as they were).
 constexpr int PREP_FP64 = 1, PREP_FP32 = 2, PREP_BF16 = 4;
 constexpr int PREP_PM = 8;  // the point-major copies, all precisions (set by prepare_points itself)
 constexpr int prep_need(int prec) { return prec == KRR_FP64 ? PREP_FP64 : prec == KRR_FP32 ? PREP_FP32 : PREP_BF16; }
+struct PrepVec {
+    int prec = KRR_FP64;
+    const void *q = nullptr;  // original order (double; float for FP32 and BF16)
+    void *qs = nullptr;       // sorted, zero-padded: double, float, or bf16 bits
+    void *qw = nullptr;       // q_j w_j (KmvpScratch::qw)
+    int *up = nullptr, *lo = nullptr;  // KmvpScratch::up, lo
+};
 hipError_t prepare_points(Prepared &P, const double *x, double sigma, void *temp, size_t temp_bytes,
-                          hipStream_t s, int kernel, int need);
+                          hipStream_t s, int kernel, int need, const PrepVec *v = nullptr);
 // KRR_KMVP_VALU=1: products take the VALU kernels (kmvp.hip).
 bool use_valu_kernel();
 
@@ -197,12 +210,26 @@ struct KmvpPlan {
 struct KmvpScratch {
     void *parts = nullptr;
     void *qw = nullptr;
+    int *up = nullptr, *lo = nullptr;  // per tile: its sources' size and its rows' floor (tile_bounds)
 };
 int kmvp_max_splits(const Prepared &P);
 int kmvp_parts_slots(const Prepared &P);
 KmvpPlan kmvp_plan(const Prepared &P, int prec);  // tuned, else a heuristic
-size_t kmvp_scratch_bytes(const Prepared &P);
 KmvpScratch carve_kmvp_scratch(Carver &cv, const Prepared &P);
+// The three parts of a square product: qw (and the tile bounds), the kernel
+// (partial sums in sc.parts, or y itself when kmvp_live_slots is 0), and the sum
+// of the partial sums + shift q, in sorted order or (perm) scattered to the
+// original one.
+hipError_t kmvp_prescale(const Prepared &P, int prec, const void *q, const KmvpScratch &sc, const int *active,
+                         hipStream_t s);
+hipError_t kmvp_core(const Prepared &P, int prec, double shift, const void *q, void *y, const KmvpScratch &sc,
+                     const int *active, hipStream_t s);
+hipError_t kmvp_finish(const Prepared &P, int prec, double shift, const void *q, void *y, const int32_t *perm,
+                       const KmvpScratch &sc, const int *active, hipStream_t s);
+// The partial-sum slots a square product of this set and precision leaves (0:
+// none, it writes y itself).
+int kmvp_live_slots(const Prepared &P, int prec);
+const void *kmvp_weights(const Prepared &P, int prec);  // w_j in the precision, null for Matern
 // y = K_hat q + shift q on sorted vectors.  active: optional device flag; when it
 // reads 0 the kernels return at once.
 hipError_t kmvp_sorted(const Prepared &P, int prec, double shift, const void *q, void *y, const KmvpScratch &sc,
@@ -303,6 +330,66 @@ __host__ __device__ inline float bf16_to_f32(uint16_t h) {
     float f;
     __builtin_memcpy(&f, &u, 4);
     return f;
+}
+
+// ---------------------------------------------------------------- negligible tile pairs
+//
+// A tile pair is left out of a symmetric product when everything it could add
+// is below 2^-40 (FP32, BF16; FP64 2^-69) of what its rows already hold: with
+// up_J >= log2 sum_{j in J} |q_j| and lo_I <= log2 min_{i in I} sum_j k_ij |q_j|,
+// the sources of J add at most 2^(up_J - a) to a row of I, a = -log2 of the
+// kernel across the gap between the tiles' boxes, and all the tiles left out
+// together at most 2^-40 (2^-69) 2^lo_I when a >= up_J - lo_I + 40 (69) +
+// log2(tiles).  That is 2^-16 of one rounding of the row's own sum, so the sums
+// come out the same to the last bit but for one row in about 2^16; a q that is
+// zero (or tiny) around a row lowers its floor, and nothing is left out there.
+// The floor of a tile's rows is the least over its eighths (32 points s) of
+// max(min_{i in s} |q_i|, 2^-reach_s sum_{i in s} |q_i|): every row has itself
+// (k = 1) and the points around it.
+constexpr int SUB = 32;               // points per eighth of a tile
+constexpr int NEVER = 1 << 28;        // up of a tile that is never left out (and -lo)
+constexpr int EPS_FP32 = 40, EPS_FP64 = 69;
+
+// -log2 of the kernel at squared scaled distance d2.
+__device__ __forceinline__ double neglog2_kernel(double d2, bool matern) {
+    if (!matern) return d2;
+    const double s = sqrt(d2);
+    return 1.4426950408889634 * s - static_cast<double>(__builtin_amdgcn_logf(static_cast<float>(1.0 + s)));
+}
+
+// up and lo of one tile from its 256 entries: thread tid of a 256-thread block
+// passes |q| of its point (0 on the padding; any NaN makes the tile NEVER left
+// out).  sh: 16 doubles.  Ends with the values stored by thread 0.
+__device__ __forceinline__ void tile_bounds(double aq, const int *__restrict__ reach, bool real, int *up, int *lo,
+                                            double *sh) {
+    double sum = aq, mn = real ? aq : INFINITY;
+#pragma unroll
+    for (int o = SUB / 2; o > 0; o /= 2) {
+        sum += __shfl_xor(sum, o, SUB);
+        mn = fmin(mn, __shfl_xor(mn, o, SUB));
+    }
+    if (threadIdx.x % SUB == 0) {
+        sh[threadIdx.x / SUB] = sum;
+        sh[8 + threadIdx.x / SUB] = mn;
+    }
+    __syncthreads();
+    // one lane per eighth, combined by three exchanges
+    if (threadIdx.x < TILE / SUB) {
+        const int k = threadIdx.x, r = reach[k];
+        double l1 = sh[k];
+        double fl = r < 0 ? INFINITY : fmax(sh[8 + k], __builtin_amdgcn_ldexp(l1, -(r < 4000 ? r : 4000)));
+#pragma unroll
+        for (int o = TILE / SUB / 2; o > 0; o /= 2) {
+            l1 += __shfl_xor(l1, o, TILE / SUB);
+            fl = fmin(fl, __shfl_xor(fl, o, TILE / SUB));
+        }
+        // frexp exponents: v < 2^e and v >= 2^(e - 1)
+        const bool fin = l1 < INFINITY;  // false for NaN
+        if (k == 0) {
+            *up = !fin ? NEVER : l1 > 0.0 ? __builtin_amdgcn_frexp_exp(l1) : -NEVER / 2;
+            *lo = fin && fl > 0.0 && fl < INFINITY ? __builtin_amdgcn_frexp_exp(fl) - 1 : -NEVER;
+        }
+    }
 }
 
 #define KRR_HIP(expr)                                   \

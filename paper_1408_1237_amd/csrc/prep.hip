@@ -52,6 +52,10 @@ Prepared carve_prepared(Carver &cv, int64_t n, int d) {
         P.slot32 = cv.take<half8_t>(static_cast<size_t>(oct) * P.n_pad);
         P.slot16 = cv.take<half8_t>(static_cast<size_t>(oct) * P.n_pad);
     }
+    if (P.dpad <= 16) {
+        P.box = cv.take<double>(2 * static_cast<size_t>(P.ntiles) * P.dpad);
+        P.sub_reach = cv.take<int>(static_cast<size_t>(P.ntiles) * (TILE / SUB));
+    }
     P.flags = cv.take<int>(4);
     return P;
 }
@@ -272,12 +276,15 @@ __device__ __forceinline__ void store_slots(const Prepared &P, int64_t j, const 
 
 template <int D, bool MAT>
 __global__ __launch_bounds__(TILE) void k_tiles(const double *__restrict__ x, int64_t n, int d, double scale,
-                                                const int32_t *__restrict__ sorted_idx, Prepared P, int need) {
+                                                const int32_t *__restrict__ sorted_idx, Prepared P, int need,
+                                                PrepVec pv) {
     constexpr int CH = D < 16 ? D : 16;  // coordinates per pass of the box
     constexpr int LANES = 16;            // lanes per coordinate
     __shared__ double s_v[CH][TILE + 4];
     __shared__ double s_lo[D], s_hi[D], s_median[D];
     __shared__ double lds[TILE / WAVE];
+    // D <= 16: per 32 points, the squared extent of each coordinate
+    __shared__ double s_ext[D <= 16 ? TILE / SUB : 1][D <= 16 ? D : 1];
     const int J = blockIdx.x, tid = threadIdx.x;
     const int64_t j = static_cast<int64_t>(J) * TILE + tid;
     const bool real = j < n;
@@ -313,7 +320,34 @@ __global__ __launch_bounds__(TILE) void k_tiles(const double *__restrict__ x, in
                 s_hi[c0 + k] = hi;
             }
         }
+        if constexpr (D <= 16) {
+            const int sub = tid % (TILE / SUB), kk = tid / (TILE / SUB);
+            if (kk < D) {
+                double lo = INFINITY, hi = -INFINITY;
+#pragma unroll 8
+                for (int i = 0; i < SUB; ++i) {
+                    // rotated by the eighth: its 8 lanes of a coordinate read other banks
+                    const double v = s_v[kk][sub * SUB + ((i + 2 * sub) & (SUB - 1))];
+                    lo = fmin(lo, v);
+                    hi = fmax(hi, v);
+                }
+                s_ext[sub][kk] = (hi - lo) * (hi - lo);
+            }
+        }
         __syncthreads();
+    }
+    if constexpr (D <= 16) {
+        if (tid < D) {
+            P.box[(static_cast<int64_t>(J) * 2 + 0) * D + tid] = s_lo[tid];
+            P.box[(static_cast<int64_t>(J) * 2 + 1) * D + tid] = s_hi[tid];
+        }
+        if (tid < TILE / SUB) {
+            double d2 = 0.0;
+            for (int k = 0; k < D; ++k) d2 += s_ext[tid][k];
+            // 1e-6: the products' kernel values carry their own rounding
+            const double r = ceil(neglog2_kernel(d2 * 1.000001, MAT) + 1e-3);
+            P.sub_reach[J * (TILE / SUB) + tid] = tid * SUB >= nreal ? -1 : (r < 1e6 ? static_cast<int>(r) : 1000000);
+        }
     }
     // the radius about the box centre decides between the two anchors
     double sqc = 0.0;
@@ -328,13 +362,14 @@ __global__ __launch_bounds__(TILE) void k_tiles(const double *__restrict__ x, in
         // position); the point of rank (nreal - 1) / 2 is the median
 #pragma unroll 1
         for (int t = 0; t < d; ++t) {
-            const double v = real ? x[static_cast<int64_t>(idx) * d + t] * scale : 0.0;
+            const double v = real ? x[static_cast<int64_t>(idx) * d + t] * scale : INFINITY;  // the padding ranks last
             s_v[0][tid] = v;
             if (tid == 0) s_median[t] = 0.5 * (s_lo[t] + s_hi[t]);  // kept if a non-finite value breaks the ranks
             __syncthreads();
             if (real) {
                 int rank = 0;
-                for (int k = 0; k < nreal; ++k) {
+#pragma unroll 16
+                for (int k = 0; k < TILE; ++k) {
                     const double u = s_v[0][k];
                     rank += (u < v || (u == v && k < tid)) ? 1 : 0;
                 }
@@ -387,48 +422,81 @@ __global__ __launch_bounds__(TILE) void k_tiles(const double *__restrict__ x, in
         // is 0 in FP32) beyond (R + 111)^2; 1e-4 margin
         const double u = MAT ? sqrt(r2) + 111.0 : sqrt(r2) + sqrt(200.0 + r2 - nj);
         P.tile_far[J] = static_cast<float>(1.0001 * u * u);
-        // FP64 Gaussian product: exponents <= -1100 (exp2 is 0 in FP64)
-        const double u64 = sqrt(r2) + sqrt(1100.0 + r2 - nj);
+        // FP64: exponents <= -1100, or for Matern e^-s at s >= 760 (0 in FP64)
+        const double u64 = MAT ? sqrt(r2) + 760.0 : sqrt(r2) + sqrt(1100.0 + r2 - nj);
         P.tile_far64[J] = static_cast<float>(1.0001 * u64 * u64);
     }
+    double w64 = 0.0;
+    float w32 = 0.f, w16 = 0.f;
     if (need & PREP_FP64) {
         P.sq64[j] = sq64;
-        P.w64[j] = (real && r2 <= WIDE_R2_FP64) ? exp2(nj - sq64) : 0.0;
+        P.w64[j] = w64 = (real && r2 <= WIDE_R2_FP64) ? exp2(nj - sq64) : 0.0;
     }
-    if (need & PREP_FP32) P.w32[j] = (real && r2 <= WIDE_R2_FP32) ? static_cast<float>(exp2(nj - sq32)) : 0.0f;
-    if (need & PREP_BF16) P.w16[j] = (real && r2 <= WIDE_R2_FP32) ? static_cast<float>(exp2(nj - sq16)) : 0.0f;
+    if (need & PREP_FP32) P.w32[j] = w32 = (real && r2 <= WIDE_R2_FP32) ? static_cast<float>(exp2(nj - sq32)) : 0.0f;
+    if (need & PREP_BF16) P.w16[j] = w16 = (real && r2 <= WIDE_R2_FP32) ? static_cast<float>(exp2(nj - sq16)) : 0.0f;
+    // the product's vector: sorted copy, prescaled copy and the tile's bounds
+    // (what a gather, a rounding and a prescale launch did, about 4.7 us each)
+    if (pv.q != nullptr) {
+        double aq;
+        if (pv.prec == KRR_FP64) {
+            const double q = real ? static_cast<const double *>(pv.q)[idx] : 0.0;
+            static_cast<double *>(pv.qs)[j] = q;
+            static_cast<double *>(pv.qw)[j] = q * w64;
+            aq = fabs(q);
+        } else {
+            float q = real ? static_cast<const float *>(pv.q)[idx] : 0.f;
+            if (pv.prec == KRR_BF16) {
+                const uint16_t h = f32_to_bf16_rne(q);
+                static_cast<uint16_t *>(pv.qs)[j] = h;
+                q = bf16_to_f32(h);
+                static_cast<float *>(pv.qw)[j] = q * w16;
+            } else {
+                static_cast<float *>(pv.qs)[j] = q;
+                static_cast<float *>(pv.qw)[j] = q * w32;
+            }
+            aq = fabs(static_cast<double>(q));
+        }
+        if constexpr (D <= 16) {
+            __threadfence_block();
+            __syncthreads();  // sub_reach was written above by this block
+            tile_bounds(aq, P.sub_reach + J * (TILE / SUB), real, pv.up + J, pv.lo + J, &s_v[0][0]);
+        }
+    }
 }
 
 template <int D>
-static hipError_t launch_tiles(const Prepared &P, const double *x, const int32_t *order, int need, hipStream_t s) {
+static hipError_t launch_tiles(const Prepared &P, const double *x, const int32_t *order, int need, const PrepVec &v,
+                               hipStream_t s) {
     if (P.kernel == KRR_KERNEL_MATERN32)
-        hipLaunchKernelGGL((k_tiles<D, true>), dim3(P.ntiles), dim3(TILE), 0, s, x, P.n, P.d, P.scale, order, P, need);
+        hipLaunchKernelGGL((k_tiles<D, true>), dim3(P.ntiles), dim3(TILE), 0, s, x, P.n, P.d, P.scale, order, P, need,
+                           v);
     else
         hipLaunchKernelGGL((k_tiles<D, false>), dim3(P.ntiles), dim3(TILE), 0, s, x, P.n, P.d, P.scale, order, P,
-                           need);
+                           need, v);
     return hipGetLastError();
 }
 
-static hipError_t build_tiles(const Prepared &P, const double *x, const int32_t *order, int need, hipStream_t s) {
+static hipError_t build_tiles(const Prepared &P, const double *x, const int32_t *order, int need, const PrepVec &v,
+                              hipStream_t s) {
     switch (P.dpad) {
-        case 1: return launch_tiles<1>(P, x, order, need, s);
-        case 2: return launch_tiles<2>(P, x, order, need, s);
-        case 3: return launch_tiles<3>(P, x, order, need, s);
-        case 4: return launch_tiles<4>(P, x, order, need, s);
-        case 6: return launch_tiles<6>(P, x, order, need, s);
-        case 8: return launch_tiles<8>(P, x, order, need, s);
-        case 12: return launch_tiles<12>(P, x, order, need, s);
-        case 16: return launch_tiles<16>(P, x, order, need, s);
-        case 24: return launch_tiles<24>(P, x, order, need, s);
-        case 32: return launch_tiles<32>(P, x, order, need, s);
-        case 48: return launch_tiles<48>(P, x, order, need, s);
-        case 64: return launch_tiles<64>(P, x, order, need, s);
+        case 1: return launch_tiles<1>(P, x, order, need, v, s);
+        case 2: return launch_tiles<2>(P, x, order, need, v, s);
+        case 3: return launch_tiles<3>(P, x, order, need, v, s);
+        case 4: return launch_tiles<4>(P, x, order, need, v, s);
+        case 6: return launch_tiles<6>(P, x, order, need, v, s);
+        case 8: return launch_tiles<8>(P, x, order, need, v, s);
+        case 12: return launch_tiles<12>(P, x, order, need, v, s);
+        case 16: return launch_tiles<16>(P, x, order, need, v, s);
+        case 24: return launch_tiles<24>(P, x, order, need, v, s);
+        case 32: return launch_tiles<32>(P, x, order, need, v, s);
+        case 48: return launch_tiles<48>(P, x, order, need, v, s);
+        case 64: return launch_tiles<64>(P, x, order, need, v, s);
         default: return hipErrorInvalidValue;
     }
 }
 
 hipError_t prepare_points(Prepared &P, const double *x, double sigma, void *temp, size_t temp_bytes,
-                          hipStream_t s, int kernel, int need) {
+                          hipStream_t s, int kernel, int need, const PrepVec *v) {
     const int64_t n = P.n;
     const int d = P.d;
     P.kernel = kernel;
@@ -462,7 +530,7 @@ hipError_t prepare_points(Prepared &P, const double *x, double sigma, void *temp
         hipLaunchKernelGGL(k_rank, dim3(static_cast<unsigned>((n + WAVE - 1) / WAVE)), dim3(RANK_THREADS), 0, s, k0,
                            static_cast<int>(n), v1);
         KRR_HIP(hipGetLastError());
-        return build_tiles(P, x, v1, need, s);
+        return build_tiles(P, x, v1, need, v ? *v : PrepVec{}, s);
     }
     rocprim::double_buffer<uint64_t> keys(k0, k1);
     rocprim::double_buffer<int32_t> vals(v0, v1);
@@ -472,7 +540,7 @@ hipError_t prepare_points(Prepared &P, const double *x, double sigma, void *temp
     if (bytes > sort_cap) return hipErrorInvalidValue;
     KRR_HIP(rocprim::radix_sort_pairs(sort_tmp, bytes, keys, vals, static_cast<size_t>(n), 0u,
                                       static_cast<unsigned>(dm * bits), s));
-    return build_tiles(P, x, static_cast<const int32_t *>(vals.current()), need, s);
+    return build_tiles(P, x, static_cast<const int32_t *>(vals.current()), need, v ? *v : PrepVec{}, s);
 }
 
 // ---------------------------------------------------------------- gather / scatter
