@@ -4,17 +4,19 @@
 //   dl/dx_i   = (1/sigma^2) sum_j (lambda_i w_j + lambda_j w_i) K_hat_ij (x_i - x_j)
 //   dl/dlogs  = -(1/sigma^2) sum_ij lambda_i w_j K_hat_ij ||x_i - x_j||^2
 //   dl/dlogg  = -gamma lambda^T w.
-// One pass over the pairs: per target row the kernel accumulates
-//   Aw = sum_j K_hat_ij w_j D_ij,  Al = sum_j K_hat_ij lambda_j D_ij,
-//   S  = sum_j K_hat_ij w_j ||D_ij||^2,
-// with D_ij = x_i - x_j in scaled coordinates formed from tile anchors and
-// offsets (t - o_j); the epilogue combines them with lambda_i, w_i in FP64.
-// Sources arrive through scalar loads (wave-uniform addresses), as in the single
-// product.  Precision: FP64 throughout (kernel values by exp2_f64), or FP32
-// offsets, kernel values and sums.  At a solution w of an ill-conditioned system
-// the row sums cancel heavily (|w| large with alternating signs), so the FP32
-// gradient carries relative row errors far above FP32 rounding; FP64 costs about
-// 1.8x the FP32 pass, small beside the solve that produces w.
+// The coefficient c_ij = (lambda_i w_j + lambda_j w_i) K_hat_ij is symmetric, so
+// one pass over the pairs needs one vector and one scalar per target row,
+//   A_i = sum_j c_ij D_ij,   S_i = sum_j c_ij ||D_ij||^2,
+// with D_ij = x_i - x_j in scaled coordinates, and
+//   dl/dx_i = A_i / (sigma^2 c),  dl/dlogs = -1/2 sum_i S_i / (sigma^2 c^2)
+// (c the coordinate scale; lambda == w: c_ij = 2 w_i w_j K_hat_ij, whose 2 w_i is
+// applied once per row).  Precision: FP64 throughout, or FP32 offsets, kernel
+// values and sums.  At a solution w of an ill-conditioned system (|w| large with
+// alternating signs) the row sums cancel heavily, so the FP32 gradient carries
+// relative row errors far above FP32 rounding; FP64 is small beside the solve
+// that produces w.
+#include <type_traits>
+
 #include "krylov.h"
 
 namespace krr {
@@ -39,12 +41,15 @@ struct GArgs {
     const void *off;  // offsets in the pass's precision, SoA
     const void *ws;   // w in sorted order
     const void *ls;   // lambda in sorted order
-    void *parts;      // [splits][n_pad][2D+1] (D+1 when lambda == w)
+    void *parts;      // [splits][n_pad][D + 1]: A_i, S_i of a column range
 };
+
+// VALU form: one lane per target row, sources at wave-uniform addresses (scalar
+// loads).
 
 template <int D, bool SAME, typename T>
 __global__ __launch_bounds__(BLOCK) void k_grad(GArgs a) {
-    constexpr int NA = SAME ? D + 1 : 2 * D + 1;
+    constexpr int NA = D + 1;
     constexpr int U = D <= 4 ? 8 : D <= 8 ? 4 : 2;
     using G = GP<T>;
     const T *__restrict__ off = static_cast<const T *>(a.off);
@@ -60,12 +65,10 @@ __global__ __launch_bounds__(BLOCK) void k_grad(GArgs a) {
         aI[k] = a.anchor[static_cast<int64_t>(bx) * D + k];
         oi[k] = off[k * n_pad + i];
     }
-    T Aw[D], Al[SAME ? 1 : D], S = T(0);
+    const T wi = wsrc[i], li = lsrc[i];
+    T A[D], S = T(0);
 #pragma unroll
-    for (int k = 0; k < D; ++k) {
-        Aw[k] = T(0);
-        if (!SAME) Al[k] = T(0);
-    }
+    for (int k = 0; k < D; ++k) A[k] = T(0);
     const int J0 = by * a.tps;
     const int J1 = min(a.ntiles, J0 + a.tps);
     for (int J = J0; J < J1; ++J) {
@@ -86,25 +89,224 @@ __global__ __launch_bounds__(BLOCK) void k_grad(GArgs a) {
                     r2 = G::fma(dl[k], dl[k], r2);
                 }
                 const T kv = G::ex2(-r2);
-                const T kw = kv * wsrc[j];
-                S = G::fma(kw, r2, S);
+                const T c = kv * (SAME ? wsrc[j] : G::fma(li, wsrc[j], lsrc[j] * wi));
+                S = G::fma(c, r2, S);
 #pragma unroll
-                for (int k = 0; k < D; ++k) Aw[k] = G::fma(kw, dl[k], Aw[k]);
-                if (!SAME) {
-                    const T kl = kv * lsrc[j];
-#pragma unroll
-                    for (int k = 0; k < D; ++k) Al[k] = G::fma(kl, dl[k], Al[k]);
-                }
+                for (int k = 0; k < D; ++k) A[k] = G::fma(c, dl[k], A[k]);
             }
         }
     }
+    const T f = SAME ? T(2) * wi : T(1);
     T *out = static_cast<T *>(a.parts) + (static_cast<int64_t>(by) * n_pad + i) * NA;
 #pragma unroll
-    for (int k = 0; k < D; ++k) out[k] = Aw[k];
-    if (!SAME)
+    for (int k = 0; k < D; ++k) out[k] = f * A[k];
+    out[D] = f * S;
+}
+
+// FP64 matrix-core form, compiled dimensions 12 and 16.  Both contractions of a
+// pair run on v_mfma_f64_16x16x4f64: the squared distance, -TN ||t' - o'||^2 =
+// [2 TN t', -TN |t'|^2, TN, TN] . [o', 1, -e0, -e1], and the row sums c_ij o'_j
+// (c as A operand straight from the exponents' accumulator layout, the sources'
+// coordinates as the 16 columns of B).  All coordinates are taken from the row
+// tile's anchor, x' = x - a_I (sources shifted when they are staged, |o'|^2 =
+// e0 + e1 in the two halves the staging threads hold), so the target operand is
+// built once per block and A_i = t'_i sum_j c_ij - sum_j c_ij o'_j; the pairs
+// that matter are within a few scaled units of the row tile, whose offsets stay
+// as short.  The VALU does the table exponential and the coefficient.  A pair
+// costs no subtraction and no fused multiply-add per coordinate: at N = 50,000,
+// d = 16 the pass took 7.7 ms in the VALU form with lambda and w summed apart.
+// A wave owns 2 groups of 16 targets, a block 128 rows of a row tile; sources are
+// staged 128 at a time, double-buffered (45 KB, two blocks per CU by registers).
+typedef double gdx4 __attribute__((ext_vector_type(4)));
+typedef double gdx2 __attribute__((ext_vector_type(2)));
+
+template <int D, bool SAME>
+__global__ __launch_bounds__(BLOCK, 2) void k_grad_mg(GArgs a) {
+    static_assert(D == 12 || D == 16, "one 16-column block of coordinates; whole chunks");
+    constexpr int NA = D + 1, TN = 256, RG = 2, ROWS = 128, SC = 128, CPT = TILE / SC;
+    constexpr int DK = D / 4 + 1;
+    constexpr int LDO = SC + 18;  // row stride 144 mod 256 bytes: both operands' reads spread over the banks
+    constexpr int PER = D / 2;    // coordinates staged per thread
+    __shared__ __align__(16) double s_o[2][16][LDO];
+    __shared__ __align__(16) double s_w[2][SC], s_l[SAME ? 1 : 2][SC];
+    __shared__ double s_e[2][2][SC];
+    __shared__ double s_tab[TN];
+    const double *__restrict__ off = static_cast<const double *>(a.off);
+    const double *__restrict__ wsrc = static_cast<const double *>(a.ws);
+    const double *__restrict__ lsrc = static_cast<const double *>(a.ls);
+    const int64_t n_pad = a.n_pad;
+    const int nrb = 2 * a.nrowblocks;
+    const int bh = blockIdx.x % nrb, by = blockIdx.x / nrb;
+    const int I = bh / 2;
+    const int tid = threadIdx.x, lane = tid % WAVE, r16 = lane % 16, g = lane / 16;
+    // source of A row r16, so that lane l's four exponents are sources 4 g + v
+    const int asrc = (r16 % 4) * 4 + r16 / 4;
+    const int64_t row0 = static_cast<int64_t>(I) * TILE + (bh % 2) * ROWS + (tid / WAVE) * (16 * RG);
+    for (int k = tid; k < TN; k += BLOCK) s_tab[k] = EXP2_TABLE256[k];
+    if constexpr (D < 16) {  // the unused coordinate columns stay zero
+        for (int k = D * LDO + tid; k < 16 * LDO; k += BLOCK) s_o[0][0][k] = s_o[1][0][k] = 0.0;
+    }
+
+    // the target operand of each group: coordinate 4 kc + g of its slots
+    double bval[RG][DK], li[RG], wi[RG];
 #pragma unroll
-        for (int k = 0; k < D; ++k) out[D + k] = Al[k];
-    out[NA - 1] = S;
+    for (int rg = 0; rg < RG; ++rg) {
+        const int64_t i = row0 + rg * 16 + r16;
+        double tt = 0.0;
+#pragma unroll
+        for (int kc = 0; kc < D / 4; ++kc) {
+            const double t = off[(4 * kc + g) * n_pad + i];
+            bval[rg][kc] = 2.0 * TN * t;
+            tt = __builtin_fma(t, t, tt);
+        }
+        tt += __shfl_xor(tt, 16, WAVE);
+        tt += __shfl_xor(tt, 32, WAVE);
+        bval[rg][D / 4] = g == 0 ? -TN * tt : (g < 3 ? static_cast<double>(TN) : 0.0);
+        li[rg] = SAME ? 0.0 : lsrc[i];
+        wi[rg] = wsrc[i];
+    }
+    // staging: source tid % 128, coordinates PER (tid / 128) .. + PER - 1
+    const int scol = tid % SC, shalf = tid / SC;
+    double st_o[PER], st_w = 0.0, st_l = 0.0;
+    auto stage_load = [&](int ci) {
+        const int J = ci / CPT;
+        const int64_t j = static_cast<int64_t>(ci) * SC + scol;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int kk = shalf * PER + k;
+            const double sh = a.anchor[static_cast<int64_t>(J) * D + kk] - a.anchor[static_cast<int64_t>(I) * D + kk];
+            st_o[k] = off[kk * n_pad + j] + sh;
+        }
+        if (shalf == 0) st_w = wsrc[j];
+        if (!SAME && shalf == 1) st_l = lsrc[j];
+    };
+    auto stage_store = [&](int buf) {
+        double e = 0.0;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            s_o[buf][shalf * PER + k][scol] = st_o[k];
+            e = __builtin_fma(st_o[k], st_o[k], e);
+        }
+        s_e[buf][shalf][scol] = -e;
+        if (shalf == 0) s_w[buf][scol] = st_w;
+        if (!SAME && shalf == 1) s_l[SAME ? 0 : buf][scol] = st_l;
+    };
+    gdx4 acc[RG];
+    double cs[RG], S[RG];
+#pragma unroll
+    for (int rg = 0; rg < RG; ++rg) {
+        acc[rg] = gdx4{0.0, 0.0, 0.0, 0.0};
+        cs[rg] = S[rg] = 0.0;
+    }
+    const int C0 = by * a.tps * CPT, C1 = min(a.ntiles, (by + 1) * a.tps) * CPT;
+    if (C0 < C1) {
+        stage_load(C0);
+        stage_store(0);
+    }
+    __syncthreads();
+    for (int ci = C0; ci < C1; ++ci) {
+        const int buf = (ci - C0) & 1;
+        if (ci + 1 < C1) stage_load(ci + 1);
+        auto exponents = [&](int st, gdx4 (&G)[RG]) {
+            double av[DK];
+#pragma unroll
+            for (int kc = 0; kc < D / 4; ++kc) av[kc] = s_o[buf][4 * kc + g][st + asrc];
+            // slots [1, -e0, -e1, 0]
+            const double e = s_e[buf][g == 2 ? 1 : 0][st + asrc];
+            av[D / 4] = g == 0 ? 1.0 : (g < 3 ? e : 0.0);
+#pragma unroll
+            for (int rg = 0; rg < RG; ++rg) {
+                G[rg] = gdx4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int kc = 0; kc < DK; ++kc)
+                    G[rg] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[kc], bval[rg][kc], G[rg], 0, 0, 0);
+            }
+        };
+        // DIAG: the chunk holds the rows' own points, whose D_ii = 0 adds nothing;
+        // their (largest) coefficient is left out so that it does not have to cancel
+        // between t'_i sum c and sum c o'
+        auto accumulate = [&](auto diag_c, int st, const gdx4 (&G)[RG]) {
+            constexpr bool DIAG = decltype(diag_c)::value;
+            // this lane's sources 4 g + v: weights, and coordinate r16 for the second contraction
+            double wv[4], lv[4], ov[4];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const gdx2 w2 = *reinterpret_cast<const gdx2 *>(&s_w[buf][st + 4 * g + 2 * h]);
+                const gdx2 o2 = *reinterpret_cast<const gdx2 *>(&s_o[buf][r16][st + 4 * g + 2 * h]);
+                wv[2 * h] = w2[0];
+                wv[2 * h + 1] = w2[1];
+                ov[2 * h] = o2[0];
+                ov[2 * h + 1] = o2[1];
+                if constexpr (!SAME) {
+                    const gdx2 l2 = *reinterpret_cast<const gdx2 *>(&s_l[buf][st + 4 * g + 2 * h]);
+                    lv[2 * h] = l2[0];
+                    lv[2 * h + 1] = l2[1];
+                }
+            }
+#pragma unroll
+            for (int rg = 0; rg < RG; ++rg)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    // far pairs: the exponential is 0 from -1100 on; keeps x in int range
+                    const double x = __builtin_fmax(G[rg][v], -2000.0 * TN);
+                    const double e = exp2_tab<TN>(x, s_tab);
+                    double u;
+                    if constexpr (SAME)
+                        u = wv[v];
+                    else
+                        u = __builtin_fma(li[rg], wv[v], lv[v] * wi[rg]);
+                    double c = e * u;
+                    if constexpr (DIAG) {
+                        const int64_t j = static_cast<int64_t>(ci) * SC + st + 4 * g + v;
+                        c = j == row0 + rg * 16 + r16 ? 0.0 : c;
+                    }
+                    cs[rg] += c;
+                    S[rg] = __builtin_fma(c, x, S[rg]);
+                    acc[rg] = __builtin_amdgcn_mfma_f64_16x16x4f64(c, ov[v], acc[rg], 0, 0, 0);
+                }
+        };
+        // the matrix cores form a step's exponents while the VALU takes the one
+        // before; not unrolled further (the compiler would spill 150 registers)
+        auto chunk = [&](auto diag_c) {
+            gdx4 G0[RG], G1[RG];
+            exponents(0, G0);
+#pragma unroll 1
+            for (int st = 0; st < SC; st += 32) {
+                exponents(st + 16, G1);
+                accumulate(diag_c, st, G0);
+                if (st + 32 < SC) exponents(st + 32, G0);
+                accumulate(diag_c, st + 16, G1);
+            }
+        };
+        if (ci / CPT == I)
+            chunk(std::true_type{});
+        else
+            chunk(std::false_type{});
+        if (ci + 1 < C1) stage_store(buf ^ 1);
+        __syncthreads();
+    }
+    // A_i = t'_i C_i - sum c o'; accumulator lane l: target g + 4 v, coordinate r16
+    double *__restrict__ parts = static_cast<double *>(a.parts) + static_cast<int64_t>(by) * n_pad * NA;
+#pragma unroll
+    for (int rg = 0; rg < RG; ++rg) {
+        double c = cs[rg], s = S[rg];
+        c += __shfl_xor(c, 16, WAVE);
+        c += __shfl_xor(c, 32, WAVE);
+        s += __shfl_xor(s, 16, WAVE);
+        s += __shfl_xor(s, 32, WAVE);
+        const double f = SAME ? 2.0 * wi[rg] : 1.0;  // of target r16
+        if (g == 0) parts[(row0 + rg * 16 + r16) * NA + D] = f * s * (-1.0 / TN);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int it = g + 4 * v;
+            const double ct = __shfl(c, it, WAVE), ft = __shfl(f, it, WAVE);
+            const int64_t i = row0 + rg * 16 + it;
+            if (r16 < D) {
+                const double t = off[r16 * n_pad + i];
+                parts[i * NA + r16] = ft * __builtin_fma(t, ct, -acc[rg][v]);
+            }
+        }
+    }
 }
 
 // Sorted copies of lambda and w in the pass's precision (0 on the padding).
@@ -126,34 +328,34 @@ __device__ __forceinline__ T gwave_sum(T v) {
     return v;
 }
 
-// gx[p_i, k] = (lambda_p Aw_k + w_p Al_k) / (sigma^2 c); sums lambda_p S_i and
-// lambda_p w_p over rows (last block writes the two scalars).
+// gx[p_i, k] = A_ik / (sigma^2 c), the column ranges added in order; sums S_i and
+// lambda_p w_p over the rows (last block writes the two scalars).  One thread per
+// (row, k) entry of the [row][D + 1] partial sums, so the reads run along memory
+// (one row per thread walking its 2 D + 1 entries took 614 us at N = 50,000,
+// d = 16).
 template <typename T>
 __global__ __launch_bounds__(BLOCK) void k_grad_finish(int64_t n, int64_t n_pad, int d, int dpad, int splits,
-                                                       int same, const int32_t *__restrict__ perm,
+                                                       const int32_t *__restrict__ perm,
                                                        const T *__restrict__ parts, const double *__restrict__ lam,
                                                        const double *__restrict__ w, double inv_s2c,
                                                        double inv_s2c2, double gamma, double *gx, double *g_ls,
                                                        double *g_lg, double *partials, unsigned *counter) {
-    const int NA = same ? dpad + 1 : 2 * dpad + 1;
+    const int NA = dpad + 1;
     double accS = 0.0, accG = 0.0;
-    for (int64_t i = blockIdx.x * static_cast<int64_t>(BLOCK) + threadIdx.x; i < n;
-         i += static_cast<int64_t>(gridDim.x) * BLOCK) {
+    for (int64_t e = blockIdx.x * static_cast<int64_t>(BLOCK) + threadIdx.x; e < n * NA;
+         e += static_cast<int64_t>(gridDim.x) * BLOCK) {
+        const int64_t i = e / NA;
+        const int k = static_cast<int>(e - i * NA);
+        if (k >= d && k < dpad) continue;
+        double s = 0.0;
+        for (int u = 0; u < splits; ++u) s += static_cast<double>(parts[static_cast<int64_t>(u) * n_pad * NA + e]);
         const int64_t p = perm[i];
-        const double li = lam[p], wi = w[p];
-        for (int k = 0; k < d; ++k) {
-            double aw = 0.0, al = 0.0;
-            for (int s = 0; s < splits; ++s) {
-                const T *o = parts + (static_cast<int64_t>(s) * n_pad + i) * NA;
-                aw += static_cast<double>(o[k]);
-                al += static_cast<double>(o[same ? k : dpad + k]);
-            }
-            gx[p * d + k] = (li * aw + wi * al) * inv_s2c;
+        if (k < d) {
+            gx[p * d + k] = s * inv_s2c;
+        } else {
+            accS += s;
+            accG += lam[p] * w[p];
         }
-        double S = 0.0;
-        for (int s = 0; s < splits; ++s) S += static_cast<double>(parts[(static_cast<int64_t>(s) * n_pad + i) * NA + NA - 1]);
-        accS += li * S;
-        accG += li * wi;
     }
     // deterministic grid reduction of the two scalars (last block)
     __shared__ double sh[2][BLOCK / WAVE];
@@ -177,14 +379,17 @@ __global__ __launch_bounds__(BLOCK) void k_grad_finish(int64_t n, int64_t n_pad,
         is_last = (atomicAdd(counter, 1u) == gridDim.x - 1);
     }
     __syncthreads();
-    if (!is_last || threadIdx.x != 0) return;
+    if (!is_last || threadIdx.x >= WAVE) return;
     __threadfence();
     double s0 = 0.0, s1 = 0.0;
-    for (unsigned b = 0; b < gridDim.x; ++b) {
+    for (unsigned b = threadIdx.x; b < gridDim.x; b += WAVE) {
         s0 += __hip_atomic_load(&partials[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         s1 += __hip_atomic_load(&partials[gridDim.x + b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    *g_ls = -s0 * inv_s2c2;
+    s0 = gwave_sum(s0);
+    s1 = gwave_sum(s1);
+    if (threadIdx.x != 0) return;
+    *g_ls = -0.5 * s0 * inv_s2c2;
     *g_lg = -gamma * s1;
     *counter = 0u;
 }
@@ -195,6 +400,7 @@ __global__ void k_zero_u32(unsigned *p) {
 
 // ---------------------------------------------------------------- host
 
+// Column ranges: about 4096 blocks of 256 rows (2048 x 2 half tiles).
 static int grad_splits(const Prepared &P) {
     int s = (4096 + P.ntiles - 1) / P.ntiles;
     int mx = P.ntiles / 2 > 1 ? P.ntiles / 2 : 1;
@@ -205,12 +411,24 @@ static int grad_splits(const Prepared &P) {
 
 size_t grad_scratch_bytes(const Prepared &P) {
     const int mx = (P.ntiles / 2 > 1 ? (P.ntiles / 2 < 32 ? P.ntiles / 2 : 32) : 1);
-    return align_up(static_cast<size_t>(mx) * P.n_pad * (2 * P.dpad + 1) * 8, 256) +
+    return align_up(static_cast<size_t>(mx) * P.n_pad * (P.dpad + 1) * 8, 256) +
            2 * align_up(static_cast<size_t>(P.n_pad) * 8, 256) + align_up(2 * VEC_BLOCKS * 8, 256) + 256;
 }
 
 template <int D, typename T>
 static hipError_t launch_grad(const GArgs &a, bool same, hipStream_t s) {
+    // FP64 at the compiled dimensions 12 and 16: below, the matrix-core form's 16
+    // coordinate columns and padded slots cost more than the VALU's d subtractions
+    // and 2 d fused multiply-adds; above 16 its operands do not fit.  FP32 stays on
+    // the VALU, which keeps D_ij = x_i - x_j itself in FP32.
+    if constexpr (sizeof(T) == 8 && (D == 12 || D == 16)) {
+        const dim3 g(2 * a.nrowblocks * a.splits);
+        if (same)
+            hipLaunchKernelGGL((k_grad_mg<D, true>), g, dim3(BLOCK), 0, s, a);
+        else
+            hipLaunchKernelGGL((k_grad_mg<D, false>), g, dim3(BLOCK), 0, s, a);
+        return hipGetLastError();
+    }
     if (same)
         hipLaunchKernelGGL((k_grad<D, true, T>), dim3(a.nrowblocks * a.splits), dim3(BLOCK), 0, s, a);
     else
@@ -225,7 +443,7 @@ static hipError_t grad_pass(const Prepared &P, double sigma, double gamma, const
     const int mx = (P.ntiles / 2 > 1 ? (P.ntiles / 2 < 32 ? P.ntiles / 2 : 32) : 1);
     Carver cv(scratch);
     GArgs a;
-    T *parts = cv.take<T>(static_cast<size_t>(mx) * P.n_pad * (2 * P.dpad + 1));
+    T *parts = cv.take<T>(static_cast<size_t>(mx) * P.n_pad * (P.dpad + 1));
     T *ls = cv.take<T>(P.n_pad);
     T *wsv = cv.take<T>(P.n_pad);
     double *partials = cv.take<double>(2 * VEC_BLOCKS);
@@ -265,8 +483,8 @@ static hipError_t grad_pass(const Prepared &P, double sigma, double gamma, const
     KRR_HIP(e);
     const double c = P.scale;
     const double s2 = sigma * sigma;
-    hipLaunchKernelGGL(k_grad_finish<T>, dim3(vec_blocks(P.n_pad)), dim3(BLOCK), 0, s, P.n, P.n_pad, P.d, P.dpad,
-                       a.splits, same ? 1 : 0, P.perm, parts, lam, w, 1.0 / (s2 * c), 1.0 / (s2 * c * c), gamma,
+    hipLaunchKernelGGL(k_grad_finish<T>, dim3(vec_blocks(P.n_pad * (P.dpad + 1))), dim3(BLOCK), 0, s, P.n, P.n_pad, P.d, P.dpad,
+                       a.splits, P.perm, parts, lam, w, 1.0 / (s2 * c), 1.0 / (s2 * c * c), gamma,
                        gx, g_ls, g_lg, partials, counter);
     return hipGetLastError();
 }
