@@ -2061,19 +2061,12 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(D <= 4 ? 
 // the tile's bounds for the symmetric products (reach non-null), once per
 // product; one block per tile.
 template <int PREC>
-__global__ __launch_bounds__(TILE) void k_prescale(int64_t n, const void *q_, const void *w_, void *qw_,
-                                                   const int *__restrict__ reach, int *up, int *lo,
-                                                   const int *active) {
+__global__ __launch_bounds__(TILE) void k_prescale(Prescale ps, const void *q_, const int *active) {
     if (active != nullptr && *active == 0) return;
     using P = Prec<PREC>;
-    using T = typename P::T;
     __shared__ double sh[2 * TILE / SUB];
     const int64_t i = blockIdx.x * static_cast<int64_t>(TILE) + threadIdx.x;
-    const T q = P::q(static_cast<const typename P::Q *>(q_)[i]);
-    if (w_ != nullptr) static_cast<T *>(qw_)[i] = q * static_cast<const T *>(w_)[i];
-    if (reach != nullptr)
-        tile_bounds(fabs(static_cast<double>(q)), reach + blockIdx.x * (TILE / SUB), i < n, up + blockIdx.x,
-                    lo + blockIdx.x, sh);
+    prescale_entry<typename P::T>(ps, i, threadIdx.x, true, P::q(static_cast<const typename P::Q *>(q_)[i]), sh);
 }
 
 // y_i = sum_s parts[s][i] (+ shift q_i when square) for i < n, 0 on the padding.
@@ -3003,13 +2996,23 @@ const void *kmvp_weights(const Prepared &P, int prec) {
                               : static_cast<const void *>(P.w16);
 }
 
+static Prescale prescale_of(const Prepared &C, int prec, const KmvpScratch &sc, bool bounds) {
+    Prescale ps;
+    ps.w = kmvp_weights(C, prec);
+    ps.qw = sc.qw;
+    ps.reach = bounds ? C.sub_reach : nullptr;
+    ps.up = sc.up;
+    ps.lo = sc.lo;
+    ps.n = C.n;
+    return ps;
+}
+
 static hipError_t launch_prescale(const Prepared &C, int prec, const void *q, const KmvpScratch &sc, bool bounds,
                                   const int *active, hipStream_t s) {
-    const void *w = kmvp_weights(C, prec);
-    const int *reach = bounds ? C.sub_reach : nullptr;
-    if (w == nullptr && reach == nullptr) return hipSuccess;
+    const Prescale ps = prescale_of(C, prec, sc, bounds);
+    if (ps.w == nullptr && ps.reach == nullptr) return hipSuccess;
     auto go = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3(C.ntiles), dim3(TILE), 0, s, C.n, q, w, sc.qw, reach, sc.up, sc.lo, active);
+        hipLaunchKernelGGL(kern, dim3(C.ntiles), dim3(TILE), 0, s, ps, q, active);
         return hipGetLastError();
     };
     return prec == KRR_FP64 ? go(k_prescale<KRR_FP64>) : prec == KRR_FP32 ? go(k_prescale<KRR_FP32>) : go(k_prescale<KRR_BF16>);
@@ -3137,9 +3140,15 @@ int kmvp_live_slots(const Prepared &P, int prec) {
     return ng > 1 ? ng : 0;
 }
 
-hipError_t kmvp_prescale(const Prepared &P, int prec, const void *q, const KmvpScratch &sc, const int *active,
-                         hipStream_t s) {
-    return launch_prescale(P, prec, q, sc, use_sym_kernel(P, prec), active, s);
+Prescale kmvp_prescaler(const Prepared &P, int prec, const KmvpScratch &sc) {
+    return prescale_of(P, prec, sc, use_sym_kernel(P, prec));
+}
+
+hipError_t kmvp_scaled(const Prepared &P, int prec, double shift, const void *q, void *y, const KmvpScratch &sc,
+                       const int *active, hipStream_t s) {
+    int parts = 0;
+    KRR_HIP(kmvp_launch(P, P, prec, square_plan(P, prec), shift, q, y, sc, active, true, &parts, s));
+    return parts > 0 ? launch_finish(P, prec, parts, shift, true, q, y, nullptr, sc, active, s) : hipSuccess;
 }
 
 hipError_t kmvp_core(const Prepared &P, int prec, double shift, const void *q, void *y, const KmvpScratch &sc,

@@ -216,12 +216,10 @@ int kmvp_max_splits(const Prepared &P);
 int kmvp_parts_slots(const Prepared &P);
 KmvpPlan kmvp_plan(const Prepared &P, int prec);  // tuned, else a heuristic
 KmvpScratch carve_kmvp_scratch(Carver &cv, const Prepared &P);
-// The three parts of a square product: qw (and the tile bounds), the kernel
+// The parts of a square product on prescaled sources: the kernel
 // (partial sums in sc.parts, or y itself when kmvp_live_slots is 0), and the sum
 // of the partial sums + shift q, in sorted order or (perm) scattered to the
 // original one.
-hipError_t kmvp_prescale(const Prepared &P, int prec, const void *q, const KmvpScratch &sc, const int *active,
-                         hipStream_t s);
 hipError_t kmvp_core(const Prepared &P, int prec, double shift, const void *q, void *y, const KmvpScratch &sc,
                      const int *active, hipStream_t s);
 hipError_t kmvp_finish(const Prepared &P, int prec, double shift, const void *q, void *y, const int32_t *perm,
@@ -230,6 +228,12 @@ hipError_t kmvp_finish(const Prepared &P, int prec, double shift, const void *q,
 // none, it writes y itself).
 int kmvp_live_slots(const Prepared &P, int prec);
 const void *kmvp_weights(const Prepared &P, int prec);  // w_j in the precision, null for Matern
+// The prescale of products of this set and precision, for kernels that produce q.
+struct Prescale;
+Prescale kmvp_prescaler(const Prepared &P, int prec, const KmvpScratch &sc);
+// core and finish on prescaled sources
+hipError_t kmvp_scaled(const Prepared &P, int prec, double shift, const void *q, void *y, const KmvpScratch &sc,
+                       const int *active, hipStream_t s);
 // y = K_hat q + shift q on sorted vectors.  active: optional device flag; when it
 // reads 0 the kernels return at once.
 hipError_t kmvp_sorted(const Prepared &P, int prec, double shift, const void *q, void *y, const KmvpScratch &sc,
@@ -357,27 +361,28 @@ __device__ __forceinline__ double neglog2_kernel(double d2, bool matern) {
     return 1.4426950408889634 * s - static_cast<double>(__builtin_amdgcn_logf(static_cast<float>(1.0 + s)));
 }
 
-// up and lo of one tile from its 256 entries: thread tid of a 256-thread block
-// passes |q| of its point (0 on the padding; any NaN makes the tile NEVER left
-// out).  sh: 16 doubles.  Ends with the values stored by thread 0.
-__device__ __forceinline__ void tile_bounds(double aq, const int *__restrict__ reach, bool real, int *up, int *lo,
-                                            double *sh) {
+// up and lo of one tile from its 256 entries: thread t of 256 passes |q| of its
+// point (0 on the padding; any NaN makes the tile NEVER left out).  sh: 16
+// doubles.  Called by whole blocks (it holds a barrier); on: this tile exists.
+// (reach < 0: no points in the eighth.)
+__device__ __forceinline__ void tile_bounds(int t, bool on, double aq, const int *__restrict__ reach, bool real,
+                                            int *up, int *lo, double *sh) {
     double sum = aq, mn = real ? aq : INFINITY;
 #pragma unroll
     for (int o = SUB / 2; o > 0; o /= 2) {
         sum += __shfl_xor(sum, o, SUB);
         mn = fmin(mn, __shfl_xor(mn, o, SUB));
     }
-    if (threadIdx.x % SUB == 0) {
-        sh[threadIdx.x / SUB] = sum;
-        sh[8 + threadIdx.x / SUB] = mn;
+    if (t % SUB == 0) {
+        sh[t / SUB] = sum;
+        sh[8 + t / SUB] = mn;
     }
     __syncthreads();
     // one lane per eighth, combined by three exchanges
-    if (threadIdx.x < TILE / SUB) {
-        const int k = threadIdx.x, r = reach[k];
-        double l1 = sh[k];
-        double fl = r < 0 ? INFINITY : fmax(sh[8 + k], __builtin_amdgcn_ldexp(l1, -(r < 4000 ? r : 4000)));
+    if (on && t < TILE / SUB) {
+        const int r = reach[t];
+        double l1 = sh[t];
+        double fl = r < 0 ? INFINITY : fmax(sh[8 + t], __builtin_amdgcn_ldexp(l1, -(r < 4000 ? r : 4000)));
 #pragma unroll
         for (int o = TILE / SUB / 2; o > 0; o /= 2) {
             l1 += __shfl_xor(l1, o, TILE / SUB);
@@ -385,10 +390,34 @@ __device__ __forceinline__ void tile_bounds(double aq, const int *__restrict__ r
         }
         // frexp exponents: v < 2^e and v >= 2^(e - 1)
         const bool fin = l1 < INFINITY;  // false for NaN
-        if (k == 0) {
+        if (t == 0) {
             *up = !fin ? NEVER : l1 > 0.0 ? __builtin_amdgcn_frexp_exp(l1) : -NEVER / 2;
             *lo = fin && fl > 0.0 && fl < INFINITY ? __builtin_amdgcn_frexp_exp(fl) - 1 : -NEVER;
         }
+    }
+}
+
+// What a square product reads beside q itself (kmvp_prescale): a kernel that
+// produces q writes it on the way.  w: the weights (null: Matern), reach: null
+// when the product takes no bounds.
+struct Prescale {
+    const void *w = nullptr;
+    void *qw = nullptr;
+    const int *reach = nullptr;
+    int *up = nullptr, *lo = nullptr;
+    int64_t n = 0;
+};
+// Entry i = 256 tile + t of q in the product's arithmetic type T; called by whole
+// blocks for whole tiles, on (as tile_bounds): the tile exists.  Ends with a
+// barrier when bounds are taken.
+template <typename T>
+__device__ __forceinline__ void prescale_entry(const Prescale &ps, int64_t i, int t, bool on, T q, double *sh) {
+    if (on && ps.w != nullptr) static_cast<T *>(ps.qw)[i] = q * static_cast<const T *>(ps.w)[i];
+    if (ps.reach != nullptr) {
+        const int64_t J = i / TILE;
+        tile_bounds(t, on, on ? fabs(static_cast<double>(q)) : 0.0, ps.reach + J * (TILE / SUB), on && i < ps.n,
+                    ps.up + J, ps.lo + J, sh);
+        __syncthreads();  // sh is reused for the next tile
     }
 }
 

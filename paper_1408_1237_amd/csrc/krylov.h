@@ -12,7 +12,11 @@ struct Red {
     static constexpr int NCOUNTERS = 16;
     double *partials = nullptr;
     unsigned *counters = nullptr;
-    static size_t partial_count(int nv_max) { return static_cast<size_t>(VEC_BLOCKS) * nv_max; }
+    // nv_max values per vector block, or one per 128 rows (the CG step's finish)
+    static size_t partial_count(int nv_max, int64_t n_pad) {
+        const size_t a = static_cast<size_t>(VEC_BLOCKS) * nv_max, b = static_cast<size_t>(n_pad / 128 + 1);
+        return a > b ? a : b;
+    }
 };
 
 // Vectors of one CG solve (T = float: inner solve; double: plain solver).
@@ -22,6 +26,7 @@ struct CgVecs {
     T *x = nullptr, *r = nullptr, *p = nullptr, *Ap = nullptr;
     uint16_t *p16 = nullptr;  // only for the bf16 product
     CgScalars<T> *S = nullptr;
+    Prescale ps;              // of the solve's products: every kernel that writes p writes it
     double *hist = nullptr;   // optional (alpha_k, beta_k) history, hist_cap pairs
     int hist_cap = 0;
 };
@@ -40,7 +45,8 @@ hipError_t cg_restart(const CgVecs<T> &c, const T *b, const T *Kx, const Red &R,
 hipError_t fg_residual(int64_t n_pad, const double *b, const double *Kx, double *r, FgmresScalars *F, double *g,
                        const Red &R, hipStream_t s);
 hipError_t fg_first_basis(int64_t n_pad, const double *r, double *v, const FgmresScalars *F, hipStream_t s);
-hipError_t cast_f2d(int64_t n_pad, const float *z, double *Zj, hipStream_t s);
+// Zj = z, with the prescale of the FP64 product that follows (ps of FP64)
+hipError_t cast_f2d(int64_t n_pad, const float *z, double *Zj, const Prescale &ps, hipStream_t s);
 hipError_t copy_d(int64_t n_pad, const double *a, double *b, hipStream_t s);
 hipError_t fill_d(double *p, int64_t n, double v, hipStream_t s);
 hipError_t zero_bytes(void *p, int64_t n, hipStream_t s);  // fill kernel (no memset nodes)

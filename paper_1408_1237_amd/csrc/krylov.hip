@@ -65,18 +65,38 @@ __device__ bool grid_reduce(T (&v)[NV], T *partials, unsigned *counter) {
 
 // ------------------------------------------------------------------ CG
 
+// A CG iteration is four launches: the product, its finish with p.Ap and the
+// step length, the update of x and r with r.r, and the new direction with its
+// prescale (a separate prescale and dot product were two more of about 4.7 us
+// each, beside products of 10 us at N = 2000 and 65 us at N = 20,000).
+
+// Entry i of p (v): the BF16 copy and the prescale; whole tiles per block.
+template <typename T>
+__device__ __forceinline__ void store_direction(const Prescale &ps, int64_t i, int t, bool on, T v, T *p,
+                                                uint16_t *p16, double *sh) {
+    if (on) p[i] = v;
+    if constexpr (sizeof(T) == 4) {
+        if (p16 != nullptr) {
+            const uint16_t h = f32_to_bf16_rne(v);
+            if (on) p16[i] = h;
+            v = bf16_to_f32(h);
+        }
+    }
+    prescale_entry<T>(ps, i, t, on, v, sh);
+}
+
 // x = 0, r = p = rhs, rr = rr0 = r.r; stop threshold tol2 * rr0.
 template <typename T, typename TV>
 __global__ __launch_bounds__(BLOCK) void k_cg_init(int64_t n_pad, const TV *__restrict__ rhs, T *x, T *r, T *p,
-                                                   uint16_t *p16, CgScalars<T> *S, double tol2, int maxit,
+                                                   uint16_t *p16, Prescale ps, CgScalars<T> *S, double tol2, int maxit,
                                                    T *partials, unsigned *counter) {
+    __shared__ double sh[2 * TILE / SUB];
     T acc[1] = {T(0)};
     GRID_STRIDE(i, n_pad) {
         const T v = static_cast<T>(rhs[i]);
         x[i] = T(0);
         r[i] = v;
-        p[i] = v;
-        if (p16) p16[i] = f32_to_bf16_rne(static_cast<float>(v));
+        store_direction(ps, i, threadIdx.x, true, v, p, p16, sh);
         acc[0] += v * v;
     }
     if (grid_reduce(acc, partials, counter) && threadIdx.x == 0) {
@@ -149,16 +169,178 @@ __global__ __launch_bounds__(BLOCK) void k_cg_update(int64_t n_pad, T *x, T *r, 
     }
 }
 
-// p = r + beta p (and its bf16 copy for the bf16 product).
+// p = r + beta p, its bf16 copy for the bf16 product, and its prescale.
 template <typename T>
 __global__ __launch_bounds__(BLOCK) void k_cg_pupdate(int64_t n_pad, const T *__restrict__ r, T *p, uint16_t *p16,
-                                                      const CgScalars<T> *S) {
+                                                      Prescale ps, const CgScalars<T> *S) {
+    __shared__ double sh[2 * TILE / SUB];
     if (S->active == 0) return;
     const T b = S->beta;
-    GRID_STRIDE(i, n_pad) {
-        const T v = r[i] + b * p[i];
-        p[i] = v;
-        if (p16) p16[i] = f32_to_bf16_rne(static_cast<float>(v));
+    GRID_STRIDE(i, n_pad) store_direction(ps, i, threadIdx.x, true, r[i] + b * p[i], p, p16, sh);
+}
+
+// Ap = sum of the product's partial sums + shift q (as k_kmvp_finish: 16 bytes of
+// each slot per lane, the slots over the waves), p.Ap and the step length by the
+// last block.
+template <typename T>
+__global__ __launch_bounds__(BLOCK) void k_cg_finish(int64_t n, int64_t n_pad, int slots, const T *__restrict__ parts,
+                                                     const T *__restrict__ p, const uint16_t *__restrict__ p16,
+                                                     double shift, T *Ap, CgScalars<T> *S, double *partials,
+                                                     unsigned *counter) {
+    constexpr int V = 16 / sizeof(T), NW = BLOCK / WAVE;
+    typedef T VT __attribute__((ext_vector_type(V)));
+    __shared__ VT s_part[NW - 1][WAVE];
+    __shared__ int is_last;
+    if (S->active == 0) return;
+    const int lane = threadIdx.x % WAVE, wv = threadIdx.x / WAVE;
+    const int64_t i0 = blockIdx.x * static_cast<int64_t>(WAVE * V) + lane * V;
+    VT acc = {};
+    if (i0 < n_pad) {
+        const VT *src = reinterpret_cast<const VT *>(parts + i0);
+        const int64_t stride = n_pad / V;
+#pragma unroll 8
+        for (int k = wv; k < slots; k += NW) acc += src[static_cast<int64_t>(k) * stride];
+    }
+    if (wv > 0) s_part[wv - 1][lane] = acc;
+    __syncthreads();
+    if (wv == 0) {
+        double d = 0.0;
+        if (i0 < n_pad) {
+#pragma unroll
+            for (int w = 0; w < NW - 1; ++w) acc += s_part[w][lane];
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                const int64_t i = i0 + v;
+                const T pi = p[i];
+                T q = pi;
+                if constexpr (sizeof(T) == 4) q = p16 != nullptr ? bf16_to_f32(p16[i]) : pi;
+                const T y = i < n ? acc[v] + static_cast<T>(shift) * q : T(0);
+                Ap[i] = y;
+                d = __builtin_fma(static_cast<double>(pi), static_cast<double>(y), d);
+            }
+        }
+        d = wave_sum(d);
+        if (lane == 0) {
+            partials[blockIdx.x] = d;
+            __threadfence();
+            is_last = (atomicAdd(counter, 1u) == gridDim.x - 1);
+        }
+    }
+    __syncthreads();
+    if (!is_last) return;
+    __threadfence();
+    double s = 0.0;
+    for (unsigned b = threadIdx.x; b < gridDim.x; b += BLOCK)
+        s += __hip_atomic_load(&partials[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    s = block_sum(s);
+    if (threadIdx.x == 0) {
+        const T pAp = static_cast<T>(s);
+        if (!(pAp > T(0)) || !isfinite(static_cast<double>(pAp))) {
+            S->status = KRR_BREAKDOWN;
+            S->active = 0;
+        } else {
+            S->pAp = pAp;
+            S->alpha = S->rr / pAp;
+        }
+        *counter = 0u;
+    }
+}
+
+// The whole vector part of a CG iteration on a short vector in one block: Ap from
+// the partial sums, the step length, x, r, r.r, the stop tests and the new
+// direction with its prescale (the kernels above and below, launched three times,
+// cost about 15 us at 2000 points; this one about 6).
+constexpr int SMALL_THREADS = 1024;
+constexpr int64_t SMALL_CG_N = 4096;
+__device__ __forceinline__ double small_sum(double v, double *sh) {
+    v = wave_sum(v);
+    __syncthreads();  // sh may still be read
+    if (threadIdx.x % WAVE == 0) sh[threadIdx.x / WAVE] = v;
+    __syncthreads();
+    double s = 0.0;
+#pragma unroll
+    for (int k = 0; k < SMALL_THREADS / WAVE; ++k) s += sh[k];
+    return s;
+}
+
+template <typename T>
+__global__ __launch_bounds__(SMALL_THREADS) void k_cg_small(int n, int n_pad, int slots, const T *__restrict__ parts,
+                                                            T *x, T *r, T *p, uint16_t *p16, Prescale ps, double shift,
+                                                            CgScalars<T> *S, double *hist, int hist_cap) {
+    constexpr int PER = static_cast<int>(SMALL_CG_N) / SMALL_THREADS;
+    __shared__ double sh[4][2 * TILE / SUB];
+    if (S->active == 0) return;
+    const int tid = threadIdx.x;
+    T pv[PER], ap[PER];
+    double d = 0.0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) ap[k] = T(0);
+    for (int u = 0; u < slots; ++u) {
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int i = tid + k * SMALL_THREADS;
+            if (i < n_pad) ap[k] += parts[static_cast<int64_t>(u) * n_pad + i];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int i = tid + k * SMALL_THREADS;
+        pv[k] = i < n_pad ? p[i] : T(0);
+        T q = pv[k];
+        if constexpr (sizeof(T) == 4) q = p16 != nullptr && i < n_pad ? bf16_to_f32(p16[i]) : q;
+        ap[k] = i < n ? ap[k] + static_cast<T>(shift) * q : T(0);
+        d = __builtin_fma(static_cast<double>(pv[k]), static_cast<double>(ap[k]), d);
+    }
+    const T pAp = static_cast<T>(small_sum(d, sh[0]));
+    const T rr0 = S->rr;
+    const int it = S->iters;
+    if (!(pAp > T(0)) || !isfinite(static_cast<double>(pAp))) {
+        __syncthreads();  // every thread has read S
+        if (tid == 0) {
+            S->status = KRR_BREAKDOWN;
+            S->active = 0;
+        }
+        return;
+    }
+    const T a = rr0 / pAp;
+    T rv[PER];
+    d = 0.0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int i = tid + k * SMALL_THREADS;
+        rv[k] = T(0);
+        if (i < n_pad) {
+            x[i] += a * pv[k];
+            rv[k] = r[i] - a * ap[k];
+            r[i] = rv[k];
+        }
+        d = __builtin_fma(static_cast<double>(rv[k]), static_cast<double>(rv[k]), d);
+    }
+    const T rr = static_cast<T>(small_sum(d, sh[0]));  // its barriers: every thread has read S
+    const T beta = rr / rr0;
+    const bool bad = !isfinite(static_cast<double>(rr)), conv = rr <= S->thresh;
+    const bool live = !bad && !conv && it + 1 < S->maxit;
+    __syncthreads();
+    if (tid == 0) {
+        S->pAp = pAp;
+        S->alpha = a;
+        S->beta = beta;
+        S->rr = rr;
+        if (hist != nullptr && it < hist_cap) {
+            hist[2 * it] = static_cast<double>(a);
+            hist[2 * it + 1] = static_cast<double>(beta);
+        }
+        S->iters = it + 1;
+        if (bad) S->status = KRR_BREAKDOWN;
+        else if (conv) S->candidate = 1;
+        S->active = live ? 1 : 0;
+    }
+    if (!live) return;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int i = tid + k * SMALL_THREADS;
+        if (k * SMALL_THREADS >= n_pad) break;  // uniform
+        store_direction(ps, i, tid % TILE, i < n_pad, rv[k] + beta * pv[k], p, p16, sh[tid / TILE]);
     }
 }
 
@@ -166,12 +348,14 @@ __global__ __launch_bounds__(BLOCK) void k_cg_pupdate(int64_t n_pad, const T *__
 // rr = r.r; iterate again when rr is above the threshold.
 template <typename T>
 __global__ __launch_bounds__(BLOCK) void k_cg_restart(int64_t n_pad, const T *__restrict__ b, const T *__restrict__ Kx,
-                                                      T *r, T *p, CgScalars<T> *S, T *partials, unsigned *counter) {
+                                                      T *r, T *p, Prescale ps, CgScalars<T> *S, T *partials,
+                                                      unsigned *counter) {
+    __shared__ double sh[2 * TILE / SUB];
     T acc[1] = {T(0)};
     GRID_STRIDE(i, n_pad) {
         const T v = b[i] - Kx[i];
         r[i] = v;
-        p[i] = v;
+        store_direction(ps, i, threadIdx.x, true, v, p, static_cast<uint16_t *>(nullptr), sh);
         acc[0] += v * v;
     }
     if (grid_reduce(acc, partials, counter) && threadIdx.x == 0) {
@@ -215,8 +399,14 @@ __global__ __launch_bounds__(BLOCK) void k_fg_first_basis(int64_t n_pad, const d
     GRID_STRIDE(i, n_pad) v[i] = r[i] * inv;
 }
 
-__global__ __launch_bounds__(BLOCK) void k_cast_f2d(int64_t n_pad, const float *__restrict__ z, double *Zj) {
-    GRID_STRIDE(i, n_pad) Zj[i] = static_cast<double>(z[i]);
+__global__ __launch_bounds__(BLOCK) void k_cast_f2d(int64_t n_pad, const float *__restrict__ z, double *Zj,
+                                                    Prescale ps) {
+    __shared__ double sh[2 * TILE / SUB];
+    GRID_STRIDE(i, n_pad) {
+        const double v = static_cast<double>(z[i]);
+        Zj[i] = v;
+        prescale_entry<double>(ps, i, threadIdx.x, true, v, sh);
+    }
 }
 
 __global__ __launch_bounds__(BLOCK) void k_copy_d(int64_t n_pad, const double *__restrict__ a, double *b) {
@@ -449,7 +639,7 @@ hipError_t red_init(const Red &R, hipStream_t s) {
 
 template <typename T, typename TV>
 hipError_t cg_init(const CgVecs<T> &c, const TV *rhs, double tol, int maxit, const Red &R, hipStream_t s) {
-    LAUNCH((k_cg_init<T, TV>), vec_blocks(c.n_pad), c.n_pad, rhs, c.x, c.r, c.p, c.p16, c.S, tol * tol, maxit,
+    LAUNCH((k_cg_init<T, TV>), vec_blocks(c.n_pad), c.n_pad, rhs, c.x, c.r, c.p, c.p16, c.ps, c.S, tol * tol, maxit,
            reinterpret_cast<T *>(R.partials), R.counters + 0);
     return hipGetLastError();
 }
@@ -458,18 +648,34 @@ template <typename T>
 hipError_t cg_step(const Prepared &P, int prec, double shift, const CgVecs<T> &c, const KmvpScratch &sc,
                    const Red &R, hipStream_t s) {
     const void *qin = (prec == KRR_BF16) ? static_cast<const void *>(c.p16) : static_cast<const void *>(c.p);
-    KRR_HIP(kmvp_sorted(P, prec, shift, qin, c.Ap, sc, &c.S->active, s));
+    KRR_HIP(kmvp_core(P, prec, shift, qin, c.Ap, sc, &c.S->active, s));
     const int nb = vec_blocks(c.n_pad);
+    const int slots = kmvp_live_slots(P, prec);
+    const T *parts = static_cast<const T *>(sc.parts);
     T *part = reinterpret_cast<T *>(R.partials);
-    LAUNCH(k_cg_alpha<T>, nb, c.n_pad, c.p, c.Ap, c.S, part, R.counters + 1);
+    // one block up to 4096 entries (16 tiles: 16 slots at most); measured at 2048
+    // and 4096, beyond it one CU's loads of the partial sums take over
+    if (slots > 0 && c.n_pad <= SMALL_CG_N) {
+        hipLaunchKernelGGL(k_cg_small<T>, dim3(1), dim3(SMALL_THREADS), 0, s, static_cast<int>(P.n),
+                           static_cast<int>(c.n_pad), slots, parts, c.x, c.r, c.p, c.p16, c.ps, shift, c.S, c.hist,
+                           c.hist_cap);
+        return hipGetLastError();
+    }
+    if (slots > 0) {
+        constexpr int rows = WAVE * static_cast<int>(16 / sizeof(T));
+        LAUNCH(k_cg_finish<T>, static_cast<unsigned>((c.n_pad + rows - 1) / rows), P.n, c.n_pad, slots, parts, c.p, c.p16,
+               shift, c.Ap, c.S, R.partials, R.counters + 14);
+    } else {
+        LAUNCH(k_cg_alpha<T>, nb, c.n_pad, c.p, c.Ap, c.S, part, R.counters + 1);
+    }
     LAUNCH(k_cg_update<T>, nb, c.n_pad, c.x, c.r, c.p, c.Ap, c.S, part, R.counters + 2, c.hist, c.hist_cap);
-    LAUNCH(k_cg_pupdate<T>, nb, c.n_pad, c.r, c.p, c.p16, c.S);
+    LAUNCH(k_cg_pupdate<T>, nb, c.n_pad, c.r, c.p, c.p16, c.ps, c.S);
     return hipGetLastError();
 }
 
 template <typename T>
 hipError_t cg_restart(const CgVecs<T> &c, const T *b, const T *Kx, const Red &R, hipStream_t s) {
-    LAUNCH(k_cg_restart<T>, vec_blocks(c.n_pad), c.n_pad, b, Kx, c.r, c.p, c.S, reinterpret_cast<T *>(R.partials),
+    LAUNCH(k_cg_restart<T>, vec_blocks(c.n_pad), c.n_pad, b, Kx, c.r, c.p, c.ps, c.S, reinterpret_cast<T *>(R.partials),
            R.counters + 3);
     return hipGetLastError();
 }
@@ -498,8 +704,8 @@ hipError_t fg_first_basis(int64_t n_pad, const double *r, double *v, const Fgmre
     return hipGetLastError();
 }
 
-hipError_t cast_f2d(int64_t n_pad, const float *z, double *Zj, hipStream_t s) {
-    LAUNCH(k_cast_f2d, vec_blocks(n_pad), n_pad, z, Zj);
+hipError_t cast_f2d(int64_t n_pad, const float *z, double *Zj, const Prescale &ps, hipStream_t s) {
+    LAUNCH(k_cast_f2d, vec_blocks(n_pad), n_pad, z, Zj, ps);
     return hipGetLastError();
 }
 

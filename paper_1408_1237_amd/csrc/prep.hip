@@ -459,7 +459,7 @@ __global__ __launch_bounds__(TILE) void k_tiles(const double *__restrict__ x, in
         if constexpr (D <= 16) {
             __threadfence_block();
             __syncthreads();  // sub_reach was written above by this block
-            tile_bounds(aq, P.sub_reach + J * (TILE / SUB), real, pv.up + J, pv.lo + J, &s_v[0][0]);
+            tile_bounds(tid, true, aq, P.sub_reach + J * (TILE / SUB), real, pv.up + J, pv.lo + J, &s_v[0][0]);
         }
     }
 }

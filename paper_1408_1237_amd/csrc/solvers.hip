@@ -55,7 +55,7 @@ SolverWork carve_solver(Carver &cv, const Prepared &P, const SolverOpts &o, bool
     W.ksc = carve_kmvp_scratch(cv, P);
     W.status = cv.take<StatusBlock>(1);
     const int nv = (m + 1) > 2 ? (m + 1) : 2;
-    W.R.partials = cv.take<double>(Red::partial_count(nv));
+    W.R.partials = cv.take<double>(Red::partial_count(nv, np));
     W.R.counters = cv.take<unsigned>(Red::NCOUNTERS);
     return W;
 }
@@ -103,19 +103,22 @@ CgVecs<double> inner_vecs<double>(const SolverWork &W, int64_t np, int) {
 }
 
 // z ~ (K_hat + shift I)^{-1} v, z0 = 0: at most maxit iterations, early stop at
-// ||r|| <= tol ||v||.  The result is written (as FP64) to out.
+// ||r|| <= tol ||v||.  The result is written (as FP64) to out; scaled: prescaled
+// for the FP64 product that follows (kmvp_scaled), unless the solve is FP64.
 static hipError_t inner_solve(const Prepared &P, int prec, double shift, const double *v, double *out, int maxit,
-                              double tol, const SolverWork &W, hipStream_t s) {
+                              double tol, const SolverWork &W, hipStream_t s, bool scaled = false) {
     if (prec == KRR_FP64) {
         CgVecs<double> c = inner_vecs<double>(W, P.n_pad, prec);
+        c.ps = kmvp_prescaler(P, prec, W.ksc);
         KRR_HIP((cg_init<double, double>(c, v, tol, maxit, W.R, s)));
         for (int it = 0; it < maxit; ++it) KRR_HIP(cg_step<double>(P, prec, shift, c, W.ksc, W.R, s));
         return copy_d(P.n_pad, c.x, out, s);
     }
     CgVecs<float> c = inner_vecs<float>(W, P.n_pad, prec);
+    c.ps = kmvp_prescaler(P, prec, W.ksc);
     KRR_HIP((cg_init<float, double>(c, v, tol, maxit, W.R, s)));
     for (int it = 0; it < maxit; ++it) KRR_HIP(cg_step<float>(P, prec, shift, c, W.ksc, W.R, s));
-    return cast_f2d(P.n_pad, c.x, out, s);
+    return cast_f2d(P.n_pad, c.x, out, scaled ? kmvp_prescaler(P, KRR_FP64, W.ksc) : Prescale{}, s);
 }
 
 int cg_inner_sorted(const Prepared &P, int prec, double shift, const double *v_s, double *z_s, int maxit,
@@ -215,11 +218,15 @@ int fgmres_sorted(const Prepared &P, double gamma, bool x0_zero, const SolverOpt
             if (o.inner == KRR_INNER_NONE) {
                 KRR_HIP_STATUS(copy_d(np, Vj, Zj, s));
             } else {
-                KRR_HIP_STATUS(inner_solve(P, o.inner_prec, o.delta, Vj, Zj, o.inner_maxit, o.inner_tol, W, s));
+                KRR_HIP_STATUS(
+                    inner_solve(P, o.inner_prec, o.delta, Vj, Zj, o.inner_maxit, o.inner_tol, W, s, true));
             }
             tm.mark(1, s);
             // w = K z_j
-            KRR_HIP_STATUS(kmvp_sorted(P, KRR_FP64, gamma, Zj, W.w, W.ksc, nullptr, s));
+            if (o.inner == KRR_INNER_NONE || o.inner_prec == KRR_FP64)
+                KRR_HIP_STATUS(kmvp_sorted(P, KRR_FP64, gamma, Zj, W.w, W.ksc, nullptr, s));
+            else
+                KRR_HIP_STATUS(kmvp_scaled(P, KRR_FP64, gamma, Zj, W.w, W.ksc, nullptr, s));
             ++mvp64;
             tm.mark(2, s);
             KRR_HIP_STATUS(fg_arnoldi(o.gs, np, j, m, W.w, W.V, W.hcol, W.hscr, W.H, W.cs, W.sn, W.g, F, W.R, s));
@@ -380,6 +387,7 @@ int cg64_sorted(const Prepared &P, double gamma, const SolverOpts &o, const Solv
     c.p = W.p64;
     c.Ap = W.Ap64;
     c.S = &W.status->c64;
+    c.ps = kmvp_prescaler(P, KRR_FP64, W.ksc);
     c.hist = W.cghist;
     c.hist_cap = o.max_outer;
     StatusBlock st;
