@@ -56,11 +56,7 @@ struct BCols {  // per-column device state (arrays of C entries unless noted)
     int *summary;      // [4]: columns in their cycle, non-finite columns, active CG columns, CG columns to check
 };
 
-__device__ __forceinline__ double bwave_sum(double v) {
-#pragma unroll
-    for (int o = WAVE / 2; o > 0; o /= 2) v += __shfl_xor(v, o, WAVE);
-    return v;
-}
+__device__ __forceinline__ double bwave_sum(double v) { return wave_total64(v); }
 
 template <int NV>
 __device__ __forceinline__ void bblock_sum(double (&v)[NV]) {
@@ -157,6 +153,8 @@ __global__ __launch_bounds__(BLOCK) void kb_cg_update(BCols B, int C, int par, f
     BCHUNK;
     if (!B.in_cycle[c] || !B.act[par * C + c]) return;
     const int c0 = B.col_chunk0[c];
+    // requested beside the partial sums
+    const float pe = p[e], ae = Ap[e], ze = z[e], re = r[e], rr = B.rr[par * C + c];
     if (threadIdx.x < WAVE) {
         const double t = wave_total(B.cgp + 4 * static_cast<int64_t>(c0), 4 * B.col_nchunk[c]);
         if (threadIdx.x == 0) s_pAp = t;
@@ -166,9 +164,9 @@ __global__ __launch_bounds__(BLOCK) void kb_cg_update(BCols B, int C, int par, f
     const bool bad = !(pAp > 0.f) || !isfinite(pAp);
     if (threadIdx.x == 0 && static_cast<int>(blockIdx.x) == c0) B.brk[c] = bad ? 1 : 0;
     if (bad) return;
-    const float a = B.rr[par * C + c] / pAp;
-    z[e] += a * p[e];
-    const float ri = r[e] - a * Ap[e];
+    const float a = rr / pAp;
+    z[e] = ze + a * pe;
+    const float ri = re - a * ae;
     r[e] = ri;
     double acc[1] = {static_cast<double>(ri) * ri};
     bblock_sum(acc);
@@ -196,15 +194,26 @@ __global__ __launch_bounds__(BLOCK) void kb_cg_direction(BCols B, int C, int par
     const int64_t row0 = static_cast<int64_t>(blockIdx.x % nchunk) * ROWS;
     const int wv = threadIdx.x / WAVE, lane = threadIdx.x % WAVE;
     const int in = FIRST ? 0 : par * C, out = FIRST ? 0 : (par ^ 1) * C;
+    // the 16 columns' states side by side, 16 lanes per column
+    __shared__ float s_beta[16];
     bool any = false;
-    for (int k = wv; k < 16; k += BLOCK / WAVE) {
+    {
+        const int k = threadIdx.x / 16, sub = threadIdx.x % 16;
         const int c = m.col0 + rbk * 16 + k;
-        int live = 0;
-        if (B.in_cycle[c]) {
-            const bool writer = row0 == 0 && lane == 0;
+        const bool cyc = B.in_cycle[c] != 0;
+        const bool run = cyc && (FIRST || (B.act[in + c] != 0 && B.brk[c] == 0));
+        double t = 0.0;
+        if (run) {
+            const double *src = B.cgr + B.col_chunk0[c];
+            const int nc = B.col_nchunk[c];
+            for (int q = sub; q < nc; q += 16) t += src[q];
+        }
+        t = row_total(t);
+        if (sub == 0) {
+            const bool writer = cyc && row0 == 0;
+            int live = 0;
             float beta = 0.f;
-            if (FIRST || (B.act[in + c] && !B.brk[c])) {
-                const double t = wave_total(B.cgr + B.col_chunk0[c], B.col_nchunk[c]);
+            if (run) {
                 const float rr = static_cast<float>(t);
                 if constexpr (FIRST) {
                     live = rr > 0.f && maxit > 0 ? 1 : 0;
@@ -223,21 +232,33 @@ __global__ __launch_bounds__(BLOCK) void kb_cg_direction(BCols B, int C, int par
                 B.iters[out + c] = B.iters[in + c];
             }
             if (writer) B.act[out + c] = live;
-            if (live) {
-                const int64_t e = m.base + static_cast<int64_t>(rbk * 16 + k) * n_pad + row0 + lane;
-                float v = p[e];
-                if constexpr (!FIRST) {
-                    v = r[e] + beta * v;
-                    p[e] = v;
-                }
-                if (PREC == KRR_BF16) v = bf16_to_f32(f32_to_bf16_rne(v));
-                s_p[k][lane] = v;
-            }
+            s_live[k] = live;
+            s_beta[k] = beta;
+            any = live != 0;
         }
-        if (lane == 0) s_live[k] = live;
-        any = any || live;
     }
     if (!__syncthreads_or(any)) return;
+    float rv[4], pv[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int k = wv + u * (BLOCK / WAVE);
+        const int64_t e = m.base + static_cast<int64_t>(rbk * 16 + k) * n_pad + row0 + lane;
+        pv[u] = s_live[k] ? p[e] : 0.f;
+        rv[u] = !FIRST && s_live[k] ? r[e] : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int k = wv + u * (BLOCK / WAVE);
+        if (!s_live[k]) continue;
+        float v = pv[u];
+        if constexpr (!FIRST) {
+            v = rv[u] + s_beta[k] * v;
+            p[m.base + static_cast<int64_t>(rbk * 16 + k) * n_pad + row0 + lane] = v;
+        }
+        if (PREC == KRR_BF16) v = bf16_to_f32(f32_to_bf16_rne(v));
+        s_p[k][lane] = v;
+    }
+    __syncthreads();
     const bool wide = m.a.tile_r2[row0 / TILE] > WIDE_R2_FP32;
     const float *w = static_cast<const float *>(m.w);
     float *qwt = static_cast<float *>(const_cast<void *>(m.a.qwt)) + (rbk * n_pad + row0) * 16;

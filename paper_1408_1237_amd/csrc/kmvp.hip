@@ -878,27 +878,6 @@ __global__ __launch_bounds__(BLOCK) void k_kmvp_mg(KArgs a) {
 // (both).  A block clears its source-side slots first; every later change of
 // an entry comes from the thread that cleared it, so the sums are formed in a
 // fixed order, independent of the launch.
-// v + v of lane l ^ 32 (v_permlane32_swap on both halves of the double): the
-// same sum, in the same order, in both lanes
-__device__ __forceinline__ double join64(unsigned lo, unsigned hi) {
-    return __builtin_bit_cast(double, (static_cast<unsigned long long>(hi) << 32) | lo);
-}
-__device__ __forceinline__ double sum_halves32(double v) {
-    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
-    const unsigned lo = static_cast<unsigned>(b), hi = static_cast<unsigned>(b >> 32);
-    const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
-    const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
-    return join64(l[0], h[0]) + join64(l[1], h[1]);
-}
-// v + v of lane l ^ 16 (v_permlane16_swap: rows of 16 lanes), likewise
-__device__ __forceinline__ double sum_rows16(double v) {
-    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
-    const unsigned lo = static_cast<unsigned>(b), hi = static_cast<unsigned>(b >> 32);
-    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
-    const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-    return join64(l[0], h[0]) + join64(l[1], h[1]);
-}
-
 // Largest group (tiles) of the symmetric product's launch (kmvp_sym_group_tiles
 // stays below it up to 6.7e7 points); also the tile pairs a block tests at once.
 constexpr int MS_MAX_GROUP_TILES = 512;

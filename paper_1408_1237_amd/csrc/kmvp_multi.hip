@@ -590,6 +590,26 @@ __global__ __launch_bounds__(BLOCK) void k_multi_prescale(int64_t n_pad, int nrh
     qwt[idx] = v;
 }
 
+// The 64 x 16 block of partial sums at src, the splits (stride apart) added from
+// the first, in order, turned over into s_y.  The loads of several splits are in
+// flight together: one at a time, ten splits took 16 us.
+template <typename T, int PER>
+__device__ __forceinline__ void sum_splits(const T *__restrict__ src, int64_t stride, int splits,
+                                           T (*s_y)[PER * BLOCK / 16 + 1]) {
+    T acc[PER];
+#pragma unroll
+    for (int e = 0; e < PER; ++e) acc[e] = T(0);
+#pragma unroll 4
+    for (int k = 0; k < splits; ++k)
+#pragma unroll
+        for (int e = 0; e < PER; ++e) acc[e] += src[k * stride + threadIdx.x + e * BLOCK];
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+        const int l = threadIdx.x + e * BLOCK;  // row l / 16, right-hand side l % 16
+        s_y[l % 16][l / 16] = acc[e];
+    }
+}
+
 // Y[p_i + r ldy] = sum_s parts[s][r / 16][i][r % 16] + shift Q[p_i + r ldq], i < n.
 // A block takes 64 sorted rows x the 16 right-hand sides of block blockIdx.y, as
 // k_multi_finish_b: reads along the [row][16] layout (splits added from the
@@ -608,13 +628,7 @@ __global__ __launch_bounds__(BLOCK) void k_multi_finish(int64_t n, int64_t n_pad
     const int rbk = blockIdx.y;
     const int64_t row0 = static_cast<int64_t>(blockIdx.x) * ROWS;
     if (row0 >= n_pad) return;
-#pragma unroll
-    for (int e = 0; e < PER; ++e) {
-        const int l = threadIdx.x + e * BLOCK;  // row l / 16, right-hand side l % 16
-        T acc = T(0);
-        for (int k = 0; k < splits; ++k) acc += parts[((static_cast<int64_t>(k) * nrb + rbk) * n_pad + row0) * 16 + l];
-        s_y[l % 16][l / 16] = acc;
-    }
+    sum_splits<T, PER>(parts + (rbk * n_pad + row0) * 16, nrb * n_pad * 16, splits, s_y);
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
@@ -686,21 +700,15 @@ __global__ __launch_bounds__(BLOCK) void k_multi_finish_b(const MSysB *__restric
     if (static_cast<int>(blockIdx.x) >= nchunk * nrb) return;
     const int rbk = blockIdx.x / nchunk;
     const int64_t row0 = static_cast<int64_t>(blockIdx.x % nchunk) * ROWS;
-    bool any = false;
-    for (int c = 0; c < 16; ++c) {
-        const int r = rbk * 16 + c;
-        any = any || (r < nrhs && gate_live(gate, m.col0 + r));
+    __shared__ int s_live[16];
+    int any = 0;
+    if (threadIdx.x < 16) {
+        const int r = rbk * 16 + threadIdx.x;
+        any = r < nrhs && gate_live(gate, m.col0 + r) ? 1 : 0;
+        s_live[threadIdx.x] = any;
     }
-    if (!any) return;
-    const T *parts = static_cast<const T *>(m.a.parts);
-#pragma unroll
-    for (int e = 0; e < PER; ++e) {
-        const int l = threadIdx.x + e * BLOCK;  // row l / 16, right-hand side l % 16
-        T acc = T(0);
-        for (int k = 0; k < m.a.splits; ++k)
-            acc += parts[((static_cast<int64_t>(k) * nrb + rbk) * n_pad + row0) * 16 + l];
-        s_y[l % 16][l / 16] = acc;
-    }
+    if (!__syncthreads_or(any)) return;
+    sum_splits<T, PER>(static_cast<const T *>(m.a.parts) + (rbk * n_pad + row0) * 16, nrb * n_pad * 16, m.a.splits, s_y);
     __syncthreads();
     T *Y = static_cast<T *>(Yall_) + m.base;
     const T *Q = static_cast<const T *>(Qall_) + m.base;
@@ -710,7 +718,7 @@ __global__ __launch_bounds__(BLOCK) void k_multi_finish_b(const MSysB *__restric
         const int l = threadIdx.x + e * BLOCK;
         const int c = l / ROWS, il = l % ROWS;
         const int r = rbk * 16 + c;
-        if (r >= nrhs || !gate_live(gate, m.col0 + r)) continue;
+        if (!s_live[c]) continue;
         const int64_t i = row0 + il, idx = static_cast<int64_t>(r) * n_pad + i;
         const T q = Q[idx];  // 0 on the padding
         T qv = q;
@@ -718,9 +726,7 @@ __global__ __launch_bounds__(BLOCK) void k_multi_finish_b(const MSysB *__restric
         const T y = i < m.a.n ? s_y[c][il] + shift * qv : T(0);
         Y[idx] = y;
         if (dots != nullptr) {  // il = lane: one wave holds 64 rows of one column
-            double d = static_cast<double>(q) * static_cast<double>(y);
-#pragma unroll
-            for (int o = WAVE / 2; o > 0; o /= 2) d += __shfl_xor(d, o, WAVE);
+            const double d = wave_total64(static_cast<double>(q) * static_cast<double>(y));
             if (il == 0) dots[(m.base + idx) / ROWS] = d;
         }
     }

@@ -11,6 +11,7 @@
 
 namespace krr {
 
+__device__ __forceinline__ double wave_sum(double v) { return wave_total64(v); }
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {
 #pragma unroll
@@ -257,10 +258,8 @@ __device__ __forceinline__ double small_sum(double v, double *sh) {
     __syncthreads();  // sh may still be read
     if (threadIdx.x % WAVE == 0) sh[threadIdx.x / WAVE] = v;
     __syncthreads();
-    double s = 0.0;
-#pragma unroll
-    for (int k = 0; k < SMALL_THREADS / WAVE; ++k) s += sh[k];
-    return s;
+    static_assert(SMALL_THREADS / WAVE == 16, "one partial per lane of a row");
+    return row_total(sh[threadIdx.x % 16]);
 }
 
 template <typename T>
@@ -271,21 +270,30 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_cg_small(int n, int n_pad, in
     __shared__ double sh[4][2 * TILE / SUB];
     if (S->active == 0) return;
     const int tid = threadIdx.x;
-    T pv[PER], ap[PER];
+    T pv[PER], ap[PER], xv[PER], rv[PER];
     double d = 0.0;
+    // everything the iteration reads is requested up front (entries past the end
+    // read entry 0 and are left out below)
 #pragma unroll
-    for (int k = 0; k < PER; ++k) ap[k] = T(0);
+    for (int k = 0; k < PER; ++k) {
+        const int i = tid + k * SMALL_THREADS, ic = i < n_pad ? i : 0;
+        pv[k] = p[ic];
+        xv[k] = x[ic];
+        rv[k] = r[ic];
+        ap[k] = T(0);
+    }
+#pragma unroll 8
     for (int u = 0; u < slots; ++u) {
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
             const int i = tid + k * SMALL_THREADS;
-            if (i < n_pad) ap[k] += parts[static_cast<int64_t>(u) * n_pad + i];
+            ap[k] += parts[u * n_pad + (i < n_pad ? i : 0)];
         }
     }
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const int i = tid + k * SMALL_THREADS;
-        pv[k] = i < n_pad ? p[i] : T(0);
+        pv[k] = i < n_pad ? pv[k] : T(0);
         T q = pv[k];
         if constexpr (sizeof(T) == 4) q = p16 != nullptr && i < n_pad ? bf16_to_f32(p16[i]) : q;
         ap[k] = i < n ? ap[k] + static_cast<T>(shift) * q : T(0);
@@ -303,15 +311,13 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_cg_small(int n, int n_pad, in
         return;
     }
     const T a = rr0 / pAp;
-    T rv[PER];
     d = 0.0;
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const int i = tid + k * SMALL_THREADS;
-        rv[k] = T(0);
+        rv[k] = i < n_pad ? rv[k] - a * ap[k] : T(0);
         if (i < n_pad) {
-            x[i] += a * pv[k];
-            rv[k] = r[i] - a * ap[k];
+            x[i] = xv[k] + a * pv[k];
             r[i] = rv[k];
         }
         d = __builtin_fma(static_cast<double>(rv[k]), static_cast<double>(rv[k]), d);

@@ -27,8 +27,7 @@ struct OrthShared {
 
 // Block sum of v, the same in every thread; buf alternates between calls.
 __device__ __forceinline__ double orth_sum(double v, OrthShared &sh, int &buf) {
-#pragma unroll
-    for (int o = WAVE / 2; o > 0; o /= 2) v += __shfl_xor(v, o, WAVE);
+    v = wave_total64(v);
     if (threadIdx.x % WAVE == 0) sh.part[buf][threadIdx.x / WAVE] = v;
     __syncthreads();
     double s = 0.0;

@@ -359,23 +359,30 @@ __global__ __launch_bounds__(TILE) void k_tiles(const double *__restrict__ x, in
     const bool median = block_reduce(sqc, MaxOp(), lds) > WIDE_R2_FP32;
     if (median) {
         // rank of this point's coordinate among the tile's real points (ties by
-        // position); the point of rank (nreal - 1) / 2 is the median
+        // position); the point of rank (nreal - 1) / 2 is the median.  Against the
+        // points of the waves before (after) this one a tie counts (does not), one
+        // comparison each; only within the wave is the position compared too.
+        const int w0 = tid / WAVE * WAVE;
+        auto below = [](double u, double v, bool tie) { return u < v || (tie && u == v) ? 1 : 0; };
 #pragma unroll 1
-        for (int t = 0; t < d; ++t) {
-            const double v = real ? x[static_cast<int64_t>(idx) * d + t] * scale : INFINITY;  // the padding ranks last
-            s_v[0][tid] = v;
-            if (tid == 0) s_median[t] = 0.5 * (s_lo[t] + s_hi[t]);  // kept if a non-finite value breaks the ranks
+        for (int c0 = 0; c0 < d; c0 += CH) {
+            for (int k = 0; k < CH && c0 + k < d; ++k)  // the padding ranks last
+                s_v[k][tid] = real ? x[static_cast<int64_t>(idx) * d + c0 + k] * scale : INFINITY;
+            // kept if a non-finite value breaks the ranks
+            if (tid < CH && c0 + tid < d) s_median[c0 + tid] = 0.5 * (s_lo[c0 + tid] + s_hi[c0 + tid]);
             __syncthreads();
-            if (real) {
+            for (int k = 0; k < CH && c0 + k < d; ++k) {
+                const double v = s_v[k][tid];
                 int rank = 0;
 #pragma unroll 16
-                for (int k = 0; k < TILE; ++k) {
-                    const double u = s_v[0][k];
-                    rank += (u < v || (u == v && k < tid)) ? 1 : 0;
-                }
-                if (rank == (nreal - 1) / 2) s_median[t] = v;
+                for (int i = 0; i < w0; ++i) rank += s_v[k][i] <= v ? 1 : 0;
+#pragma unroll 16
+                for (int i = 0; i < WAVE; ++i) rank += below(s_v[k][w0 + i], v, i < tid - w0);
+#pragma unroll 16
+                for (int i = w0 + WAVE; i < TILE; ++i) rank += s_v[k][i] < v ? 1 : 0;
+                if (real && rank == (nreal - 1) / 2) s_median[c0 + k] = v;
             }
-            __syncthreads();  // s_v is rewritten for the next coordinate
+            __syncthreads();  // s_v is rewritten for the next coordinates
         }
     }
     // offsets from the chosen anchor (padding coordinates and points are zero)
