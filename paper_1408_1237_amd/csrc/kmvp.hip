@@ -1729,12 +1729,18 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(D <= 4 ? 
     auto stage_load = [&](int J) {
         const int64_t j = static_cast<int64_t>(J) * TILE + tid;
         if (a.tile_r2[J] > P::wide) {
+            const Off *op = off + j;
 #pragma unroll
             for (int c = 0; c < 2 * KC; ++c) {
                 uintx4_t u;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const float o = (4 * c + e < D) ? P::off(off[(4 * c + e) * n_pad + j]) : 0.f;
+                    float o = 0.f;
+                    if (4 * c + e < D) {
+                        o = P::off(*op);
+                        op += n_pad;
+                        asm volatile("" : "+v"(op));  // no addresses of this rare path kept over the loops
+                    }
                     u[e] = __builtin_bit_cast(unsigned, o);
                 }
                 st_a[c] = __builtin_bit_cast(half8_t, u);
@@ -1928,10 +1934,13 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(D <= 4 ? 
                             __asm__ __volatile__("" ::: "memory");
                             const int64_t i = row0 + 8 * (v2 / 4) + 4 * h + v2 % 4;
                             float tg[D];
+                            const Off *rp = row_off + i;
 #pragma unroll
-                            for (int k = 0; k < D; ++k)
-                                tg[k] = static_cast<float>((aI[k] - aJ[k]) +
-                                                           static_cast<double>(P::off(row_off[k * a.n_pad_rows + i])));
+                            for (int k = 0; k < D; ++k) {
+                                tg[k] = static_cast<float>((aI[k] - aJ[k]) + static_cast<double>(P::off(*rp)));
+                                rp += a.n_pad_rows;
+                                asm volatile("" : "+v"(rp));
+                            }
                             const float qi = i < a.n_rows ? P::q(q[i]) : 0.f;
                             float sacc = 0.f;
 #pragma unroll
