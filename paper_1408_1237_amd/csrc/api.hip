@@ -288,7 +288,7 @@ static int kmvp_single(const krr_points *pts, int kernel, double sigma, double s
     KRR_HIP_STATUS(prepare_points(L.P, pts->x, sigma, L.temp, L.temp_bytes, s, kernel, prep_need(prec), &v));
     if (tune) KRR_HIP_STATUS(kmvp_tune(L.P, prec, v.qs, L.y, L.W.ksc, s));
     KRR_HIP_STATUS(kmvp_core(L.P, prec, shift, v.qs, L.y, L.W.ksc, nullptr, s));
-    if (kmvp_live_slots(L.P, prec) > 0)
+    if (kmvp_live_slots(L.P, prec).n > 0)
         KRR_HIP_STATUS(kmvp_finish(L.P, prec, shift, v.qs, y, L.P.perm, L.W.ksc, nullptr, s));
     else if (prec == KRR_FP64)
         KRR_HIP_STATUS((scatter_sorted<double, double>(L.P, static_cast<double *>(L.y), static_cast<double *>(y), s)));

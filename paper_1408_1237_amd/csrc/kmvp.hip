@@ -105,6 +105,7 @@ struct KArgs {
     const void *q;
     const void *qw;  // q_j * w_j in the arithmetic type (folded tiles)
     const void *w;   // w_j in the arithmetic type (symmetric product: the source terms)
+    int units;       // symmetric products: blocks per pair of groups (kmvp_sym_units)
     int zmem;        // symmetric product: 1 adds the source terms into the slots in memory even
                      // where the column group fits in LDS (the two paths are bitwise equal)
     void *out;
@@ -878,6 +879,16 @@ __global__ __launch_bounds__(BLOCK) void k_kmvp_mg(KArgs a) {
 // (both).  A block clears its source-side slots first; every later change of
 // an entry comes from the thread that cleared it, so the sums are formed in a
 // fixed order, independent of the launch.
+//
+// RG groups of 16 targets per wave: 4 (a block takes a row tile at once) below
+// d = 8; 2 from there (two units of 128 rows, against the same column tiles):
+// four groups' operands and accumulators do not fit the registers (d = 12: 150
+// spilled; N = 60,000: d = 8 2068 -> 1959 us, d = 12 2684 -> 2328; with the
+// addresses of the inner loops kept opaque, below, d = 16 N = 25,000 841 -> 523).
+// Small sets: a.units blocks per pair of groups (kmvp_sym_units), one unit of the
+// row tile each, with one slot per unit for the source terms: rows of tile t have
+// target terms in the slots t units .. and source terms of tile R < t in the
+// slots R units + unit.
 // Largest group (tiles) of the symmetric product's launch (kmvp_sym_group_tiles
 // stays below it up to 6.7e7 points); also the tile pairs a block tests at once.
 constexpr int MS_MAX_GROUP_TILES = 512;
@@ -898,7 +909,7 @@ constexpr int ms_zacc_tiles() {
     return t > 16 ? 16 : (t < 1 ? 1 : t);
 }
 
-template <int D, bool MAT>
+template <int D, bool MAT, int RG>
 __global__ __launch_bounds__(BLOCK, 2) void k_kmvp_ms(KArgs a) {
     if (a.active != nullptr && *a.active == 0) return;
     using M = MG<KRR_FP64>;
@@ -907,11 +918,8 @@ __global__ __launch_bounds__(BLOCK, 2) void k_kmvp_ms(KArgs a) {
     // chunks of 4 over the d + 1 coordinates [o, 1] (Matern: d + 2, [o, 1, |o'|^2])
     constexpr int DK = (D + (MAT ? 5 : 4)) / 4;
     constexpr double L2E = 1.4426950408889634074, LN2 = 0.69314718055994530942;
-    // groups of 16 targets per wave: 4 (a block takes a row tile at once), or
-    // 2 at d = 16, where four groups' operands and accumulators do not fit (a
-    // block then takes a row tile in two units of 128 rows); there the source
-    // tile is also staged in one buffer (two would leave one block per CU)
-    constexpr int RG = D >= 16 ? 2 : 4;
+    // at d = 16 the source tile is staged in one buffer (two would leave one block
+    // per CU)
     constexpr int UNITS = 4 / RG;
     constexpr int NBUF = D >= 16 ? 1 : 2;
     constexpr int NW = BLOCK / WAVE;
@@ -951,7 +959,7 @@ __global__ __launch_bounds__(BLOCK, 2) void k_kmvp_ms(KArgs a) {
     // sits near the diagonal, a few blocks of every row, and contiguous ranges
     // per XCD (rows of very different lengths) would load them unevenly.
     const int nb_off = ng * (ng - 1) / 2;
-    const int b = blockIdx.x;
+    const int S = RG == 4 ? 1 : a.units, b = blockIdx.x / S, part = blockIdx.x % S;
     int R, C;
     if (b < nb_off) {
         const double m = 2.0 * ng - 1.0;
@@ -971,12 +979,12 @@ __global__ __launch_bounds__(BLOCK, 2) void k_kmvp_ms(KArgs a) {
     const int asrc = (r16 % 4) * 4 + r16 / 4;  // target of A row r16 within a group of 16
     const int I0 = R * gs, I1 = min(a.ntiles, I0 + gs);
     const int C0 = C * gs, C1 = min(a.ntiles, C0 + gs);
-    T *__restrict__ zslot = out + static_cast<int64_t>(R) * n_pad;  // source terms of the tiles of group C
-    T *__restrict__ yslot = out + static_cast<int64_t>(C) * n_pad;  // target terms of the tiles of group R
+    T *__restrict__ zslot = out + static_cast<int64_t>(R * S + part) * n_pad;  // source terms of the tiles of group C
+    T *__restrict__ yslot = out + static_cast<int64_t>(C + R * (S - 1)) * n_pad;  // target terms of the tiles of group R
     // the source terms accumulate in LDS and are stored once (a group that
     // does not fit adds them into its cleared slots in memory instead)
     const bool zlds = a.zmem == 0 && C1 - C0 <= ZMAX;
-    for (int J = C0; J < C1; ++J) {
+    for (int J = C0; J < C1 && !(S > 1 && diag); ++J) {
         if (zlds)
             s_zacc[J - C0][tid] = T(0);
         else
@@ -986,8 +994,13 @@ __global__ __launch_bounds__(BLOCK, 2) void k_kmvp_ms(KArgs a) {
     T st_o[D], st_q, st_e = T(0);
     auto stage_load = [&](int J) {
         const int64_t j = static_cast<int64_t>(J) * TILE + tid;
+        const T *op = off + j;
 #pragma unroll
-        for (int k = 0; k < D; ++k) st_o[k] = off[k * n_pad + j];
+        for (int k = 0; k < D; ++k) {
+            st_o[k] = *op;
+            op += n_pad;
+            asm volatile("" : "+v"(op));  // no D addresses kept over the loops (here and below)
+        }
         if constexpr (MAT) {
             st_q = q[j];  // no folded weights
             st_e = static_cast<T>(L2E * L2E) * a.sq[j];
@@ -1018,9 +1031,11 @@ __global__ __launch_bounds__(BLOCK, 2) void k_kmvp_ms(KArgs a) {
     }
     int skipped = 0;
     for (int I = I0; I < I1; ++I) {
-        double aI[D];
+        double aK[D < 16 ? D : 1];
+        if constexpr (D < 16) {
 #pragma unroll
-        for (int k = 0; k < D; ++k) aI[k] = a.row_anchor[static_cast<int64_t>(I) * D + k];
+            for (int k = 0; k < D; ++k) aK[k] = a.row_anchor[static_cast<int64_t>(I) * D + k];
+        }
         // which column tiles are live: the block's pairs at once, or per row tile
         const int Js = diag ? I : C0;
         const unsigned char *live = s_live;
@@ -1035,15 +1050,15 @@ __global__ __launch_bounds__(BLOCK, 2) void k_kmvp_ms(KArgs a) {
             return J;
         };
         const int Jfirst = next_live(Js);
-        skipped += Jfirst - Js;
+        if (part == 0) skipped += Jfirst - Js;
         if (Jfirst >= C1) {
             // no live column tile: zero target terms (the source-side slots stay as they are)
             const int64_t i = static_cast<int64_t>(I) * TILE + tid;
-            if (!diag) yslot[i] = T(0);
+            if (!diag && (S == 1 || tid / (TILE / UNITS) == part)) yslot[i] = T(0);
             if (!at_once) __syncthreads();  // s_live is rewritten for the next row tile
             continue;
         }
-        for (int unit = 0; unit < UNITS; ++unit) {
+        for (int unit = part; unit < (S > 1 ? part + 1 : UNITS); ++unit) {
         const int64_t row0 = static_cast<int64_t>(I) * TILE + unit * (TILE / UNITS) + wv * (16 * RG);
         int J = Jfirst;
         T oi[KEEP ? RG : 1][KEEP ? D : 1];
@@ -1077,6 +1092,12 @@ __global__ __launch_bounds__(BLOCK, 2) void k_kmvp_ms(KArgs a) {
             const double r2 = a.tile_r2[J];
             const double nj = a.tile_nj[J];
             const double *__restrict__ aJ = a.anchor + static_cast<int64_t>(J) * D;
+            // at d = 16 the row tile's anchor is read again per column tile, with aJ's
+            // loads (kept in registers, its 32 were spilled)
+            int Ia = I;
+            if constexpr (D >= 16) asm volatile("" : "+s"(Ia));
+            const double *__restrict__ aR = a.row_anchor + static_cast<int64_t>(Ia) * D;
+            auto aI = [&](int k) { return D < 16 ? aK[D < 16 ? k : 0] : aR[k]; };
             auto tile = [&](auto sym_c) {
                 constexpr bool SYM = decltype(sym_c)::value;
                 if (r2 <= WIDE_R2_FP64) {
@@ -1086,14 +1107,18 @@ __global__ __launch_bounds__(BLOCK, 2) void k_kmvp_ms(KArgs a) {
                     for (int rg = 0; rg < RG; ++rg) {
                         T t[D];
                         double tt = 0.0;
+                        const T *rp = row_off + row0 + rg * 16 + asrc;
 #pragma unroll
                         for (int k = 0; k < D; ++k) {
                             T o;
-                            if constexpr (KEEP)
+                            if constexpr (KEEP) {
                                 o = oi[rg][k];
-                            else
-                                o = row_off[k * a.n_pad_rows + row0 + rg * 16 + asrc];
-                            t[k] = (aI[k] - aJ[k]) + o;
+                            } else {
+                                o = *rp;
+                                rp += a.n_pad_rows;
+                                asm volatile("" : "+v"(rp));
+                            }
+                            t[k] = (aI(k) - aJ[k]) + o;
                             tt = __builtin_fma(t[k], t[k], tt);
                         }
                         if constexpr (MAT) {
@@ -1200,8 +1225,13 @@ __global__ __launch_bounds__(BLOCK, 2) void k_kmvp_ms(KArgs a) {
                             const int rg = rv / 4, v = rv % 4;
                             const int64_t i = row0 + rg * 16 + 4 * g + v;
                             T t[D];
+                            const T *rp = row_off + i;
 #pragma unroll
-                            for (int k = 0; k < D; ++k) t[k] = (aI[k] - aJ[k]) + row_off[k * a.n_pad_rows + i];
+                            for (int k = 0; k < D; ++k) {
+                                t[k] = (aI(k) - aJ[k]) + *rp;
+                                rp += a.n_pad_rows;
+                                asm volatile("" : "+v"(rp));
+                            }
                             const T qi = i < a.n_rows ? q[i] : T(0);
                             T sacc = T(0);
 #pragma unroll
@@ -1292,6 +1322,8 @@ __global__ __launch_bounds__(BLOCK, 2) void k_kmvp_ms(KArgs a) {
             const int64_t i = static_cast<int64_t>(I) * TILE + il;
             if (!diag)
                 yslot[i] = s_z[tid];
+            else if (S > 1)
+                yslot[i] = s_z[tid];  // one tile: no source terms
             else if (zlds)
                 yslot[i] = s_z[tid] + s_zacc[I - C0][il];  // the source terms of tile I are complete
             else
@@ -1662,7 +1694,9 @@ __device__ __forceinline__ float dpp_f32(float v) {
 // tile in two units of 128 rows, each against the same column tiles.  At
 // d = 16 the source tiles are staged in one buffer (after a barrier that ends
 // every wave's reads), which keeps two blocks per CU.
-template <int D, int PREC, bool MAT>
+// SHARED: small sets, one block per row unit (kmvp_sym_units), with the slots of
+// k_kmvp_ms (a launch argument in its place cost 1-3 % at d = 8, N = 50,000).
+template <int D, int PREC, bool MAT, bool SHARED>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(D <= 4 ? 3 : 2))) void k_kmvp_mhs(KArgs a) {
     if (a.active != nullptr && *a.active == 0) return;
     using P = Prec<PREC>;
@@ -1693,7 +1727,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(D <= 4 ? 
 
     // block -> group pair (R, C), as k_kmvp_ms
     const int nb_off = ng * (ng - 1) / 2;
-    const int b = blockIdx.x;
+    constexpr int S = SHARED ? TILE / UNIT : 1;
+    const int b = blockIdx.x / S, part = SHARED ? blockIdx.x % S : 0;
     int R, C;
     if (b < nb_off) {
         const double m = 2.0 * ng - 1.0;
@@ -1712,10 +1747,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(D <= 4 ? 
     const int r32 = lane % 32, h = lane / 32;
     const int I0 = R * gs, I1 = min(a.ntiles, I0 + gs);
     const int C0 = C * gs, C1 = min(a.ntiles, C0 + gs);
-    float *__restrict__ zslot = out + static_cast<int64_t>(R) * n_pad;
-    float *__restrict__ yslot = out + static_cast<int64_t>(C) * n_pad;
+    float *__restrict__ zslot = out + static_cast<int64_t>(R * S + part) * n_pad;
+    float *__restrict__ yslot = out + static_cast<int64_t>(C + R * (S - 1)) * n_pad;
     const bool zlds = a.zmem == 0 && C1 - C0 <= ZMAX;
-    for (int J = C0; J < C1; ++J) {
+    for (int J = C0; J < C1 && !(S > 1 && diag); ++J) {
         if (zlds)
             s_zacc[J - C0][tid] = 0.f;
         else
@@ -1774,9 +1809,11 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(D <= 4 ? 
     }
     int skipped = 0;
     for (int I = I0; I < I1; ++I) {
-        double aI[D];
+        double aK[D < 16 ? D : 1];
+        if constexpr (D < 16) {
 #pragma unroll
-        for (int k = 0; k < D; ++k) aI[k] = a.row_anchor[static_cast<int64_t>(I) * D + k];
+            for (int k = 0; k < D; ++k) aK[k] = a.row_anchor[static_cast<int64_t>(I) * D + k];
+        }
         const int Js = diag ? I : C0;
         const unsigned char *live = s_live;
         if (!at_once) {
@@ -1790,14 +1827,14 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(D <= 4 ? 
             return J;
         };
         const int Jfirst = next_live(Js);
-        skipped += Jfirst - Js;
+        if (part == 0) skipped += Jfirst - Js;
         if (Jfirst >= C1) {
             const int64_t i = static_cast<int64_t>(I) * TILE + tid;
-            if (!diag) yslot[i] = 0.f;
+            if (!diag && (S == 1 || tid / UNIT == part)) yslot[i] = 0.f;
             if (!at_once) __syncthreads();  // s_live is rewritten for the next row tile
             continue;
         }
-        for (int half = 0; half < TILE / UNIT; ++half) {
+        for (int half = part; half < (S > 1 ? part + 1 : TILE / UNIT); ++half) {
             const int64_t row0 = static_cast<int64_t>(I) * TILE + half * UNIT + wv * 32;
             // the lane's A-operand target row0 + r32 (octet h of its slots)
             float oi[D];
@@ -1828,6 +1865,13 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(D <= 4 ? 
                 const float njf = static_cast<float>(a.tile_nj[J]);  // a small integer
                 const float far_t2 = a.tile_far[J];
                 const double *__restrict__ aJ = a.anchor + static_cast<int64_t>(J) * D;
+                // at d = 16 the row tile's anchor is read again per column tile, with
+                // aJ's loads (kept in registers, its 32 were spilled; N = 60,000
+                // Matern 761 -> 730 us; at d = 8 the kept one is 3 % faster)
+                int Ia = I;
+                if constexpr (D >= 16) asm volatile("" : "+s"(Ia));
+                const double *__restrict__ aR = a.row_anchor + static_cast<int64_t>(Ia) * D;
+                auto aI = [&](int k) { return D < 16 ? aK[D < 16 ? k : 0] : aR[k]; };
                 const bool sym = J != I;
                 const int64_t jz = static_cast<int64_t>(J) * TILE + tid;
                 const float zold = (sym && !zlds) ? zslot[jz] : 0.f;
@@ -1840,7 +1884,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(D <= 4 ? 
                         double tt = 0.0;
 #pragma unroll
                         for (int k = 0; k < D; ++k) {
-                            const double td = (aI[k] - aJ[k]) + static_cast<double>(oi[k]);
+                            const double td = (aI(k) - aJ[k]) + static_cast<double>(oi[k]);
                             t[k] = static_cast<float>(td);
                             tt = __builtin_fma(td, td, tt);
                         }
@@ -1937,7 +1981,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(D <= 4 ? 
                             const Off *rp = row_off + i;
 #pragma unroll
                             for (int k = 0; k < D; ++k) {
-                                tg[k] = static_cast<float>((aI[k] - aJ[k]) + static_cast<double>(P::off(*rp)));
+                                tg[k] = static_cast<float>((aI(k) - aJ[k]) + static_cast<double>(P::off(*rp)));
                                 rp += a.n_pad_rows;
                                 asm volatile("" : "+v"(rp));
                             }
@@ -2030,6 +2074,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(D <= 4 ? 
                 const int64_t i = static_cast<int64_t>(I) * TILE + il;
                 if (!diag)
                     yslot[i] = s_z[tid];
+                else if (S > 1)
+                    yslot[i] = s_z[tid];  // one tile: no source terms
                 else if (zlds)
                     yslot[i] = s_z[tid] + s_zacc[I - C0][il];  // the source terms of tile I are complete
                 else
@@ -2067,7 +2113,7 @@ template <int PREC>
 constexpr int finish_rows() { return WAVE * static_cast<int>(16 / sizeof(typename Prec<PREC>::T)); }
 // perm non-null: y in the original order (row i to perm[i], the padding left out).
 template <int PREC>
-__global__ __launch_bounds__(BLOCK) void k_kmvp_finish(int64_t n, int64_t n_pad, int ngroups, const void *parts_,
+__global__ __launch_bounds__(BLOCK) void k_kmvp_finish(int64_t n, int64_t n_pad, PartSlots slots, const void *parts_,
                                                        const void *q_, double shift, int square, void *y_,
                                                        const int32_t *__restrict__ perm, const int *active) {
     if (active != nullptr && *active == 0) return;
@@ -2083,11 +2129,13 @@ __global__ __launch_bounds__(BLOCK) void k_kmvp_finish(int64_t n, int64_t n_pad,
     const int lane = threadIdx.x % WAVE, wv = threadIdx.x / WAVE;
     const int64_t i0 = blockIdx.x * static_cast<int64_t>(finish_rows<PREC>()) + lane * V;
     VT acc = {};
+    // the block's rows lie in one tile
+    const int ns = slots.n + static_cast<int>(blockIdx.x * finish_rows<PREC>() / TILE) * slots.step;
     if (i0 < n_pad) {  // n_pad is a multiple of V: the whole vector is inside
         const VT *p = reinterpret_cast<const VT *>(parts + i0);
         const int64_t stride = n_pad / V;
 #pragma unroll 8
-        for (int k = wv; k < ngroups; k += NW) acc += p[static_cast<int64_t>(k) * stride];
+        for (int k = wv; k < ns; k += NW) acc += p[static_cast<int64_t>(k) * stride];
     }
     if (wv > 0) s_part[wv - 1][lane] = acc;
     __syncthreads();
@@ -2688,9 +2736,31 @@ int kmvp_sym_ngroups(const Prepared &P) {
     const int gs = kmvp_sym_group_tiles(P);
     return (P.ntiles + gs - 1) / gs;
 }
+// Blocks per pair of groups of the symmetric products, each with a share of the
+// row tile (one tile per group): one block per pair of tiles leaves compute units
+// idle up to 22 tiles (253 pairs) and, at one wave per SIMD, shows every latency.
+// FP64: 4 blocks of 64 rows up to 12 tiles (312 blocks), 2 of 128 rows up to 32
+// (1056); kernel, one block against these (us):  n = 2000: d = 2 24.9 / 13.8,
+// d = 16 57.7 / 19.3;  n = 5000: 25.8 / 22.4, 56.8 / 41.3;  n = 8000: 48.8 /
+// 45.9, 97.9 / 84.5;  beyond, the shares' set-up costs more than it fills (n =
+// 11,000: 61.7 / 69.5, 125 / 128).  FP32 / BF16: 2 blocks of 128 rows up to 20
+// tiles (n = 2000: 11.8 / 9.0; n = 5000: 12.8 / 11.0; n = 8000: 16.9 / 16.8 and
+// the sum over the slots 2 us longer).
+static int kmvp_sym_units(const Prepared &P, int prec) {
+    if (prec == KRR_FP64) return P.ntiles <= 12 ? 4 : P.ntiles <= 32 ? 2 : 1;
+    return P.ntiles <= 20 ? 2 : 1;
+}
 // Partial-sum slots of a square product's scratch (either layout).
 int kmvp_parts_slots(const Prepared &P) {
-    const int a = kmvp_ngroups(P), b = sym_capable(P) ? kmvp_sym_ngroups(P) : 0;
+    const int a = kmvp_ngroups(P);
+    int b = 0;
+    if (sym_capable(P)) {
+        b = kmvp_sym_ngroups(P);
+        for (int prec : {KRR_FP64, KRR_FP32, KRR_BF16}) {
+            const int s = kmvp_sym_ngroups(P) + (P.ntiles - 1) * (kmvp_sym_units(P, prec) - 1);
+            b = s > b ? s : b;
+        }
+    }
     return a > b ? a : b;
 }
 
@@ -2909,24 +2979,28 @@ static bool use_sym_kernel(const Prepared &P, int prec) {
 template <int D>
 static hipError_t launch_kmvp_sym(const KArgs &a, bool mat, hipStream_t s) {
     if constexpr (ms_supported<D>()) {
-        const int nb = a.ngroups * (a.ngroups + 1) / 2;
-        if (mat)
-            hipLaunchKernelGGL((k_kmvp_ms<D, true>), dim3(nb), dim3(BLOCK), 0, s, a);
-        else
-            hipLaunchKernelGGL((k_kmvp_ms<D, false>), dim3(nb), dim3(BLOCK), 0, s, a);
-        return hipGetLastError();
+        const int nb = a.ngroups * (a.ngroups + 1) / 2 * a.units;
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(nb), dim3(BLOCK), 0, s, a);
+            return hipGetLastError();
+        };
+        if (a.units == 4) return mat ? go(k_kmvp_ms<D, true, 1>) : go(k_kmvp_ms<D, false, 1>);
+        if constexpr (D < 8)
+            if (a.units == 1) return mat ? go(k_kmvp_ms<D, true, 4>) : go(k_kmvp_ms<D, false, 4>);
+        return mat ? go(k_kmvp_ms<D, true, 2>) : go(k_kmvp_ms<D, false, 2>);
     }
     return hipErrorInvalidValue;
 }
 
 template <int D, int PREC>
 static hipError_t launch_kmvp_sym_h(const KArgs &a, bool mat, hipStream_t s) {
-    const int nb = a.ngroups * (a.ngroups + 1) / 2;
-    if (mat)
-        hipLaunchKernelGGL((k_kmvp_mhs<D, PREC, true>), dim3(nb), dim3(BLOCK), 0, s, a);
-    else
-        hipLaunchKernelGGL((k_kmvp_mhs<D, PREC, false>), dim3(nb), dim3(BLOCK), 0, s, a);
-    return hipGetLastError();
+    const int nb = a.ngroups * (a.ngroups + 1) / 2 * a.units;
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(nb), dim3(BLOCK), 0, s, a);
+        return hipGetLastError();
+    };
+    if (a.units > 1) return mat ? go(k_kmvp_mhs<D, PREC, true, true>) : go(k_kmvp_mhs<D, PREC, false, true>);
+    return mat ? go(k_kmvp_mhs<D, PREC, true, false>) : go(k_kmvp_mhs<D, PREC, false, false>);
 }
 
 template <int PREC>
@@ -3006,11 +3080,11 @@ static hipError_t launch_prescale(const Prepared &C, int prec, const void *q, co
     return prec == KRR_FP64 ? go(k_prescale<KRR_FP64>) : prec == KRR_FP32 ? go(k_prescale<KRR_FP32>) : go(k_prescale<KRR_BF16>);
 }
 
-static hipError_t launch_finish(const Prepared &R, int prec, int ng, double shift, bool square, const void *q, void *y,
+static hipError_t launch_finish(const Prepared &R, int prec, PartSlots slots, double shift, bool square, const void *q, void *y,
                                 const int32_t *perm, const KmvpScratch &sc, const int *active, hipStream_t s) {
     auto go = [&](auto kern, int rows) {
         hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>((R.n_pad + rows - 1) / rows)), dim3(BLOCK), 0, s, R.n,
-                           R.n_pad, ng, sc.parts, q, shift, square ? 1 : 0, y, perm, active);
+                           R.n_pad, slots, sc.parts, q, shift, square ? 1 : 0, y, perm, active);
         return hipGetLastError();
     };
     return prec == KRR_FP64   ? go(k_kmvp_finish<KRR_FP64>, finish_rows<KRR_FP64>())
@@ -3023,7 +3097,7 @@ static hipError_t launch_finish(const Prepared &R, int prec, int ng, double shif
 // slots it left in sc.parts (0: it wrote y, with the shift).
 static hipError_t kmvp_launch(const Prepared &R, const Prepared &C, int prec, const KmvpPlan &pl, double shift,
                               const void *q, void *y, const KmvpScratch &sc, const int *active, bool timed_slot,
-                              int *parts, hipStream_t s) {
+                              PartSlots *parts, hipStream_t s) {
     const bool square = (&R == &C);
     // the symmetric kernels for square products (plan.sym_gs > 0)
     const bool sym = square && pl.sym_gs > 0;
@@ -3061,7 +3135,9 @@ static hipError_t kmvp_launch(const Prepared &R, const Prepared &C, int prec, co
     a.lo = sc.lo;
     a.clear = prec == KRR_FP64 ? EPS_FP64 : EPS_FP32;
     for (int t = 1; t < C.ntiles; t *= 2) ++a.clear;  // + ceil(log2(tiles))
-    *parts = use_parts ? a.ngroups : 0;
+    a.units = sym ? pl.sym_units : 1;
+    *parts = PartSlots{};
+    if (use_parts) *parts = PartSlots{a.ngroups, a.units - 1};
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     const bool timed =
         timed_slot && profile_slot(prec, static_cast<double>(R.n) * static_cast<double>(C.n), &ev0, &ev1,
@@ -3102,16 +3178,16 @@ static hipError_t kmvp_run(const Prepared &R, const Prepared &C, int prec, const
                            const void *q, void *y, const KmvpScratch &sc, const int *active, bool timed_slot,
                            hipStream_t s) {
     const bool square = (&R == &C);
-    int parts = 0;
+    PartSlots parts;
     KRR_HIP(launch_prescale(C, prec, q, sc, square && pl.sym_gs > 0, active, s));
     KRR_HIP(kmvp_launch(R, C, prec, pl, shift, q, y, sc, active, timed_slot, &parts, s));
-    return parts > 0 ? launch_finish(R, prec, parts, shift, square, q, y, nullptr, sc, active, s) : hipSuccess;
+    return parts.n > 0 ? launch_finish(R, prec, parts, shift, square, q, y, nullptr, sc, active, s) : hipSuccess;
 }
 
 static KmvpPlan square_plan(const Prepared &P, int prec) {
     KmvpPlan pl;
     if (use_sym_kernel(P, prec))
-        pl.sym_gs = kmvp_sym_group_tiles(P);
+        pl.sym_gs = kmvp_sym_group_tiles(P), pl.sym_units = kmvp_sym_units(P, prec);
     else
         pl = kmvp_plan(P, prec);
     return pl;
@@ -3122,10 +3198,10 @@ hipError_t kmvp_sorted(const Prepared &P, int prec, double shift, const void *q,
     return kmvp_run(P, P, prec, square_plan(P, prec), shift, q, y, sc, active, true, s);
 }
 
-int kmvp_live_slots(const Prepared &P, int prec) {
-    if (use_sym_kernel(P, prec)) return kmvp_sym_ngroups(P);
+PartSlots kmvp_live_slots(const Prepared &P, int prec) {
+    if (use_sym_kernel(P, prec)) return PartSlots{kmvp_sym_ngroups(P), kmvp_sym_units(P, prec) - 1};
     const int ng = kmvp_ngroups(P);
-    return ng > 1 ? ng : 0;
+    return PartSlots{ng > 1 ? ng : 0, 0};
 }
 
 Prescale kmvp_prescaler(const Prepared &P, int prec, const KmvpScratch &sc) {
@@ -3134,14 +3210,14 @@ Prescale kmvp_prescaler(const Prepared &P, int prec, const KmvpScratch &sc) {
 
 hipError_t kmvp_scaled(const Prepared &P, int prec, double shift, const void *q, void *y, const KmvpScratch &sc,
                        const int *active, hipStream_t s) {
-    int parts = 0;
+    PartSlots parts;
     KRR_HIP(kmvp_launch(P, P, prec, square_plan(P, prec), shift, q, y, sc, active, true, &parts, s));
-    return parts > 0 ? launch_finish(P, prec, parts, shift, true, q, y, nullptr, sc, active, s) : hipSuccess;
+    return parts.n > 0 ? launch_finish(P, prec, parts, shift, true, q, y, nullptr, sc, active, s) : hipSuccess;
 }
 
 hipError_t kmvp_core(const Prepared &P, int prec, double shift, const void *q, void *y, const KmvpScratch &sc,
                      const int *active, hipStream_t s) {
-    int parts = 0;
+    PartSlots parts;
     return kmvp_launch(P, P, prec, square_plan(P, prec), shift, q, y, sc, active, true, &parts, s);
 }
 

@@ -202,7 +202,8 @@ hipError_t scatter_sorted(const Prepared &P, const Tin *src, Tout *dst, hipStrea
 struct KmvpPlan {
     int splits = 1;          // column splits
     int tiles_per_split = 0;
-    int sym_gs = 0;          // > 0: the symmetric FP64 kernel with groups of sym_gs tiles
+    int sym_gs = 0;          // > 0: the symmetric kernels with groups of sym_gs tiles
+    int sym_units = 1;       // and blocks per pair of groups
 };
 // Scratch of one product: group partial sums (kmvp_parts_slots x n_pad, 8
 // bytes each)
@@ -217,16 +218,19 @@ int kmvp_parts_slots(const Prepared &P);
 KmvpPlan kmvp_plan(const Prepared &P, int prec);  // tuned, else a heuristic
 KmvpScratch carve_kmvp_scratch(Carver &cv, const Prepared &P);
 // The parts of a square product on prescaled sources: the kernel
-// (partial sums in sc.parts, or y itself when kmvp_live_slots is 0), and the sum
+// (partial sums in sc.parts, or y itself when kmvp_live_slots has none), and the sum
 // of the partial sums + shift q, in sorted order or (perm) scattered to the
 // original one.
 hipError_t kmvp_core(const Prepared &P, int prec, double shift, const void *q, void *y, const KmvpScratch &sc,
                      const int *active, hipStream_t s);
 hipError_t kmvp_finish(const Prepared &P, int prec, double shift, const void *q, void *y, const int32_t *perm,
                        const KmvpScratch &sc, const int *active, hipStream_t s);
-// The partial-sum slots a square product of this set and precision leaves (0:
+// The partial-sum slots a square product of this set and precision leaves (n = 0:
 // none, it writes y itself).
-int kmvp_live_slots(const Prepared &P, int prec);
+struct PartSlots {
+    int n = 0, step = 0;  // rows of tile t: the first n + t step slots
+};
+PartSlots kmvp_live_slots(const Prepared &P, int prec);
 const void *kmvp_weights(const Prepared &P, int prec);  // w_j in the precision, null for Matern
 // The prescale of products of this set and precision, for kernels that produce q.
 struct Prescale;

@@ -184,7 +184,7 @@ __global__ __launch_bounds__(BLOCK) void k_cg_pupdate(int64_t n_pad, const T *__
 // each slot per lane, the slots over the waves), p.Ap and the step length by the
 // last block.
 template <typename T>
-__global__ __launch_bounds__(BLOCK) void k_cg_finish(int64_t n, int64_t n_pad, int slots, const T *__restrict__ parts,
+__global__ __launch_bounds__(BLOCK) void k_cg_finish(int64_t n, int64_t n_pad, PartSlots slots, const T *__restrict__ parts,
                                                      const T *__restrict__ p, const uint16_t *__restrict__ p16,
                                                      double shift, T *Ap, CgScalars<T> *S, double *partials,
                                                      unsigned *counter) {
@@ -196,11 +196,13 @@ __global__ __launch_bounds__(BLOCK) void k_cg_finish(int64_t n, int64_t n_pad, i
     const int lane = threadIdx.x % WAVE, wv = threadIdx.x / WAVE;
     const int64_t i0 = blockIdx.x * static_cast<int64_t>(WAVE * V) + lane * V;
     VT acc = {};
+    // the block's rows lie in one tile
+    const int ns = slots.n + static_cast<int>(blockIdx.x * (WAVE * V) / TILE) * slots.step;
     if (i0 < n_pad) {
         const VT *src = reinterpret_cast<const VT *>(parts + i0);
         const int64_t stride = n_pad / V;
 #pragma unroll 8
-        for (int k = wv; k < slots; k += NW) acc += src[static_cast<int64_t>(k) * stride];
+        for (int k = wv; k < ns; k += NW) acc += src[static_cast<int64_t>(k) * stride];
     }
     if (wv > 0) s_part[wv - 1][lane] = acc;
     __syncthreads();
@@ -263,7 +265,7 @@ __device__ __forceinline__ double small_sum(double v, double *sh) {
 }
 
 template <typename T>
-__global__ __launch_bounds__(SMALL_THREADS) void k_cg_small(int n, int n_pad, int slots, const T *__restrict__ parts,
+__global__ __launch_bounds__(SMALL_THREADS) void k_cg_small(int n, int n_pad, PartSlots slots, const T *__restrict__ parts,
                                                             T *x, T *r, T *p, uint16_t *p16, Prescale ps, double shift,
                                                             CgScalars<T> *S, double *hist, int hist_cap) {
     constexpr int PER = static_cast<int>(SMALL_CG_N) / SMALL_THREADS;
@@ -283,11 +285,13 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_cg_small(int n, int n_pad, in
         ap[k] = T(0);
     }
 #pragma unroll 8
-    for (int u = 0; u < slots; ++u) {
+    for (int u = 0; u < slots.n + (n_pad / TILE - 1) * slots.step; ++u) {
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
             const int i = tid + k * SMALL_THREADS;
-            ap[k] += parts[u * n_pad + (i < n_pad ? i : 0)];
+            const bool in = i < n_pad && u < slots.n + i / TILE * slots.step;
+            const T v = parts[in ? u * n_pad + i : 0];
+            ap[k] += in ? v : T(0);
         }
     }
 #pragma unroll
@@ -656,18 +660,18 @@ hipError_t cg_step(const Prepared &P, int prec, double shift, const CgVecs<T> &c
     const void *qin = (prec == KRR_BF16) ? static_cast<const void *>(c.p16) : static_cast<const void *>(c.p);
     KRR_HIP(kmvp_core(P, prec, shift, qin, c.Ap, sc, &c.S->active, s));
     const int nb = vec_blocks(c.n_pad);
-    const int slots = kmvp_live_slots(P, prec);
+    const PartSlots slots = kmvp_live_slots(P, prec);
     const T *parts = static_cast<const T *>(sc.parts);
     T *part = reinterpret_cast<T *>(R.partials);
     // one block up to 4096 entries (16 tiles: 16 slots at most); measured at 2048
     // and 4096, beyond it one CU's loads of the partial sums take over
-    if (slots > 0 && c.n_pad <= SMALL_CG_N) {
+    if (slots.n > 0 && c.n_pad <= SMALL_CG_N) {
         hipLaunchKernelGGL(k_cg_small<T>, dim3(1), dim3(SMALL_THREADS), 0, s, static_cast<int>(P.n),
                            static_cast<int>(c.n_pad), slots, parts, c.x, c.r, c.p, c.p16, c.ps, shift, c.S, c.hist,
                            c.hist_cap);
         return hipGetLastError();
     }
-    if (slots > 0) {
+    if (slots.n > 0) {
         constexpr int rows = WAVE * static_cast<int>(16 / sizeof(T));
         LAUNCH(k_cg_finish<T>, static_cast<unsigned>((c.n_pad + rows - 1) / rows), P.n, c.n_pad, slots, parts, c.p, c.p16,
                shift, c.Ap, c.S, R.partials, R.counters + 14);
