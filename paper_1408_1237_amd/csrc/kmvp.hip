@@ -3338,6 +3338,8 @@ thread_local bool g_prof_suspended = false;
 
 void profile_suspend(bool on) { g_prof_suspended = on; }
 
+bool profiling() { return g_prof.on; }
+
 int progress_every() {
     static const int every = [] {
         const char *v = std::getenv("KRR_PROGRESS");

@@ -322,6 +322,7 @@ hipError_t predict_var_block(const double *B, const double *W, int64_t n, int64_
 // Progress lines on stderr: KRR_PROGRESS=k prints one line every k outer steps
 // of a solve (0 or unset: silent).
 int progress_every();
+bool profiling();  // a launch timing (profile_begin) is running
 
 // bf16 conversion of a float vector (round to nearest even).
 hipError_t to_bf16(const float *src, uint16_t *dst, int64_t n, hipStream_t s);

@@ -34,8 +34,11 @@ struct CgVecs {
 int vec_blocks(int64_t n_pad);
 hipError_t red_init(const Red &R, hipStream_t s);
 
+// gate (null: none): an FGMRES state; the solve is started finished (no iteration)
+// when it has broken down or its estimate is at gate_tol.
 template <typename T, typename TV>
-hipError_t cg_init(const CgVecs<T> &c, const TV *rhs, double tol, int maxit, const Red &R, hipStream_t s);
+hipError_t cg_init(const CgVecs<T> &c, const TV *rhs, double tol, int maxit, const Red &R, hipStream_t s,
+                   const FgmresScalars *gate = nullptr, double gate_tol = 0.0);
 template <typename T>
 hipError_t cg_step(const Prepared &P, int prec, double shift, const CgVecs<T> &c, const KmvpScratch &sc,
                    const Red &R, hipStream_t s);

@@ -90,7 +90,8 @@ __device__ __forceinline__ void store_direction(const Prescale &ps, int64_t i, i
 template <typename T, typename TV>
 __global__ __launch_bounds__(BLOCK) void k_cg_init(int64_t n_pad, const TV *__restrict__ rhs, T *x, T *r, T *p,
                                                    uint16_t *p16, Prescale ps, CgScalars<T> *S, double tol2, int maxit,
-                                                   T *partials, unsigned *counter) {
+                                                   const FgmresScalars *gate, double gate_tol, T *partials,
+                                                   unsigned *counter) {
     __shared__ double sh[2 * TILE / SUB];
     T acc[1] = {T(0)};
     GRID_STRIDE(i, n_pad) {
@@ -110,7 +111,8 @@ __global__ __launch_bounds__(BLOCK) void k_cg_init(int64_t n_pad, const TV *__re
         S->maxit = maxit;
         S->status = isfinite(static_cast<double>(rr)) ? 0 : KRR_ENONFINITE;
         S->candidate = (rr == T(0)) ? 1 : 0;
-        S->active = (rr > T(0) && maxit > 0 && S->status == 0) ? 1 : 0;
+        const bool stop = gate != nullptr && (gate->breakdown || gate->nonfinite || gate->est <= gate_tol);
+        S->active = (rr > T(0) && maxit > 0 && S->status == 0 && !stop) ? 1 : 0;
     }
 }
 
@@ -648,9 +650,10 @@ hipError_t red_init(const Red &R, hipStream_t s) {
 }
 
 template <typename T, typename TV>
-hipError_t cg_init(const CgVecs<T> &c, const TV *rhs, double tol, int maxit, const Red &R, hipStream_t s) {
+hipError_t cg_init(const CgVecs<T> &c, const TV *rhs, double tol, int maxit, const Red &R, hipStream_t s,
+                   const FgmresScalars *gate, double gate_tol) {
     LAUNCH((k_cg_init<T, TV>), vec_blocks(c.n_pad), c.n_pad, rhs, c.x, c.r, c.p, c.p16, c.ps, c.S, tol * tol, maxit,
-           reinterpret_cast<T *>(R.partials), R.counters + 0);
+           gate, gate_tol, reinterpret_cast<T *>(R.partials), R.counters + 0);
     return hipGetLastError();
 }
 
@@ -691,11 +694,11 @@ hipError_t cg_restart(const CgVecs<T> &c, const T *b, const T *Kx, const Red &R,
 }
 
 template hipError_t cg_init<float, double>(const CgVecs<float> &, const double *, double, int, const Red &,
-                                           hipStream_t);
+                                           hipStream_t, const FgmresScalars *, double);
 template hipError_t cg_init<float, float>(const CgVecs<float> &, const float *, double, int, const Red &,
-                                          hipStream_t);
+                                          hipStream_t, const FgmresScalars *, double);
 template hipError_t cg_init<double, double>(const CgVecs<double> &, const double *, double, int, const Red &,
-                                            hipStream_t);
+                                            hipStream_t, const FgmresScalars *, double);
 template hipError_t cg_step<float>(const Prepared &, int, double, const CgVecs<float> &, const KmvpScratch &,
                                    const Red &, hipStream_t);
 template hipError_t cg_step<double>(const Prepared &, int, double, const CgVecs<double> &, const KmvpScratch &,
