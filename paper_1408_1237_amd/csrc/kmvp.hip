@@ -148,8 +148,7 @@ __device__ __forceinline__ bool tiles_far(const double (&aI)[D], double rI, cons
 // concave log2(1 + s) at s = 7).  One thread per pair, a block's pairs at once:
 // the test is one round trip to memory.
 template <int D, bool MAT, bool F64>
-__device__ __forceinline__ bool pair_live(const KArgs &a, int I, int J) {
-    const double *bi = a.box + static_cast<int64_t>(I) * 2 * D, *bj = a.box + static_cast<int64_t>(J) * 2 * D;
+__device__ __forceinline__ bool gap_live(const KArgs &a, int I, int J, const double *bi, const double *bj) {
     const int need = max(a.up[J] - a.lo[I], a.up[I] - a.lo[J]) + a.clear;
     const float r2 = MAT ? 0.f : static_cast<float>(a.tile_r2[J]);
     double d2 = 0.0;
@@ -168,6 +167,40 @@ __device__ __forceinline__ bool pair_live(const KArgs &a, int I, int J) {
         far = (F64 ? 1101.f : 201.f) + 0.5f * r2;
     }
     return static_cast<float>(d2) < fminf(negl, far) * 1.00001f + 1e-3f;
+}
+template <int D, bool MAT, bool F64>
+__device__ __forceinline__ bool pair_live(const KArgs &a, int I, int J) {
+    return gap_live<D, MAT, F64>(a, I, J, a.box + static_cast<int64_t>(I) * BOX * D, a.box + static_cast<int64_t>(J) * BOX * D);
+}
+// The same for the two halves (128 rows) of tile I against tile J: bit h for half
+// h, never where the half holds no points.  The halves' parts of what a row or a
+// source of J loses add up to the tile's at most.  N = 1e5, d = 3, sigma = 1/20 of
+// the cube: 61 % of the pairs of a half are live, against 65 % of the tiles'.
+template <int D, bool MAT, bool F64>
+__device__ __forceinline__ unsigned char halves_live(const KArgs &a, int I, int J) {
+    const double *bi = a.box + static_cast<int64_t>(I) * BOX * D, *bj = a.box + static_cast<int64_t>(J) * BOX * D;
+    return (gap_live<D, MAT, F64>(a, I, J, bi + 2 * D, bj) ? 1 : 0) | (gap_live<D, MAT, F64>(a, I, J, bi + 4 * D, bj) ? 2 : 0);
+}
+
+// The entries of live (of tile C0 on) that have a bit of `bits`, up to 64 of them.
+__device__ __forceinline__ uint64_t live_mask(const unsigned char *live, int n, int bits, int lane) {
+    return __ballot(lane < n && (live[min(lane, n - 1)] & bits) != 0);
+}
+// The first column tile from J on (below C1) that has one, else C1: out of the
+// mask where a group has at most 64 tiles (one look at LDS per row unit; walking
+// the entries one by one was a chain of LDS reads on mostly dead groups).
+__device__ __forceinline__ int next_live_tile(uint64_t mask, const unsigned char *live, int C0, int J, int C1, int bits,
+                                              int lane) {
+    if (C1 - C0 <= WAVE) {
+        if (J >= C1) return C1;
+        const uint64_t m = mask >> (J - C0);
+        return m != 0 ? J + __builtin_ctzll(m) : C1;
+    }
+    for (; J < C1; J += WAVE) {
+        const uint64_t m = live_mask(live + (J - C0), C1 - J, bits, lane);
+        if (m != 0) return J + __builtin_ctzll(m);
+    }
+    return C1;
 }
 
 template <int D, int PREC>
@@ -1799,12 +1832,22 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(D <= 4 ? 
         swap_halves(zl, z0, z1);
         s_z[wv * TILE + cb + r32] = z0 + z1;
     };
-    // live tests of the block's tile pairs (the diagonal's lower half unused)
+    // live tests of the block's tile pairs (the diagonal's lower half unused): per
+    // half of the row tile, a row unit each, up to d = 4 (N = 1e5, d = 3 2-3 % fewer
+    // us, clustered N = 1e6 3-5 %); above, boxes seldom clear anything and the tests
+    // per unit cost 2-3 % (Matern, d = 8, N = 50,000), and so they do on sets of up
+    // to 100 tiles (one tile per group)
+    constexpr bool HALVES = D <= 4;
+    auto test = [&](int I, int J) -> unsigned char {
+        if constexpr (HALVES)
+            if (gs > 1) return halves_live<D, MAT, false>(a, I, J);
+        return pair_live<D, MAT, false>(a, I, J) ? 3 : 0;
+    };
     const bool skip = a.row_r2 != nullptr;  // null: no skipping
     const bool at_once = (I1 - I0) * (C1 - C0) <= MS_MAX_GROUP_TILES;
     if (at_once) {
         for (int t = tid; t < (I1 - I0) * (C1 - C0); t += BLOCK)
-            s_live[t] = skip ? pair_live<D, MAT, false>(a, I0 + t / (C1 - C0), C0 + t % (C1 - C0)) : 1;
+            s_live[t] = skip ? test(I0 + t / (C1 - C0), C0 + t % (C1 - C0)) : 3;
         __syncthreads();
     }
     int skipped = 0;
@@ -1817,24 +1860,42 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(D <= 4 ? 
         const int Js = diag ? I : C0;
         const unsigned char *live = s_live;
         if (!at_once) {
-            for (int jj = tid; jj < C1 - C0; jj += BLOCK) s_live[jj] = skip ? pair_live<D, MAT, false>(a, I, C0 + jj) : 1;
+            for (int jj = tid; jj < C1 - C0; jj += BLOCK) s_live[jj] = skip ? test(I, C0 + jj) : 3;
             __syncthreads();
         } else {
             live += (I - I0) * (C1 - C0);
         }
-        auto next_live = [&](int J) {
+        auto scan = [&](int J) {
             while (J < C1 && live[J - C0] == 0) ++J;
             return J;
         };
-        const int Jfirst = next_live(Js);
-        if (part == 0) skipped += Jfirst - Js;
-        if (Jfirst >= C1) {
-            const int64_t i = static_cast<int64_t>(I) * TILE + tid;
-            if (!diag && (S == 1 || tid / UNIT == part)) yslot[i] = 0.f;
-            if (!at_once) __syncthreads();  // s_live is rewritten for the next row tile
-            continue;
+        int Jfirst = 0;
+        if constexpr (!HALVES) {
+            Jfirst = scan(Js);
+            if (part == 0) skipped += Jfirst - Js;
+            if (Jfirst >= C1) {
+                // no live column tile: zero target terms (the source-side slots stay as they are)
+                const int64_t i = static_cast<int64_t>(I) * TILE + tid;
+                if (!diag && (S == 1 || tid / UNIT == part)) yslot[i] = 0.f;
+                if (!at_once) __syncthreads();  // s_live is rewritten for the next row tile
+                continue;
+            }
         }
         for (int half = part; half < (S > 1 ? part + 1 : TILE / UNIT); ++half) {
+            const uint64_t mask = HALVES ? live_mask(live, C1 - C0, 1 << half, lane) : 0;
+            auto next_live = [&](int J) {
+                if constexpr (HALVES) return next_live_tile(mask, live, C0, J, C1, 1 << half, lane);
+                return scan(J);
+            };
+            if constexpr (HALVES) {
+                Jfirst = next_live(Js);
+                skipped += Jfirst - Js;
+                if (Jfirst >= C1) {
+                    // (on the diagonal only the padding has none)
+                    if (!diag && tid < UNIT) yslot[static_cast<int64_t>(I) * TILE + half * UNIT + tid] = 0.f;
+                    continue;
+                }
+            }
             const int64_t row0 = static_cast<int64_t>(I) * TILE + half * UNIT + wv * 32;
             // the lane's A-operand target row0 + r32 (octet h of its slots)
             float oi[D];
@@ -1859,7 +1920,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(D <= 4 ? 
             int buf = 0;
             while (J < C1) {
                 const int Jn = next_live(J + 1);
-                if (half == 0) skipped += Jn - J - 1;
+                if (HALVES || half == 0) skipped += Jn - J - 1;
                 if (Jn < C1) stage_load(Jn);
                 const double r2 = a.tile_r2[J];
                 const float njf = static_cast<float>(a.tile_nj[J]);  // a small integer
@@ -2083,12 +2144,13 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(D <= 4 ? 
             }
             __syncthreads();
         }
+        if (HALVES && !at_once) __syncthreads();  // s_live is rewritten for the next row tile
     }
     if (zlds && !diag) {
         for (int J = C0; J < C1; ++J) zslot[static_cast<int64_t>(J) * TILE + tid] = s_zacc[J - C0][tid];
     }
     if (a.skip_count != nullptr && tid == 0 && skipped > 0)
-        atomicAdd(a.skip_count, static_cast<unsigned long long>(skipped) * 2 * TILE);
+        atomicAdd(a.skip_count, static_cast<unsigned long long>(skipped) * 2 * (HALVES ? UNIT : TILE));
 }
 
 // qw_j = q_j * w_j (the per-source factor of the folded form; w null: none), and

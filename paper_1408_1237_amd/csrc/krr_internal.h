@@ -125,6 +125,7 @@ struct RedScratch {
     static constexpr int NPARTIAL_SLOTS = 4;
 };
 
+constexpr int BOX = 6;  // vectors of a tile's boxes: low and high corner of the tile and of each half
 struct Prepared {
     int64_t n = 0, n_pad = 0;
     int d = 0, dpad = 0;      // dpad: dimension of the kernel instance (>= d, extra coords 0)
@@ -153,9 +154,9 @@ struct Prepared {
     // 2 split_chunks(dpad) octets per point, octet-major ([octet][n_pad]), for dpad <= 48
     void *slot32 = nullptr;
     void *slot16 = nullptr;
-    // per tile, dpad <= 16 (the symmetric products): its bounding box in scaled
-    // coordinates ([tile][lo, hi][dpad]) and, per 32 points of it, the ceiling of
-    // -log2 of the kernel across their box (neglog2_kernel; -1: no points)
+    // per tile, dpad <= 16 (the symmetric products): the bounding boxes of it and of
+    // its two halves in scaled coordinates ([tile][BOX][dpad]) and, per 32 points of it,
+    // the ceiling of -log2 of the kernel across their box (neglog2_kernel; -1: no points)
     double *box = nullptr;
     int *sub_reach = nullptr;  // [tile][8]
     int *flags = nullptr;     // [0]: non-finite input seen

@@ -53,7 +53,7 @@ Prepared carve_prepared(Carver &cv, int64_t n, int d) {
         P.slot16 = cv.take<half8_t>(static_cast<size_t>(oct) * P.n_pad);
     }
     if (P.dpad <= 16) {
-        P.box = cv.take<double>(2 * static_cast<size_t>(P.ntiles) * P.dpad);
+        P.box = cv.take<double>(BOX * static_cast<size_t>(P.ntiles) * P.dpad);
         P.sub_reach = cv.take<int>(static_cast<size_t>(P.ntiles) * (TILE / SUB));
     }
     P.flags = cv.take<int>(4);
@@ -302,7 +302,7 @@ __global__ __launch_bounds__(TILE) void k_tiles(const double *__restrict__ x, in
             if (c0 + k < D) s_v[k][tid] = real ? xr[c0 + k] * scale : NAN;  // fmin / fmax pass a NaN over
         __syncthreads();
         const int k = tid / LANES, part = tid % LANES;
-        if (k < CH && c0 + k < D) {
+        if (D > 16 && k < CH && c0 + k < D) {
             double lo = INFINITY, hi = -INFINITY;
 #pragma unroll
             for (int i = 0; i < TILE / LANES; ++i) {
@@ -324,7 +324,7 @@ __global__ __launch_bounds__(TILE) void k_tiles(const double *__restrict__ x, in
             const int sub = tid % (TILE / SUB), kk = tid / (TILE / SUB);
             if (kk < D) {
                 double lo = INFINITY, hi = -INFINITY;
-#pragma unroll 8
+#pragma unroll
                 for (int i = 0; i < SUB; ++i) {
                     // rotated by the eighth: its 8 lanes of a coordinate read other banks
                     const double v = s_v[kk][sub * SUB + ((i + 2 * sub) & (SUB - 1))];
@@ -332,15 +332,27 @@ __global__ __launch_bounds__(TILE) void k_tiles(const double *__restrict__ x, in
                     hi = fmax(hi, v);
                 }
                 s_ext[sub][kk] = (hi - lo) * (hi - lo);
+                // the eighths' boxes (neighbouring lanes) make those of the halves and
+                // of the tile
+                double *bx = P.box + static_cast<int64_t>(J) * BOX * D + kk;
+#pragma unroll
+                for (int off = 1; off < TILE / SUB; off *= 2) {
+                    if (off == TILE / SUB / 2 && (sub & (off - 1)) == 0) {
+                        bx[(2 + sub / off * 2) * D] = lo;
+                        bx[(3 + sub / off * 2) * D] = hi;
+                    }
+                    lo = fmin(lo, __shfl_xor(lo, off, WAVE));
+                    hi = fmax(hi, __shfl_xor(hi, off, WAVE));
+                }
+                if (sub == 0) {
+                    bx[0] = s_lo[kk] = lo;
+                    bx[D] = s_hi[kk] = hi;
+                }
             }
         }
         __syncthreads();
     }
     if constexpr (D <= 16) {
-        if (tid < D) {
-            P.box[(static_cast<int64_t>(J) * 2 + 0) * D + tid] = s_lo[tid];
-            P.box[(static_cast<int64_t>(J) * 2 + 1) * D + tid] = s_hi[tid];
-        }
         if (tid < TILE / SUB) {
             double d2 = 0.0;
             for (int k = 0; k < D; ++k) d2 += s_ext[tid][k];
