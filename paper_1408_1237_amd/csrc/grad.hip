@@ -10,7 +10,9 @@
 // with D_ij = x_i - x_j in scaled coordinates, and
 //   dl/dx_i = A_i / (sigma^2 c),  dl/dlogs = -1/2 sum_i S_i / (sigma^2 c^2)
 // (c the coordinate scale; lambda == w: c_ij = 2 w_i w_j K_hat_ij, whose 2 w_i is
-// applied once per row).  Precision: FP64 throughout, or FP32 offsets, kernel
+// applied once per row).  The FP32 pass keeps the sums with w and with lambda
+// apart (sum_j w_j K_hat_ij D_ij, the same with lambda_j, and sum_j w_j K_hat_ij
+// ||D_ij||^2) and multiplies by lambda_i and w_i in FP64.  Precision: FP64 throughout, or FP32 offsets, kernel
 // values and sums.  At a solution w of an ill-conditioned system (|w| large with
 // alternating signs) the row sums cancel heavily, so the FP32 gradient carries
 // relative row errors far above FP32 rounding; FP64 is small beside the solve
@@ -41,15 +43,23 @@ struct GArgs {
     const void *off;  // offsets in the pass's precision, SoA
     const void *ws;   // w in sorted order
     const void *ls;   // lambda in sorted order
-    void *parts;      // [splits][n_pad][D + 1]: A_i, S_i of a column range
+    void *parts;      // [splits][n_pad][grad_sums]: A_i, S_i of a column range
 };
+
+// Sums of a row: A_i and S_i; FP32 with lambda != w two vectors and S_i.
+template <typename T>
+__host__ __device__ constexpr int grad_sums(int dpad, bool same) {
+    return sizeof(T) == 8 || same ? dpad + 1 : 2 * dpad + 1;
+}
 
 // VALU form: one lane per target row, sources at wave-uniform addresses (scalar
 // loads).
 
 template <int D, bool SAME, typename T>
 __global__ __launch_bounds__(BLOCK) void k_grad(GArgs a) {
-    constexpr int NA = D + 1;
+    constexpr int NA = grad_sums<T>(D, SAME);
+    constexpr bool TWO = NA > D + 1;      // sums with lambda apart
+    constexpr bool APART = sizeof(T) == 4;  // row factors left to the finish
     constexpr int U = D <= 4 ? 8 : D <= 8 ? 4 : 2;
     using G = GP<T>;
     const T *__restrict__ off = static_cast<const T *>(a.off);
@@ -66,9 +76,12 @@ __global__ __launch_bounds__(BLOCK) void k_grad(GArgs a) {
         oi[k] = off[k * n_pad + i];
     }
     const T wi = wsrc[i], li = lsrc[i];
-    T A[D], S = T(0);
+    T A[D], Al[TWO ? D : 1], S = T(0);
 #pragma unroll
-    for (int k = 0; k < D; ++k) A[k] = T(0);
+    for (int k = 0; k < D; ++k) {
+        A[k] = T(0);
+        if (TWO) Al[k] = T(0);
+    }
     const int J0 = by * a.tps;
     const int J1 = min(a.ntiles, J0 + a.tps);
     for (int J = J0; J < J1; ++J) {
@@ -89,18 +102,26 @@ __global__ __launch_bounds__(BLOCK) void k_grad(GArgs a) {
                     r2 = G::fma(dl[k], dl[k], r2);
                 }
                 const T kv = G::ex2(-r2);
-                const T c = kv * (SAME ? wsrc[j] : G::fma(li, wsrc[j], lsrc[j] * wi));
+                const T c = kv * (SAME || APART ? wsrc[j] : G::fma(li, wsrc[j], lsrc[j] * wi));
                 S = G::fma(c, r2, S);
 #pragma unroll
                 for (int k = 0; k < D; ++k) A[k] = G::fma(c, dl[k], A[k]);
+                if constexpr (TWO) {
+                    const T cl = kv * lsrc[j];
+#pragma unroll
+                    for (int k = 0; k < D; ++k) Al[k] = G::fma(cl, dl[k], Al[k]);
+                }
             }
         }
     }
-    const T f = SAME ? T(2) * wi : T(1);
+    const T f = SAME && !APART ? T(2) * wi : T(1);
     T *out = static_cast<T *>(a.parts) + (static_cast<int64_t>(by) * n_pad + i) * NA;
 #pragma unroll
     for (int k = 0; k < D; ++k) out[k] = f * A[k];
-    out[D] = f * S;
+    if constexpr (TWO)
+#pragma unroll
+        for (int k = 0; k < D; ++k) out[D + k] = Al[k];
+    out[NA - 1] = f * S;
 }
 
 // FP64 matrix-core form, compiled dimensions 12 and 16.  Both contractions of a
@@ -328,28 +349,35 @@ __device__ __forceinline__ T gwave_sum(T v) {
     return v;
 }
 
-// gx[p_i, k] = A_ik / (sigma^2 c), the column ranges added in order; sums S_i and
-// lambda_p w_p over the rows (last block writes the two scalars).  One thread per
-// (row, k) entry of the [row][D + 1] partial sums, so the reads run along memory
+// gx[p_i, k] = A_ik / (sigma^2 c) (FP32: lambda_i and w_i times the row's two sums),
+// the column ranges added in order; sums S_i (lambda_i S_i) and lambda_p w_p over the
+// rows (last block writes the two scalars).  One thread per (row, k) entry, so the reads run along memory
 // (one row per thread walking its 2 D + 1 entries took 614 us at N = 50,000,
 // d = 16).
 template <typename T>
 __global__ __launch_bounds__(BLOCK) void k_grad_finish(int64_t n, int64_t n_pad, int d, int dpad, int splits,
-                                                       const int32_t *__restrict__ perm,
+                                                       bool same, const int32_t *__restrict__ perm,
                                                        const T *__restrict__ parts, const double *__restrict__ lam,
                                                        const double *__restrict__ w, double inv_s2c,
                                                        double inv_s2c2, double gamma, double *gx, double *g_ls,
                                                        double *g_lg, double *partials, unsigned *counter) {
-    const int NA = dpad + 1;
+    constexpr bool APART = sizeof(T) == 4;
+    const int ne = dpad + 1, NA = grad_sums<T>(dpad, same);
     double accS = 0.0, accG = 0.0;
-    for (int64_t e = blockIdx.x * static_cast<int64_t>(BLOCK) + threadIdx.x; e < n * NA;
+    for (int64_t e = blockIdx.x * static_cast<int64_t>(BLOCK) + threadIdx.x; e < n * ne;
          e += static_cast<int64_t>(gridDim.x) * BLOCK) {
-        const int64_t i = e / NA;
-        const int k = static_cast<int>(e - i * NA);
+        const int64_t i = e / ne;
+        const int k = static_cast<int>(e - i * ne);
         if (k >= d && k < dpad) continue;
-        double s = 0.0;
-        for (int u = 0; u < splits; ++u) s += static_cast<double>(parts[static_cast<int64_t>(u) * n_pad * NA + e]);
         const int64_t p = perm[i];
+        auto sum = [&](int c) {
+            double v = 0.0;
+            for (int u = 0; u < splits; ++u)
+                v += static_cast<double>(parts[(static_cast<int64_t>(u) * n_pad + i) * NA + c]);
+            return v;
+        };
+        double s = sum(k < d ? k : NA - 1);
+        if constexpr (APART) s = k < d ? lam[p] * s + w[p] * (same ? s : sum(dpad + k)) : lam[p] * s;
         if (k < d) {
             gx[p * d + k] = s * inv_s2c;
         } else {
@@ -389,7 +417,7 @@ __global__ __launch_bounds__(BLOCK) void k_grad_finish(int64_t n, int64_t n_pad,
     s0 = gwave_sum(s0);
     s1 = gwave_sum(s1);
     if (threadIdx.x != 0) return;
-    *g_ls = -0.5 * s0 * inv_s2c2;
+    *g_ls = (APART ? -1.0 : -0.5) * s0 * inv_s2c2;
     *g_lg = -gamma * s1;
     *counter = 0u;
 }
@@ -443,7 +471,7 @@ static hipError_t grad_pass(const Prepared &P, double sigma, double gamma, const
     const int mx = (P.ntiles / 2 > 1 ? (P.ntiles / 2 < 32 ? P.ntiles / 2 : 32) : 1);
     Carver cv(scratch);
     GArgs a;
-    T *parts = cv.take<T>(static_cast<size_t>(mx) * P.n_pad * (P.dpad + 1));
+    T *parts = cv.take<T>(static_cast<size_t>(mx) * P.n_pad * grad_sums<T>(P.dpad, same));
     T *ls = cv.take<T>(P.n_pad);
     T *wsv = cv.take<T>(P.n_pad);
     double *partials = cv.take<double>(2 * VEC_BLOCKS);
@@ -484,7 +512,7 @@ static hipError_t grad_pass(const Prepared &P, double sigma, double gamma, const
     const double c = P.scale;
     const double s2 = sigma * sigma;
     hipLaunchKernelGGL(k_grad_finish<T>, dim3(vec_blocks(P.n_pad * (P.dpad + 1))), dim3(BLOCK), 0, s, P.n, P.n_pad, P.d, P.dpad,
-                       a.splits, P.perm, parts, lam, w, 1.0 / (s2 * c), 1.0 / (s2 * c * c), gamma,
+                       a.splits, same, P.perm, parts, lam, w, 1.0 / (s2 * c), 1.0 / (s2 * c * c), gamma,
                        gx, g_ls, g_lg, partials, counter);
     return hipGetLastError();
 }

@@ -3025,7 +3025,8 @@ static bool use_sym_kernel(const Prepared &P, int prec) {
     // (N = 1e5: 4-10 % at d = 4-12, 15 % on the kriging shape, 20 % on the
     // clustered one); at 16 only with groups of at least 8 tiles (N above
     // about 180,000: 8 % at N = 2e5), where a row unit meets enough column
-    // tiles to repay its set-up (N = 1e5, groups of 4: 11 % slower)
+    // tiles to repay its set-up (N = 1e5, groups of 4: 1.62 ms in either
+    // form; N = 50,000, groups of 2: 2 % slower)
     // Matern-3/2 (FP32 / BF16): at every compiled dimension up to 16, groups of
     // 4 tiles included (its pair costs more: N = 1e5, 1.26-1.41x at d = 3-12,
     // 1.14x at d = 16; N = 2e5, d = 16: 1.24x); FP64: see k_kmvp_ms
