@@ -40,6 +40,8 @@ struct GArgs {
     int64_t n, n_pad;
     int ntiles, nrowblocks, splits, tps;
     const double *anchor;
+    const double *tile_r2;
+    double above;     // VALU form: row tiles of R^2 > above (-1: all)
     const void *off;  // offsets in the pass's precision, SoA
     const void *ws;   // w in sorted order
     const void *ls;   // lambda in sorted order
@@ -53,8 +55,7 @@ __host__ __device__ constexpr int grad_sums(int dpad, bool same) {
 }
 
 // VALU form: one lane per target row, sources at wave-uniform addresses (scalar
-// loads).
-
+// loads); explicit differences.
 template <int D, bool SAME, typename T>
 __global__ __launch_bounds__(BLOCK) void k_grad(GArgs a) {
     constexpr int NA = grad_sums<T>(D, SAME);
@@ -67,6 +68,7 @@ __global__ __launch_bounds__(BLOCK) void k_grad(GArgs a) {
     const T *__restrict__ lsrc = static_cast<const T *>(a.ls);
     const int64_t n_pad = a.n_pad;
     const int bx = blockIdx.x % a.nrowblocks, by = blockIdx.x / a.nrowblocks;
+    if (a.tile_r2[bx] <= a.above) return;
     const int64_t i = static_cast<int64_t>(bx) * BLOCK + threadIdx.x;
     double aI[D];
     T oi[D];
@@ -131,15 +133,31 @@ __global__ __launch_bounds__(BLOCK) void k_grad(GArgs a) {
 // coordinates as the 16 columns of B).  All coordinates are taken from the row
 // tile's anchor, x' = x - a_I (sources shifted when they are staged, |o'|^2 =
 // e0 + e1 in the two halves the staging threads hold), so the target operand is
-// built once per block and A_i = t'_i sum_j c_ij - sum_j c_ij o'_j; the pairs
-// that matter are within a few scaled units of the row tile, whose offsets stay
-// as short.  The VALU does the table exponential and the coefficient.  A pair
-// costs no subtraction and no fused multiply-add per coordinate: at N = 50,000,
-// d = 16 the pass took 7.7 ms in the VALU form with lambda and w summed apart.
+// built once per block and A_i = t'_i sum_j c_ij - sum_j c_ij o'_j.  The VALU does
+// the table exponential and the coefficient.  A pair costs no subtraction and no
+// fused multiply-add per coordinate: at N = 50,000, d = 16 the pass took 7.7 ms in
+// the VALU form with lambda and w summed apart.
+//
+// The expanded distance carries an absolute error of a few 2^-53 |t'|^2, whatever
+// the distance.  So a row tile takes this form only up to R^2 = MG_R2 (its
+// own |t'|^2; the sources that matter are within a few scaled units of it), and
+// pairs closer than r^2 = MG_NEAR, whose r^2 would lose its relative accuracy, are
+// formed again from their differences (rare: the wave looks at the smallest of its
+// 512 exponents); wider row tiles are left to k_grad.  Relative error of gx
+// against the explicit form's, N about 1000:
+//   N(0, I), d = 9-16, R^2 2-4.6: 6.6e-16 - 1.0e-15, against 6.8e-16 - 1.2e-15
+//   (R^2 11-31: 0.9-2.3e-15 against 0.8-1.3e-15: beyond the line);
+//   40 clusters spread by 1e4 (R^2 1e9): 2e-7 against 2e-12 without the line.
 // A wave owns 2 groups of 16 targets, a block 128 rows of a row tile; sources are
 // staged 128 at a time, double-buffered (45 KB, two blocks per CU by registers).
 typedef double gdx4 __attribute__((ext_vector_type(4)));
 typedef double gdx2 __attribute__((ext_vector_type(2)));
+
+constexpr double MG_R2 = 4.0;
+constexpr double MG_NEAR = 1.0 / 64.0;
+__device__ __forceinline__ unsigned high_word(double v) {
+    return static_cast<unsigned>(__builtin_bit_cast(unsigned long long, v) >> 32);
+}
 
 template <int D, bool SAME>
 __global__ __launch_bounds__(BLOCK, 2) void k_grad_mg(GArgs a) {
@@ -159,6 +177,7 @@ __global__ __launch_bounds__(BLOCK, 2) void k_grad_mg(GArgs a) {
     const int nrb = 2 * a.nrowblocks;
     const int bh = blockIdx.x % nrb, by = blockIdx.x / nrb;
     const int I = bh / 2;
+    if (!(a.tile_r2[I] <= MG_R2)) return;
     const int tid = threadIdx.x, lane = tid % WAVE, r16 = lane % 16, g = lane / 16;
     // source of A row r16, so that lane l's four exponents are sources 4 g + v
     const int asrc = (r16 % 4) * 4 + r16 / 4;
@@ -201,14 +220,16 @@ __global__ __launch_bounds__(BLOCK, 2) void k_grad_mg(GArgs a) {
         if (shalf == 0) st_w = wsrc[j];
         if (!SAME && shalf == 1) st_l = lsrc[j];
     };
-    auto stage_store = [&](int buf) {
+    auto stage_store = [&](int ci, int buf) {
+        const int64_t j = static_cast<int64_t>(ci) * SC + scol;
         double e = 0.0;
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
             s_o[buf][shalf * PER + k][scol] = st_o[k];
             e = __builtin_fma(st_o[k], st_o[k], e);
         }
-        s_e[buf][shalf][scol] = -e;
+        // the padding, which would lie at its tile's anchor, goes far away
+        s_e[buf][shalf][scol] = j < a.n ? -e : -e - 1e6;
         if (shalf == 0) s_w[buf][scol] = st_w;
         if (!SAME && shalf == 1) s_l[SAME ? 0 : buf][scol] = st_l;
     };
@@ -222,7 +243,7 @@ __global__ __launch_bounds__(BLOCK, 2) void k_grad_mg(GArgs a) {
     const int C0 = by * a.tps * CPT, C1 = min(a.ntiles, (by + 1) * a.tps) * CPT;
     if (C0 < C1) {
         stage_load(C0);
-        stage_store(0);
+        stage_store(C0, 0);
     }
     __syncthreads();
     for (int ci = C0; ci < C1; ++ci) {
@@ -243,11 +264,45 @@ __global__ __launch_bounds__(BLOCK, 2) void k_grad_mg(GArgs a) {
                     G[rg] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[kc], bval[rg][kc], G[rg], 0, 0, 0);
             }
         };
+        // x > -TN MG_NEAR (and x > 0, from rounding): high words below that of the
+        // bound, as unsigned numbers
+        constexpr unsigned NEAR_HI = 0xC0100000u;  // of -4.0
+        static_assert(TN * MG_NEAR == 4.0, "NEAR_HI");
+        auto near_pairs = [&](auto diag_c, int st, gdx4 (&G)[RG]) {
+            auto near = [&](int rg, int v) {
+                const int64_t j = static_cast<int64_t>(ci) * SC + st + 4 * g + v;
+                return high_word(G[rg][v]) < NEAR_HI && !(decltype(diag_c)::value && j == row0 + rg * 16 + r16);
+            };
+            bool any = false;
+            if constexpr (decltype(diag_c)::value) {
+#pragma unroll
+                for (int e = 0; e < 4 * RG; ++e) any = any || near(e / 4, e % 4);
+            } else {
+                unsigned least = high_word(G[0][0]);
+#pragma unroll
+                for (int e = 1; e < 4 * RG; ++e) least = min(least, high_word(G[e / 4][e % 4]));
+                any = least < NEAR_HI;
+            }
+            if (__builtin_expect(__ballot(any) == 0, 1)) return;
+#pragma unroll
+            for (int e = 0; e < 4 * RG; ++e) {
+                const int rg = e / 4, v = e % 4;
+                if (!near(rg, v)) continue;
+                double r2 = 0.0;
+#pragma unroll 1
+                for (int k = 0; k < D; ++k) {
+                    const double dl = off[k * n_pad + row0 + rg * 16 + r16] - s_o[buf][k][st + 4 * g + v];
+                    r2 = __builtin_fma(dl, dl, r2);
+                }
+                G[rg][v] = -TN * r2;
+            }
+        };
         // DIAG: the chunk holds the rows' own points, whose D_ii = 0 adds nothing;
         // their (largest) coefficient is left out so that it does not have to cancel
         // between t'_i sum c and sum c o'
-        auto accumulate = [&](auto diag_c, int st, const gdx4 (&G)[RG]) {
+        auto accumulate = [&](auto diag_c, int st, gdx4 (&G)[RG]) {
             constexpr bool DIAG = decltype(diag_c)::value;
+            near_pairs(diag_c, st, G);
             // this lane's sources 4 g + v: weights, and coordinate r16 for the second contraction
             double wv[4], lv[4], ov[4];
 #pragma unroll
@@ -303,7 +358,7 @@ __global__ __launch_bounds__(BLOCK, 2) void k_grad_mg(GArgs a) {
             chunk(std::true_type{});
         else
             chunk(std::false_type{});
-        if (ci + 1 < C1) stage_store(buf ^ 1);
+        if (ci + 1 < C1) stage_store(ci + 1, buf ^ 1);
         __syncthreads();
     }
     // A_i = t'_i C_i - sum c o'; accumulator lane l: target g + 4 v, coordinate r16
@@ -448,19 +503,24 @@ static hipError_t launch_grad(const GArgs &a, bool same, hipStream_t s) {
     // FP64 at the compiled dimensions 12 and 16: below, the matrix-core form's 16
     // coordinate columns and padded slots cost more than the VALU's d subtractions
     // and 2 d fused multiply-adds; above 16 its operands do not fit.  FP32 stays on
-    // the VALU, which keeps D_ij = x_i - x_j itself in FP32.
+    // the VALU, which keeps D_ij = x_i - x_j itself in FP32.  The wide row tiles are
+    // a launch of their own (its blocks return at once on compact ones; inside the
+    // matrix-core kernel, at 2 waves per SIMD, they took 2.5 times as long).
+    GArgs v = a;
+    v.above = -1.0;
     if constexpr (sizeof(T) == 8 && (D == 12 || D == 16)) {
+        v.above = MG_R2;
         const dim3 g(2 * a.nrowblocks * a.splits);
         if (same)
             hipLaunchKernelGGL((k_grad_mg<D, true>), g, dim3(BLOCK), 0, s, a);
         else
             hipLaunchKernelGGL((k_grad_mg<D, false>), g, dim3(BLOCK), 0, s, a);
-        return hipGetLastError();
+        KRR_HIP(hipGetLastError());
     }
     if (same)
-        hipLaunchKernelGGL((k_grad<D, true, T>), dim3(a.nrowblocks * a.splits), dim3(BLOCK), 0, s, a);
+        hipLaunchKernelGGL((k_grad<D, true, T>), dim3(a.nrowblocks * a.splits), dim3(BLOCK), 0, s, v);
     else
-        hipLaunchKernelGGL((k_grad<D, false, T>), dim3(a.nrowblocks * a.splits), dim3(BLOCK), 0, s, a);
+        hipLaunchKernelGGL((k_grad<D, false, T>), dim3(a.nrowblocks * a.splits), dim3(BLOCK), 0, s, v);
     return hipGetLastError();
 }
 
@@ -484,6 +544,7 @@ static hipError_t grad_pass(const Prepared &P, double sigma, double gamma, const
     a.tps = (P.ntiles + splits_req - 1) / splits_req;
     a.splits = (P.ntiles + a.tps - 1) / a.tps;
     a.anchor = P.anchor;
+    a.tile_r2 = P.tile_r2;
     a.off = sizeof(T) == 8 ? static_cast<const void *>(P.off64) : static_cast<const void *>(P.off32);
     a.ws = wsv;
     a.ls = ls;
