@@ -41,7 +41,8 @@ struct GArgs {
     int ntiles, nrowblocks, splits, tps;
     const double *anchor;
     const double *tile_r2;
-    double above;     // VALU form: row tiles of R^2 > above (-1: all)
+    const double *box;  // tile boxes (krr_internal.h)
+    bool rest;          // VALU form: only the row tiles that mg_tile refuses
     const void *off;  // offsets in the pass's precision, SoA
     const void *ws;   // w in sorted order
     const void *ls;   // lambda in sorted order
@@ -52,6 +53,17 @@ struct GArgs {
 template <typename T>
 __host__ __device__ constexpr int grad_sums(int dpad, bool same) {
     return sizeof(T) == 8 || same ? dpad + 1 : 2 * dpad + 1;
+}
+
+// Row tiles up to this R^2, all coordinates finite, take the matrix-core form.
+constexpr double MG_R2 = 4.0;
+template <int D>
+__device__ __forceinline__ bool finite_tile(const GArgs &a, int J) {
+    return a.box[static_cast<int64_t>(J) * BOX * D] != -INFINITY;
+}
+template <int D>
+__device__ __forceinline__ bool mg_tile(const GArgs &a, int I) {
+    return a.tile_r2[I] <= MG_R2 && finite_tile<D>(a, I);
 }
 
 // VALU form: one lane per target row, sources at wave-uniform addresses (scalar
@@ -68,7 +80,7 @@ __global__ __launch_bounds__(BLOCK) void k_grad(GArgs a) {
     const T *__restrict__ lsrc = static_cast<const T *>(a.ls);
     const int64_t n_pad = a.n_pad;
     const int bx = blockIdx.x % a.nrowblocks, by = blockIdx.x / a.nrowblocks;
-    if (a.tile_r2[bx] <= a.above) return;
+    if (a.rest && mg_tile<D>(a, bx)) return;
     const int64_t i = static_cast<int64_t>(bx) * BLOCK + threadIdx.x;
     double aI[D];
     T oi[D];
@@ -153,7 +165,6 @@ __global__ __launch_bounds__(BLOCK) void k_grad(GArgs a) {
 typedef double gdx4 __attribute__((ext_vector_type(4)));
 typedef double gdx2 __attribute__((ext_vector_type(2)));
 
-constexpr double MG_R2 = 4.0;
 constexpr double MG_NEAR = 1.0 / 64.0;
 __device__ __forceinline__ unsigned high_word(double v) {
     return static_cast<unsigned>(__builtin_bit_cast(unsigned long long, v) >> 32);
@@ -177,7 +188,7 @@ __global__ __launch_bounds__(BLOCK, 2) void k_grad_mg(GArgs a) {
     const int nrb = 2 * a.nrowblocks;
     const int bh = blockIdx.x % nrb, by = blockIdx.x / nrb;
     const int I = bh / 2;
-    if (!(a.tile_r2[I] <= MG_R2)) return;
+    if (!mg_tile<D>(a, I)) return;
     const int tid = threadIdx.x, lane = tid % WAVE, r16 = lane % 16, g = lane / 16;
     // source of A row r16, so that lane l's four exponents are sources 4 g + v
     const int asrc = (r16 % 4) * 4 + r16 / 4;
@@ -354,6 +365,8 @@ __global__ __launch_bounds__(BLOCK, 2) void k_grad_mg(GArgs a) {
                 accumulate(diag_c, st + 16, G1);
             }
         };
+        // the clamp of x below hides a NaN distance, whose r^2 belongs into S
+        if (!finite_tile<D>(a, ci / CPT)) S[0] = S[1] = NAN;
         if (ci / CPT == I)
             chunk(std::true_type{});
         else
@@ -507,9 +520,9 @@ static hipError_t launch_grad(const GArgs &a, bool same, hipStream_t s) {
     // a launch of their own (its blocks return at once on compact ones; inside the
     // matrix-core kernel, at 2 waves per SIMD, they took 2.5 times as long).
     GArgs v = a;
-    v.above = -1.0;
+    v.rest = false;
     if constexpr (sizeof(T) == 8 && (D == 12 || D == 16)) {
-        v.above = MG_R2;
+        v.rest = true;
         const dim3 g(2 * a.nrowblocks * a.splits);
         if (same)
             hipLaunchKernelGGL((k_grad_mg<D, true>), g, dim3(BLOCK), 0, s, a);
@@ -545,6 +558,7 @@ static hipError_t grad_pass(const Prepared &P, double sigma, double gamma, const
     a.splits = (P.ntiles + a.tps - 1) / a.tps;
     a.anchor = P.anchor;
     a.tile_r2 = P.tile_r2;
+    a.box = P.box;
     a.off = sizeof(T) == 8 ? static_cast<const void *>(P.off64) : static_cast<const void *>(P.off32);
     a.ws = wsv;
     a.ls = ls;

@@ -145,8 +145,10 @@ __device__ __forceinline__ bool tiles_far(const double (&aI)[D], double rI, cons
 // Gaussian argument is at most -d2 + |o|^2 - N_J <= -d2 + R2_J / 2 + 1), nor when
 // it is negligible (krr_internal.h).  d2: squared gap of the tiles' boxes.  For
 // Matern, -log2 k = log2(e) s - log2(1 + s) >= 1.2624 s - 1.74 (the tangent of the
-// concave log2(1 + s) at s = 7).  One thread per pair, a block's pairs at once:
-// the test is one round trip to memory.
+// concave log2(1 + s) at s = 7).  A tile is live against itself (d2 = 0, and the two
+// differences in need add up to at least 0), and one with a non-finite coordinate
+// against every tile (unbounded boxes: d2 = 0), so that a NaN reaches every row.
+// One thread per pair, a block's pairs at once: the test is one round trip to memory.
 template <int D, bool MAT, bool F64>
 __device__ __forceinline__ bool gap_live(const KArgs &a, int I, int J, const double *bi, const double *bj) {
     const int need = max(a.up[J] - a.lo[I], a.up[I] - a.lo[J]) + a.clear;

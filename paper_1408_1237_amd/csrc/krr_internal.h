@@ -155,7 +155,8 @@ struct Prepared {
     void *slot32 = nullptr;
     void *slot16 = nullptr;
     // per tile, dpad <= 16 (the symmetric products): the bounding boxes of it and of
-    // its two halves in scaled coordinates ([tile][BOX][dpad]) and, per 32 points of it,
+    // its two halves in scaled coordinates ([tile][BOX][dpad]; -inf .. inf where the
+    // tile holds a non-finite coordinate) and, per 32 points of it,
     // the ceiling of -log2 of the kernel across their box (neglog2_kernel; -1: no points)
     double *box = nullptr;
     int *sub_reach = nullptr;  // [tile][8]

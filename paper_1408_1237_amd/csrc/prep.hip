@@ -295,6 +295,15 @@ __global__ __launch_bounds__(TILE) void k_tiles(const double *__restrict__ x, in
     double xr[D];  // the point's coordinates, unscaled (0 beyond d and on the padding)
 #pragma unroll
     for (int t = 0; t < D; ++t) xr[t] = (real && t < d) ? x[static_cast<int64_t>(idx) * d + t] : 0.0;
+    // the minima and maxima below pass a NaN over (the anchor is that of the finite
+    // points); a tile with a non-finite coordinate stores unbounded boxes
+    bool unbounded = false;
+    if constexpr (D <= 16) {
+        int nf = 0;
+#pragma unroll
+        for (int t = 0; t < D; ++t) nf |= isfinite(xr[t] * scale) ? 0 : 1;
+        unbounded = __syncthreads_or(nf) != 0;
+    }
 #pragma unroll
     for (int c0 = 0; c0 < D; c0 += CH) {
 #pragma unroll
@@ -338,15 +347,17 @@ __global__ __launch_bounds__(TILE) void k_tiles(const double *__restrict__ x, in
 #pragma unroll
                 for (int off = 1; off < TILE / SUB; off *= 2) {
                     if (off == TILE / SUB / 2 && (sub & (off - 1)) == 0) {
-                        bx[(2 + sub / off * 2) * D] = lo;
-                        bx[(3 + sub / off * 2) * D] = hi;
+                        bx[(2 + sub / off * 2) * D] = unbounded ? -INFINITY : lo;
+                        bx[(3 + sub / off * 2) * D] = unbounded ? INFINITY : hi;
                     }
                     lo = fmin(lo, __shfl_xor(lo, off, WAVE));
                     hi = fmax(hi, __shfl_xor(hi, off, WAVE));
                 }
                 if (sub == 0) {
-                    bx[0] = s_lo[kk] = lo;
-                    bx[D] = s_hi[kk] = hi;
+                    s_lo[kk] = lo;
+                    s_hi[kk] = hi;
+                    bx[0] = unbounded ? -INFINITY : lo;
+                    bx[D] = unbounded ? INFINITY : hi;
                 }
             }
         }
