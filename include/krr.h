@@ -23,7 +23,8 @@
  *  - Work is enqueued on `stream` (a hipStream_t; NULL is the default stream).
  *    The product and gradient calls are asynchronous.  The solvers read small
  *    status words back from the device (one per outer step, or per group of CG
- *    iterations) and therefore synchronise `stream`.
+ *    iterations) and therefore synchronise `stream`, and no other stream; their
+ *    page-locked host copies are one array of a few KB that the process keeps.
  *  - Return values: KRR_OK (0); positive values mean the call completed with
  *    a result but not the requested one (KRR_NOT_CONVERGED: the best iterate is
  *    in the output; KRR_BREAKDOWN: a non-positive curvature or non-finite value

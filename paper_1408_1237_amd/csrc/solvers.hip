@@ -9,6 +9,7 @@
 // outer step (FGMRES: while the device is already in the next step's inner solve)
 // or per group of iterations (plain CG).
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 
@@ -179,20 +180,63 @@ struct StepTimer {
 };
 
 // Page-locked host copy of the status block, so that reading it does not hold up
-// what is enqueued after the copy.  Null where page-locked memory cannot be had.
-struct HostStatus {
-    StatusBlock *p = nullptr;
-    HostStatus() {
-        if (hipHostMalloc(reinterpret_cast<void **>(&p), sizeof(StatusBlock), hipHostMallocDefault) != hipSuccess) {
-            (void)hipGetLastError();
-            p = nullptr;
-        }
+// what is enqueued after the copy: a slot of one small array that the process
+// makes at its first solve and keeps.  (Allocated and freed by each solve, the
+// free waited for everything enqueued on the device's other streams: a solve of
+// 0.13 s beside 2 s of another stream's work returned after 1.9 s.)  Null when
+// every slot is in use or page-locked memory cannot be had.
+class HostStatus {
+public:
+    explicit HostStatus(hipStream_t s) : s_(s) {
+        StatusBlock *base = slots();
+        for (int k = 0; base != nullptr && k < SLOTS; ++k)
+            if (!busy_[k].exchange(true)) {
+                p_ = base + k;
+                k_ = k;
+                return;
+            }
     }
     ~HostStatus() {
-        if (p) (void)hipHostFree(p);
+        if (p_ == nullptr) return;
+        if (pending_) (void)hipStreamSynchronize(s_);  // left on an error: the copy may still land
+        busy_[k_].store(false);
     }
     HostStatus(const HostStatus &) = delete;
     HostStatus &operator=(const HostStatus &) = delete;
+    bool ok() const { return p_ != nullptr; }
+    // copies the status and records e after it; read waits for e
+    hipError_t copy(const StatusBlock *d, hipEvent_t e) {
+        pending_ = true;
+        KRR_HIP(hipMemcpyAsync(p_, d, sizeof(StatusBlock), hipMemcpyDeviceToHost, s_));
+        return hipEventRecord(e, s_);
+    }
+    hipError_t read(hipEvent_t e, StatusBlock &st) {
+        KRR_HIP(hipEventSynchronize(e));
+        pending_ = false;
+        st = *p_;
+        return hipSuccess;
+    }
+
+private:
+    static constexpr int SLOTS = 32;
+    static inline std::atomic<bool> busy_[SLOTS] = {};
+    static StatusBlock *slots() {
+        static StatusBlock *const base = [] {
+            // allowed also while another thread captures a graph
+            hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+            const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+            void *m = nullptr;
+            if (hipHostMalloc(&m, SLOTS * sizeof(StatusBlock), hipHostMallocPortable) != hipSuccess) m = nullptr;
+            if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
+            if (m == nullptr) (void)hipGetLastError();
+            return static_cast<StatusBlock *>(m);
+        }();
+        return base;
+    }
+    hipStream_t s_;
+    StatusBlock *p_ = nullptr;
+    int k_ = 0;
+    bool pending_ = false;
 };
 
 int fgmres_sorted(const Prepared &P, double gamma, bool x0_zero, const SolverOpts &o, const SolverWork &W,
@@ -205,13 +249,13 @@ int fgmres_sorted(const Prepared &P, double gamma, bool x0_zero, const SolverOpt
     int outer = 0, inner_total = 0, cycles = 0;
     int result = KRR_NOT_CONVERGED;
     StepTimer tm;
-    HostStatus hst;
+    HostStatus hst(s);
     // With the status copied asynchronously the next step's inner solve is
     // enqueued before this step's status is read: the device does not wait for
     // the host (an outer step at N = 2000: 268 -> 235 us).  The inner solve
     // looks at the FGMRES state itself and does nothing once that has stopped.
     // Not under launch timing, which would count the launches of that solve.
-    const bool ahead = hst.p != nullptr && tm.ok && !profiling();
+    const bool ahead = hst.ok() && tm.ok && !profiling();
 
     KRR_HIP_STATUS(red_init(W.R, s));
     KRR_HIP_STATUS(tune_products(P, W, o.inner != KRR_INNER_NONE, o.inner_prec, s));
@@ -261,14 +305,12 @@ int fgmres_sorted(const Prepared &P, double gamma, bool x0_zero, const SolverOpt
             KRR_HIP_STATUS(fg_arnoldi(o.gs, np, j, m, W.w, W.V, W.hcol, W.hscr, W.H, W.cs, W.sn, W.g, F, W.R, s));
             const bool more = j + 1 < m && outer + 1 < o.max_outer;
             if (ahead) {
-                KRR_HIP_STATUS(hipMemcpyAsync(hst.p, W.status, sizeof(StatusBlock), hipMemcpyDeviceToHost, s));
-                KRR_HIP_STATUS(hipEventRecord(tm.ev[outer & 1][3], s));
+                KRR_HIP_STATUS(hst.copy(W.status, tm.ev[outer & 1][3]));
                 if (more) {
                     tm.mark(outer + 1, 0, s);
                     KRR_HIP_STATUS(inner(j + 1));
                 }
-                KRR_HIP_STATUS(hipEventSynchronize(tm.ev[outer & 1][3]));
-                st = *hst.p;
+                KRR_HIP_STATUS(hst.read(tm.ev[outer & 1][3], st));
             } else {
                 tm.mark(outer, 3, s);
                 KRR_HIP_STATUS(read_status(W.status, st, s));
