@@ -253,10 +253,19 @@ __global__ __launch_bounds__(BLOCK) void k_cg_finish(int64_t n, int64_t n_pad, P
 
 // The whole vector part of a CG iteration on a short vector in one block: Ap from
 // the partial sums, the step length, x, r, r.r, the stop tests and the new
-// direction with its prescale (the kernels above and below, launched three times,
-// cost about 15 us at 2000 points; this one about 6).
+// direction with its prescale, in place of the three launches above and below.
+//
+// One CU reads every slot of the partial sums (the longest tile's count for all,
+// entries past a tile's own count as entry 0), so it pays up to SMALL_CG_BYTES of
+// slots per entry.  A tile of a shared symmetric product has up to tiles + (tiles - 1)
+// (units - 1) of them.  us per iteration, one block / three launches:
+//   FP64, d = 2: 4 tiles (13 slots) 24.2 / 25.3, 5 (17) 26.7 / 25.6, 12 (45) 45.6 / 28.8
+//   FP32, d = 2: 12 tiles (23 slots) 21.8 / 23.2, 13 (25) 22.6 / 22.9, 14 (27) 23.3 / 22.8
+//   d = 20 (a slot per tile): FP32 16 tiles 18.1 / 24.1, FP64 10 28.3 / 29.7, 12 38.7 / 38.4,
+//   14 40.4 / 39.4
 constexpr int SMALL_THREADS = 1024;
 constexpr int64_t SMALL_CG_N = 4096;
+constexpr int SMALL_CG_BYTES = 104;
 __device__ __forceinline__ double small_sum(double v, double *sh) {
     v = wave_sum(v);
     __syncthreads();  // sh may still be read
@@ -666,9 +675,8 @@ hipError_t cg_step(const Prepared &P, int prec, double shift, const CgVecs<T> &c
     const PartSlots slots = kmvp_live_slots(P, prec);
     const T *parts = static_cast<const T *>(sc.parts);
     T *part = reinterpret_cast<T *>(R.partials);
-    // one block up to 4096 entries (16 tiles: 16 slots at most); measured at 2048
-    // and 4096, beyond it one CU's loads of the partial sums take over
-    if (slots.n > 0 && c.n_pad <= SMALL_CG_N) {
+    const int most = slots.n + (P.ntiles - 1) * slots.step;
+    if (most > 0 && most * static_cast<int>(sizeof(T)) <= SMALL_CG_BYTES && c.n_pad <= SMALL_CG_N) {
         hipLaunchKernelGGL(k_cg_small<T>, dim3(1), dim3(SMALL_THREADS), 0, s, static_cast<int>(P.n),
                            static_cast<int>(c.n_pad), slots, parts, c.x, c.r, c.p, c.p16, c.ps, shift, c.S, c.hist,
                            c.hist_cap);
