@@ -9,8 +9,8 @@
 //   A_i = sum_j c_ij D_ij,   S_i = sum_j c_ij ||D_ij||^2,
 // with D_ij = x_i - x_j in scaled coordinates, and
 //   dl/dx_i = A_i / (sigma^2 c),  dl/dlogs = -1/2 sum_i S_i / (sigma^2 c^2)
-// (c the coordinate scale; lambda == w: c_ij = 2 w_i w_j K_hat_ij, whose 2 w_i is
-// applied once per row).  The FP32 pass keeps the sums with w and with lambda
+// (c the coordinate scale; lambda == w: c_ij = 2 w_i w_j K_hat_ij, whose 2 w_i the
+// finish applies, once per row).  The FP32 pass keeps the sums with w and with lambda
 // apart (sum_j w_j K_hat_ij D_ij, the same with lambda_j, and sum_j w_j K_hat_ij
 // ||D_ij||^2) and multiplies by lambda_i and w_i in FP64.  Precision: FP64 throughout, or FP32 offsets, kernel
 // values and sums.  At a solution w of an ill-conditioned system (|w| large with
@@ -89,7 +89,7 @@ __global__ __launch_bounds__(BLOCK) void k_grad(GArgs a) {
         aI[k] = a.anchor[static_cast<int64_t>(bx) * D + k];
         oi[k] = off[k * n_pad + i];
     }
-    const T wi = wsrc[i], li = lsrc[i];
+    const T wi = SAME || APART ? T(0) : wsrc[i], li = SAME || APART ? T(0) : lsrc[i];
     T A[D], Al[TWO ? D : 1], S = T(0);
 #pragma unroll
     for (int k = 0; k < D; ++k) {
@@ -128,14 +128,13 @@ __global__ __launch_bounds__(BLOCK) void k_grad(GArgs a) {
             }
         }
     }
-    const T f = SAME && !APART ? T(2) * wi : T(1);
     T *out = static_cast<T *>(a.parts) + (static_cast<int64_t>(by) * n_pad + i) * NA;
 #pragma unroll
-    for (int k = 0; k < D; ++k) out[k] = f * A[k];
+    for (int k = 0; k < D; ++k) out[k] = A[k];
     if constexpr (TWO)
 #pragma unroll
         for (int k = 0; k < D; ++k) out[D + k] = Al[k];
-    out[NA - 1] = f * S;
+    out[NA - 1] = S;
 }
 
 // FP64 matrix-core form, compiled dimensions 12 and 16.  Both contractions of a
@@ -383,16 +382,15 @@ __global__ __launch_bounds__(BLOCK, 2) void k_grad_mg(GArgs a) {
         c += __shfl_xor(c, 32, WAVE);
         s += __shfl_xor(s, 16, WAVE);
         s += __shfl_xor(s, 32, WAVE);
-        const double f = SAME ? 2.0 * wi[rg] : 1.0;  // of target r16
-        if (g == 0) parts[(row0 + rg * 16 + r16) * NA + D] = f * s * (-1.0 / TN);
+        if (g == 0) parts[(row0 + rg * 16 + r16) * NA + D] = s * (-1.0 / TN);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int it = g + 4 * v;
-            const double ct = __shfl(c, it, WAVE), ft = __shfl(f, it, WAVE);
+            const double ct = __shfl(c, it, WAVE);
             const int64_t i = row0 + rg * 16 + it;
             if (r16 < D) {
                 const double t = off[r16 * n_pad + i];
-                parts[i * NA + r16] = ft * __builtin_fma(t, ct, -acc[rg][v]);
+                parts[i * NA + r16] = __builtin_fma(t, ct, -acc[rg][v]);
             }
         }
     }
@@ -417,7 +415,9 @@ __device__ __forceinline__ T gwave_sum(T v) {
     return v;
 }
 
-// gx[p_i, k] = A_ik / (sigma^2 c) (FP32: lambda_i and w_i times the row's two sums),
+// gx[p_i, k] = A_ik / (sigma^2 c) (FP32: lambda_i and w_i times the row's two sums;
+// FP64 with lambda == w: 2 w_i times the row's sum.  In the pass itself that factor cost
+// 30 more spilled registers at d = 60, N = 25,000 30.9 ms against 25.4),
 // the column ranges added in order; sums S_i (lambda_i S_i) and lambda_p w_p over the
 // rows (last block writes the two scalars).  One thread per (row, k) entry, so the reads run along memory
 // (one row per thread walking its 2 D + 1 entries took 614 us at N = 50,000,
@@ -445,7 +445,10 @@ __global__ __launch_bounds__(BLOCK) void k_grad_finish(int64_t n, int64_t n_pad,
             return v;
         };
         double s = sum(k < d ? k : NA - 1);
-        if constexpr (APART) s = k < d ? lam[p] * s + w[p] * (same ? s : sum(dpad + k)) : lam[p] * s;
+        if constexpr (APART)
+            s = k < d ? lam[p] * s + w[p] * (same ? s : sum(dpad + k)) : lam[p] * s;
+        else if (same)
+            s *= 2.0 * w[p];
         if (k < d) {
             gx[p * d + k] = s * inv_s2c;
         } else {
