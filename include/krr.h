@@ -142,7 +142,9 @@ typedef struct {
     double t_ortho_ms;
     int32_t batch_steps;   /* several systems or columns: outer steps (CG: iterations) the batch ran, else 0 */
     int32_t batch_tiles;   /* several systems or columns: column tiles per work item of the batched
-                              products (autotuned once per process; first dimension class), else 0 */
+                              products for a system of 256 tiles or more (autotuned once per process;
+                              first dimension class; smaller systems are cut into as many items as
+                              256 tiles would be, down to single tiles), else 0 */
 } krr_info;
 
 /* Solver modes of krr_solve. */
@@ -243,8 +245,10 @@ int kmvp_gauss_cross(const krr_points *targets /* host */, const krr_points *sou
  *   *g_loggamma   = -gamma lam^T w
  * gx is n x d row-major double (device); g_logsigma and g_loggamma are single
  * doubles in device memory.  lam may equal w (the case l = y^T K^{-1} y).
- * prec: KRR_FP64 (kernel values, differences and sums in FP64) or KRR_FP32
- * (FP32 pair loop, FP64 epilogue); other values give KRR_EINVAL.  At the
+ * prec: KRR_FP64 (kernel values, differences and sums in FP64; at d = 9 to 16 the
+ * rows of tiles of radius up to 2.3 sigma expand them about the tile's centre, but for
+ * the distances of close pairs) or KRR_FP32 (FP32 pair loop, FP64 epilogue); other
+ * values give KRR_EINVAL.  At the
  * solution of an ill-conditioned system the row sums cancel heavily, so the
  * FP32 pass loses accuracy well beyond FP32 rounding. */
 int kmvp_grad(const krr_points *pts /* host */, double sigma, double gamma, int32_t prec,
@@ -340,7 +344,7 @@ int krr_lanczos_extremes(const double *alpha /* host, k */, const double *beta /
  * kernel).  krr_profile_end() waits for the recorded events and returns, per
  * product precision, the launch count, the summed kernel time and the summed
  * algorithmic pair count (n_targets x n_sources, padding excluded), of which
- * pairs_skipped were in far tile pairs (exactly zero, not evaluated).  At most
+ * pairs_skipped were in tile pairs left out (see below).  At most
  * max_launches launches are recorded (later ones are counted in `dropped`).
  * No device memory is allocated (the skipped-pair counters are a static device
  * array); begin and end synchronise the device.  Not thread-safe. */
@@ -348,8 +352,10 @@ typedef struct {
     int64_t launches;
     double total_ms;
     double pairs;
-    double pairs_skipped; /* of `pairs`, those in tile pairs the product kernels skipped because every
-                             kernel value there is exactly zero in the product's precision (far tiles) */
+    double pairs_skipped; /* of `pairs`, those in tile pairs the product kernels left out: every kernel
+                             value there is exactly zero in the product's precision (far tiles), or, in
+                             square products up to d = 16, all that a row loses is below 2^-40 (FP64
+                             2^-69) of sum_j K_hat_ij |q_j| */
 } krr_profile_entry;
 
 typedef struct {

@@ -1066,7 +1066,7 @@ int batch_setup(BatchRun &R, const krr_points *probs, int nprob, const double *s
             hin[e].col0 = hout[e].col0 = order[e] * Rp;
         }
     };
-    // KRR_BATCH_TPS=k fixes the column tiles per work item
+    // KRR_BATCH_TPS=k fixes the column tiles per work item (as system_tps takes them)
     const char *ftps = std::getenv("KRR_BATCH_TPS");
     const int forced = ftps ? std::max(std::atoi(ftps), kTpsMin) : 0;  // the scratch holds kTpsMin tiles and up
     // the tuned product: the inner one of a flexible solve (on the zeroed FP32

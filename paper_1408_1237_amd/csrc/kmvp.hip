@@ -2927,8 +2927,9 @@ bool use_valu_kernel() {
     const char *v = std::getenv("KRR_KMVP_VALU");
     return v && v[0] == '1';
 }
-// KRR_NO_TILE_SKIP=1 computes far tile pairs too (their terms are exactly zero;
-// used to check that skipping them changes nothing)
+// KRR_NO_TILE_SKIP=1 computes every tile pair (used to check that leaving pairs
+// out changes nothing beyond its bound: the far ones are exactly zero, those that the
+// symmetric products leave out as negligible below 2^-40, FP64 2^-69, of a row)
 static bool use_tile_skip() {
     const char *v = std::getenv("KRR_NO_TILE_SKIP");
     return !(v && v[0] == '1');
