@@ -152,9 +152,10 @@ __global__ __launch_bounds__(BLOCK) void k_grad(GArgs a) {
 // The expanded distance carries an absolute error of a few 2^-53 |t'|^2, whatever
 // the distance.  So a row tile takes this form only up to R^2 = MG_R2 (its
 // own |t'|^2; the sources that matter are within a few scaled units of it), and
-// pairs closer than r^2 = MG_NEAR, whose r^2 would lose its relative accuracy, are
-// formed again from their differences (rare: the wave looks at the smallest of its
-// 512 exponents); wider row tiles are left to k_grad.  Relative error of gx
+// pairs closer than r^2 = R^2 MG_NEAR, whose r^2 would lose its relative accuracy,
+// are formed again from their differences (rare: the wave looks at the smallest of
+// its 512 exponents; a fixed line of 1/64 met every pair of smooth kernels, N = 20,000,
+// d = 12, sigma = 5 sqrt(d) 1.5 ms against 0.8); wider row tiles are left to k_grad.  Relative error of gx
 // against the explicit form's, N about 1000:
 //   N(0, I), d = 9-16, R^2 2-4.6: 6.6e-16 - 1.0e-15, against 6.8e-16 - 1.2e-15
 //   (R^2 11-31: 0.9-2.3e-15 against 0.8-1.3e-15: beyond the line);
@@ -164,7 +165,7 @@ __global__ __launch_bounds__(BLOCK) void k_grad(GArgs a) {
 typedef double gdx4 __attribute__((ext_vector_type(4)));
 typedef double gdx2 __attribute__((ext_vector_type(2)));
 
-constexpr double MG_NEAR = 1.0 / 64.0;
+constexpr double MG_NEAR = 1.0 / 256.0;
 __device__ __forceinline__ unsigned high_word(double v) {
     return static_cast<unsigned>(__builtin_bit_cast(unsigned long long, v) >> 32);
 }
@@ -188,6 +189,9 @@ __global__ __launch_bounds__(BLOCK, 2) void k_grad_mg(GArgs a) {
     const int bh = blockIdx.x % nrb, by = blockIdx.x / nrb;
     const int I = bh / 2;
     if (!mg_tile<D>(a, I)) return;
+    // x > -TN R^2 MG_NEAR (and x > 0, from rounding): high words below that of the
+    // bound, as unsigned numbers
+    const unsigned near_hi = __builtin_amdgcn_readfirstlane(high_word(-TN * MG_NEAR * a.tile_r2[I]));
     const int tid = threadIdx.x, lane = tid % WAVE, r16 = lane % 16, g = lane / 16;
     // source of A row r16, so that lane l's four exponents are sources 4 g + v
     const int asrc = (r16 % 4) * 4 + r16 / 4;
@@ -274,14 +278,10 @@ __global__ __launch_bounds__(BLOCK, 2) void k_grad_mg(GArgs a) {
                     G[rg] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[kc], bval[rg][kc], G[rg], 0, 0, 0);
             }
         };
-        // x > -TN MG_NEAR (and x > 0, from rounding): high words below that of the
-        // bound, as unsigned numbers
-        constexpr unsigned NEAR_HI = 0xC0100000u;  // of -4.0
-        static_assert(TN * MG_NEAR == 4.0, "NEAR_HI");
         auto near_pairs = [&](auto diag_c, int st, gdx4 (&G)[RG]) {
             auto near = [&](int rg, int v) {
                 const int64_t j = static_cast<int64_t>(ci) * SC + st + 4 * g + v;
-                return high_word(G[rg][v]) < NEAR_HI && !(decltype(diag_c)::value && j == row0 + rg * 16 + r16);
+                return high_word(G[rg][v]) < near_hi && !(decltype(diag_c)::value && j == row0 + rg * 16 + r16);
             };
             bool any = false;
             if constexpr (decltype(diag_c)::value) {
@@ -291,7 +291,7 @@ __global__ __launch_bounds__(BLOCK, 2) void k_grad_mg(GArgs a) {
                 unsigned least = high_word(G[0][0]);
 #pragma unroll
                 for (int e = 1; e < 4 * RG; ++e) least = min(least, high_word(G[e / 4][e % 4]));
-                any = least < NEAR_HI;
+                any = least < near_hi;
             }
             if (__builtin_expect(__ballot(any) == 0, 1)) return;
             // every pair of the lane at once: copies of ten points, N = 50,000, d = 16, 5.6 ms
